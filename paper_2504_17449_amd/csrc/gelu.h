@@ -1,0 +1,44 @@
+// GELU(x) = x Phi(x) = max(x, 0) - a Phi(-a) with a = |x|, two ways.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace hmi {
+
+// a Phi(-a) is a smooth bump (at most 0.17, below 1.3e-4 beyond a = 4): Phi(-a) is replaced by a degree-6 polynomial in
+// u = a/2 - 1 on [0, 4], fitted so that |a (Q(u) - Phi(-a))| <= 2e-4 everywhere (a is clamped at 4); GELU(0) = 0 exactly.
+// Ten fp32 vector-ALU operations (40 clocks a wavefront), no transcendental: for the epilogues of large bf16 launches,
+// where the matrix cores wait for it.  (The same polynomial in packed fp16 is 1.5 % of a launch faster, but its rounding
+// lifts the error to 5e-4 near x = -3.8, where the result itself is only -2e-4: not used.)
+__device__ __forceinline__ float gelu_poly(float x) {
+  const float a = fminf(fabsf(x), 4.0f);
+  const float u = fmaf(a, 0.5f, -1.0f);
+  float q = -0.0411399369f;
+  q = fmaf(q, u, 0.0706263031f);
+  q = fmaf(q, u, 0.0492447267f);
+  q = fmaf(q, u, -0.212425632f);
+  q = fmaf(q, u, 0.219460411f);
+  q = fmaf(q, u, -0.108456779f);
+  q = fmaf(q, u, 0.0226731103f);
+  return fmaf(-a, q, fmaxf(x, 0.0f));
+}
+
+// Phi(-a) = exp(-a^2 / 2) t P(t), t = 1 / (1 + 0.3 a): exp(a^2 / 2) Phi(-a) is smooth in t, and the degree-7 P was fitted
+// (least squares, reweighted towards equal relative errors) to 1.5e-7 relative over [0, 14], beyond which exp underflows.
+// fp32 accuracy, in the negative tail too (1.4e-6 relative), where 0.5 x (1 + erf(x / sqrt 2)) cancels; twelve operations
+// and two transcendentals (80 clocks a wavefront; erff takes about twice that).
+__device__ __forceinline__ float gelu_f32(float x) {
+  const float a = fabsf(x);
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.3f, a, 1.0f));
+  float p = 0.03567523509263992f;
+  p = fmaf(p, t, -0.15720497071743011f);
+  p = fmaf(p, t, 0.2063566893339157f);
+  p = fmaf(p, t, -0.053686533123254776f);
+  p = fmaf(p, t, 0.12856313586235046f);
+  p = fmaf(p, t, 0.09991303831338882f);
+  p = fmaf(p, t, 0.12075402587652206f);
+  p = fmaf(p, t, 0.11962929368019104f);
+  const float e = __builtin_amdgcn_exp2f(a * a * -0.72134752044448170f);   // exp(-a^2 / 2)
+  return fmaf(-a * t * p, e, fmaxf(x, 0.0f));
+}
+
+}  // namespace hmi

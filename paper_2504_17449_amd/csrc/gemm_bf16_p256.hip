@@ -36,6 +36,8 @@
 //     row's 256 or 512 contiguous bytes: full-line requests again.
 #include "hmi_kernels.h"
 
+#include "gelu.h"
+
 namespace hmi {
 namespace {
 
@@ -71,25 +73,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   bf16x2 p = {(__bf16)lo, (__bf16)hi};                       // round to nearest even
   return __builtin_bit_cast(uint32_t, p);
-}
-
-// GELU(x) = x Phi(x) = max(x, 0) - a Phi(-a) with a = |x|.  a Phi(-a) is a smooth bump (at
-// most 0.17, below 1.3e-4 beyond a = 4): Phi(-a) is replaced by a degree-6 polynomial in
-// u = a/2 - 1 on [0, 4], fitted so that |a (Q(u) - Phi(-a))| <= 2e-4 everywhere (a is clamped
-// at 4); GELU(0) = 0 exactly.  Ten fp32 vector-ALU operations, no transcendental.  (The same
-// polynomial in packed fp16 is 1.5 % of a launch faster, but its rounding lifts the error to
-// 5e-4 near x = -3.8, where the result itself is only -2e-4: not used.)
-__device__ __forceinline__ float gelu_poly(float x) {
-  const float a = fminf(fabsf(x), 4.0f);
-  const float u = fmaf(a, 0.5f, -1.0f);
-  float q = -0.0411399369f;
-  q = fmaf(q, u, 0.0706263031f);
-  q = fmaf(q, u, 0.0492447267f);
-  q = fmaf(q, u, -0.212425632f);
-  q = fmaf(q, u, 0.219460411f);
-  q = fmaf(q, u, -0.108456779f);
-  q = fmaf(q, u, 0.0226731103f);
-  return fmaf(-a, q, fmaxf(x, 0.0f));
 }
 
 // LDS chunk swizzles (a row is 8 chunks of 16 bytes, two rows per 256-byte bank line).

@@ -21,7 +21,8 @@
 // Same contract as the other grouped GEMMs (GemmArgs / Route), epilogues included.
 #include "hmi_kernels.h"
 
-#include <math.h>
+#include "gelu.h"
+
 
 namespace hmi {
 namespace {
@@ -55,7 +56,8 @@ struct Ring {
   static_assert(LDS_BYTES <= 163840 && 8 * (INFL - 1) < 64, "ring");
 };
 constexpr int kDeepMaxItems = 1024;
-constexpr int kSplitMaxItems = 384;                        // measured: 192 items 25 -> 9 us per launch, 576 and 768 items slower with it
+constexpr int kSplitMaxItems = 256;                        // one round of workgroups: 192 items 25 -> 9 us per launch; 288 items are a second
+                                                           // round (13.6 us, 64 x 64 tiles 12.1)
 
 #define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
@@ -65,7 +67,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   bf16x2 p = {(__bf16)lo, (__bf16)hi};
   return __builtin_bit_cast(uint32_t, p);
 }
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
 // Chunk swizzles of a 128-byte row in LDS (activation rows are read by consecutive lanes, weight rows
 // in the order perm_w: either way the 16 lanes the LDS serves together hit 16 different chunks), and the
@@ -79,7 +80,7 @@ __device__ __forceinline__ int perm_w(int i) { return ((i >> 2) & 1) * 16 + (i >
 // otherwise an item is a whole tile and its wavefront takes the tile's row blocks one after the other
 // (decode steps: nearly every tile holds a single, short row block).
 //
-// SPLIT: the workgroup is KSPLIT wavefronts that share one item (row_split items only); wavefront w
+// SPLIT: the workgroup is KSPLIT wavefronts that share one item (one row block: row_split); wavefront w
 // multiplies the w-th quarter of k.  Everything that decides whether a wavefront leaves early is the same
 // for the whole workgroup, so all of them reach the barrier in front of the sum.
 // WNT: the weights are per-tenant matrices that this launch reads once and the next one does not find in any cache
@@ -209,7 +210,7 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
   }
   if (g.epi == EPI_BIAS_GELU) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = gelu_erf(v[r]);
+    for (int r = 0; r < 16; ++r) v[r] = gelu_f32(v[r]);
   } else if (g.epi == EPI_BIAS_RELU) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = fmaxf(v[r], 0.0f);
@@ -278,11 +279,14 @@ static void launch_ring(const GemmArgs& g, const Route& rt, hipStream_t s, long 
 // 128-row m-tiles and n_mtiles its length, all operands 16-byte aligned (lda, ldc, ldr multiples of 8).
 void launch_gemm_bf16_skinny(const GemmArgs& g, const Route& rt, hipStream_t s) {
   const int row_split = g.n_rows > 32LL * g.n_mtiles ? 1 : 0;
-  const long long n_items = (long long)g.n_mtiles * (g.n_out / SK) * (row_split ? 4 : 1);
+  const long long n_panels = (long long)g.n_mtiles * (g.n_out / SK);
+  const long long n_items = n_panels * (row_split ? 4 : 1);
   if (n_items <= 0) return;
-  // few items, long k: one workgroup per item with k shared by its wavefronts
-  if (row_split && n_items <= kSplitMaxItems && g.k % (64 * KSPLIT) == 0 && g.k >= 64 * KSPLIT * 2)
-    return launch_ring<true, true>(g, rt, s, n_items, row_split);
+  // few items, long k: one workgroup per item with k shared by its wavefronts (an item is always one row block there: of a
+  // tile's four workgroups those without rows leave at once, and are not counted where most tiles are one short row block)
+  const long long n_busy = row_split ? (g.n_rows + SK - 1) / SK * (g.n_out / SK) : n_panels;
+  if (n_busy <= kSplitMaxItems && g.k % (64 * KSPLIT) == 0 && g.k >= 64 * KSPLIT * 2)
+    return launch_ring<true, true>(g, rt, s, n_panels * 4, 1);
   if (n_items <= kDeepMaxItems) return launch_ring<false, true>(g, rt, s, n_items, row_split);
   launch_ring<false, false>(g, rt, s, n_items, row_split);
 }

@@ -56,7 +56,7 @@ void launch_router(const Route& rt, int R, hipStream_t s);
 
 // Per-device set-up of the kernels that need more than the default dynamic LDS: pool creation
 // calls these once per device, with that device current, before any launch on it.
-void init_gemm_bf16_kernels();
+void init_gemm_tile_kernels();
 void init_gemm_bf16_p256_kernels();
 void init_gemm_bf16_skinny_kernels();
 void init_adapter_bf16_kernels();
@@ -86,6 +86,7 @@ struct GemmArgs {
   int n_mtiles_list[2];               // exact m-tile counts of both tile lists, computed on the host
   int which_tiles;                    // set by the launcher: index into Route::tile_* ...
   int n_mtiles;                       // ... and that list's count
+  int gelu_poly;                      // set by the launcher: which form of GELU the tile kernel's epilogue takes (gelu.h)
 };
 
 void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s);

@@ -97,7 +97,7 @@ int device_setup(int device) {
   if (g_device_cus[device] == 0) {
     int n_cu = 0;
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu < 1) return 0;
-    init_gemm_bf16_kernels();
+    init_gemm_tile_kernels();
     init_gemm_bf16_p256_kernels();
     init_gemm_bf16_skinny_kernels();
     init_adapter_bf16_kernels();
