@@ -166,7 +166,7 @@ struct KvArgs {
   uint16_t* cache;     // the layer's lines
   int d, n_heads, max_len;
 };
-void launch_kv_store(const KvArgs& a, const Route& rt, int R, hipStream_t s);
+void launch_kv_store(const KvArgs& a, const Route& rt, int R, int longest, hipStream_t s);   // longest: rows of the longest request
 void launch_attn_decode(const KvArgs& a, const Route& rt, int R, hipStream_t s);
 
 }  // namespace hmi

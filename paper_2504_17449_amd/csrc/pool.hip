@@ -1077,7 +1077,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
         k.qkv = p->w_qkv; k.ctx = p->w_ctx; k.d = d; k.n_heads = c.n_heads; k.max_len = p->kv_max_len;
         k.cache = p->d_kv + (size_t)layer * p->kv_seqs * 2 * (size_t)d * p->kv_max_len;
         ProfSpan ps(p, HMI_KERNEL_ATTENTION);
-        if (kv == KV_PREFILL) launch_kv_store(k, rt, R, s);
+        if (kv == KV_PREFILL) launch_kv_store(k, rt, R, max_len, s);
         else { launch_attn_decode(k, rt, R, s); return; }
       }
       AttnArgs a{};
