@@ -130,18 +130,19 @@ struct LnArgs {
 };
 void launch_layernorm(const LnArgs& a, const Route& rt, hipStream_t s);
 
-// Per-tenant output heads.  A head image holds kHeadCols class rows of d weights (rows at or
-// beyond the tenant's class count are zero) and then kHeadCols biases, in the storage dtype, so
-// that raw[row, c] = b_t[c] + W_t[c] . h[row] is a grouped GEMM with n_out = kHeadCols and fp32
-// output.  launch_head_select masks raw by the tenant's {n_classes, per_token} (meta), writes the
-// scores [N, max_classes] (optional) and labels[row] = first arg-max (-1: no prediction).
+// Per-tenant output heads.  A head image (indexed by tenant) holds kHeadCols class rows of d weights (rows at or beyond
+// the tenant's class count are zero) and then, at b_off, kHeadCols biases, in the storage dtype; meta is the tenant's
+// {n_classes, per_token}.  Writes labels[row] = first arg-max (-1: no prediction) and the scores [N, max_classes]
+// (optional; -inf where the tenant has no such class or the row no prediction).
 constexpr int kHeadCols = 64;
 struct HeadArgs {
-  const float* raw; float* scores; int32_t* labels;
+  const char* h;                      // [N, d] storage dtype
+  const char* heads; size_t head_stride, b_off;
+  float* scores; int32_t* labels;
   const int32_t* meta;
-  int max_classes;
+  int max_classes, d;
 };
-void launch_head_select(const HeadArgs& a, const Route& rt, int R, hipStream_t s);
+void launch_head(const HeadArgs& a, const Route& rt, int R, int longest, bool bf16, hipStream_t s);   // longest: rows of the longest request
 
 // Per-request multi-head attention on packed qkv [N, 3d] (q | k | v) -> ctx [N, d].
 struct AttnArgs {
@@ -157,7 +158,7 @@ struct PlotArgs {
   const int32_t* frag_ids; const int32_t* tok_off;
   char* x; int d;
 };
-void launch_plot_aggregate(const PlotArgs& a, int R, bool bf16, hipStream_t s);
+void launch_plot_aggregate(const PlotArgs& a, int R, int longest, long long rows, bool bf16, hipStream_t s);
 
 // Key/value cache of one layer: [slot][k | v][head][position][64] bf16.
 struct KvArgs {

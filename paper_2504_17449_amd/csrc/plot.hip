@@ -4,9 +4,14 @@
 // rows and forms, for every token, the sum of its representations in the fragments that contain
 // it divided by their number.
 //
-// One workgroup per request, one wavefront per token in turn; a lane moves 16-byte chunks of the
-// up to three source vectors (third token of the previous fragment, second of its own, first of
-// the next), adds in fp32 and rounds once.  HBM-bound: 3 reads and 1 write of d elements per token.
+// A workgroup takes a few consecutive tokens of one request, a wavefront one of them in turn; a lane moves 16-byte
+// chunks of the up to three source vectors (third token of the previous fragment, second of its own, first of the next),
+// adds in fp32 and rounds once.  HBM-bound: 3 reads and 1 write of d elements per token.
+//
+// How many tokens: the launch reads two request offsets per workgroup over the host link, so a large batch is cut into
+// about two thousand workgroups; a small one gives every wavefront a single token, since it lasts as long as its longest
+// chain of them.  Measured, d = 768 (before: one workgroup per request): 141 tokens of two requests 33 us -> 5, 2 664
+// tokens of 37 requests 43 -> 7, 65 536 tokens of 512 requests 60 -> 56 (7.2 TB/s).
 #include "hmi_kernels.h"
 
 namespace hmi {
@@ -18,7 +23,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float bf2f(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
-constexpr int kIdsInLds = 2048;   // fragment ids of a request kept in LDS (longer requests read the rest from memory)
+constexpr int kMaxTokens = 64;      // tokens a workgroup is given at most
 
 // the (up to) three source vectors of one token and its scale
 struct Sources { const char* s0; const char* s1; const char* s2; float scale; };
@@ -43,30 +48,33 @@ __device__ __forceinline__ void sum_chunk(const Sources& t, char* dst, int c) {
 }
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void plot_aggregate_kernel(PlotArgs a) {
-  __shared__ int ids_s[kIdsInLds];
+__global__ __launch_bounds__(256) void plot_aggregate_kernel(PlotArgs a, int per_wg) {
+  __shared__ int ids_s[kMaxTokens + 2];             // table rows of the fragments of tokens t0 - 1 .. t1, clamped into the table
   constexpr int EPC = BF16 ? 8 : 4;                 // elements per 16-byte chunk
-  const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int start = a.tok_off[r], len = a.tok_off[r + 1] - start;
+  const int t0 = blockIdx.x * per_wg, t1 = min(t0 + per_wg, len);
+  if (t0 >= len) return;
   const int chunks = a.d / EPC;
   const size_t vec = (size_t)a.d * (BF16 ? 2 : 4);  // bytes of one representation
-  // the request's table rows (clamped into the table), read once
-  const int in_lds = min(len, kIdsInLds);
-  for (int i = threadIdx.x; i < in_lds; i += 256) ids_s[i] = min(max(a.frag_ids[start + i], 0), a.n_entries - 1);
+  for (int i = threadIdx.x; i < t1 - t0 + 2; i += 256) {
+    const int t = min(max(t0 - 1 + i, 0), len - 1);
+    ids_s[i] = min(max(a.frag_ids[start + t], 0), a.n_entries - 1);
+  }
   __syncthreads();
-  auto id_at = [&](int j) { return j < in_lds ? ids_s[j] : min(max(a.frag_ids[start + j], 0), a.n_entries - 1); };
   // token i is the third token of fragment i-1, the second of fragment i, the first of fragment i+1
   auto sources = [&](int i) {
+    const int* id = ids_s + (i - t0 + 1);
     Sources t;
-    t.s1 = a.table + ((size_t)id_at(i) * 3 + 1) * vec;
-    t.s0 = i > 0 ? a.table + ((size_t)id_at(i - 1) * 3 + 2) * vec : nullptr;
-    t.s2 = i < len - 1 ? a.table + ((size_t)id_at(i + 1) * 3 + 0) * vec : nullptr;
+    t.s1 = a.table + ((size_t)id[0] * 3 + 1) * vec;
+    t.s0 = i > 0 ? a.table + ((size_t)id[-1] * 3 + 2) * vec : nullptr;
+    t.s2 = i < len - 1 ? a.table + ((size_t)id[1] * 3 + 0) * vec : nullptr;
     t.scale = 1.0f / (float)(1 + (i > 0) + (i < len - 1));
     return t;
   };
   // one wavefront per token in turn, two tokens per trip: their six source vectors are in flight together
-  for (int i = wave; i < len; i += 8) {
-    const bool two = i + 4 < len;
+  for (int i = t0 + wave; i < t1; i += 8) {
+    const bool two = i + 4 < t1;
     const Sources ta = sources(i), tb = sources(two ? i + 4 : i);
     char* da = a.x + (size_t)(start + i) * vec;
     char* db = a.x + (size_t)(start + i + 4) * vec;
@@ -79,10 +87,13 @@ __global__ __launch_bounds__(256) void plot_aggregate_kernel(PlotArgs a) {
 
 }  // namespace
 
-void launch_plot_aggregate(const PlotArgs& a, int R, bool bf16, hipStream_t s) {
+void launch_plot_aggregate(const PlotArgs& a, int R, int longest, long long rows, bool bf16, hipStream_t s) {
   if (R <= 0) return;
-  if (bf16) hipLaunchKernelGGL(plot_aggregate_kernel<true>, dim3(R), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(plot_aggregate_kernel<false>, dim3(R), dim3(256), 0, s, a);
+  int per_wg = 4;
+  while (per_wg < kMaxTokens && rows > 2048LL * per_wg) per_wg *= 2;
+  const dim3 grid((longest + per_wg - 1) / per_wg, R);
+  if (bf16) hipLaunchKernelGGL(plot_aggregate_kernel<true>, grid, dim3(256), 0, s, a, per_wg);
+  else hipLaunchKernelGGL(plot_aggregate_kernel<false>, grid, dim3(256), 0, s, a, per_wg);
 }
 
 }  // namespace hmi

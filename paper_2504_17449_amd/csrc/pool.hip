@@ -171,9 +171,7 @@ struct hmi_pool {
   int32_t* d_head_meta = nullptr;      // [tenant] {n_classes, per_token}
   std::vector<uint8_t> head_loaded;
   std::vector<int32_t> last_distinct;  // tenants of the last routed batch
-  int last_n_mtiles[2] = {0, 0};       // its m-tile counts
-  int last_N = 0;                      // and rows
-  float* w_scores = nullptr;           // [max_tokens, kHeadCols] raw scores
+  int last_max_len = 0;                // its longest request
 
   // key/value cache for decoding (hmi_kv_create): [layer][sequence slot][k | v][head][position][64] bf16
   uint16_t* d_kv = nullptr;
@@ -267,7 +265,6 @@ void free_all(hmi_pool* p) {
   (void)hipFree(p->d_shared);
   (void)hipFree(p->d_heads);
   (void)hipFree(p->d_head_meta);
-  (void)hipFree(p->w_scores);
   (void)hipFree(p->d_kv);
   (void)hipFree(p->d_idx);
   (void)hipFree(p->w_qkv); (void)hipFree(p->w_ctx); (void)hipFree(p->w_hmid);
@@ -483,7 +480,6 @@ static int32_t create_impl(const hmi_pool_config_t* cfg, hmi_pool_t** out) {
     p->head_stride = align_up((size_t)kHeadCols * (c.d_model + 1) * p->esize, kAlign);
     CREATE_TRY(hipMalloc(&p->d_heads, p->head_stride * (size_t)c.max_tenants));
     CREATE_TRY(hipMemset(p->d_heads, 0, p->head_stride * (size_t)c.max_tenants));
-    CREATE_TRY(hipMalloc(&p->w_scores, (size_t)c.max_tokens * kHeadCols * sizeof(float)));
     CREATE_TRY(hipMalloc(&p->d_head_meta, sizeof(int32_t) * 2 * (size_t)c.max_tenants));
     CREATE_TRY(hipMemset(p->d_head_meta, 0, sizeof(int32_t) * 2 * (size_t)c.max_tenants));
     p->head_loaded.assign(c.max_tenants, 0);
@@ -768,20 +764,11 @@ int32_t hmi_head_forward(hmi_pool_t* p, const void* h, float* scores, int32_t* l
   for (int t : p->last_distinct)
     if (!p->head_loaded[t]) return fail(p, HMI_ERR_TENANT, "tenant %d has no output head", t);
   HIP_TRY(p, hipSetDevice(c.device));
-  // raw scores: grouped GEMM over the tenant route of that batch; heads are indexed by tenant, not by slot
-  Route rh = p->rt;
-  rh.seg_slot = p->rt.seg_tenant;
-  GemmArgs g{};
-  g.A = h; g.lda = c.d_model; g.C = p->w_scores; g.ldc = kHeadCols; g.out_f32 = 1;
-  g.pool = p->d_heads; g.slot_stride = p->head_stride;
-  g.w_off = 0; g.b_off = (size_t)kHeadCols * c.d_model * p->esize;
-  g.n_out = kHeadCols; g.k = c.d_model; g.n_rows = p->last_N; g.epi = EPI_BIAS;
-  g.n_mtiles_list[0] = p->last_n_mtiles[0]; g.n_mtiles_list[1] = p->last_n_mtiles[1];
-  g.which_tiles = 0; g.n_mtiles = g.n_mtiles_list[0];
-  if (p->bf16) launch_gemm_bf16(g, rh, p->compute); else launch_gemm_f32(g, rh, p->compute);
   HeadArgs a{};
-  a.raw = p->w_scores; a.scores = scores; a.labels = labels; a.meta = p->d_head_meta; a.max_classes = c.max_classes;
-  launch_head_select(a, p->rt, p->last_R, p->compute);
+  a.h = static_cast<const char*>(h); a.heads = p->d_heads; a.head_stride = p->head_stride;
+  a.b_off = (size_t)kHeadCols * c.d_model * p->esize;
+  a.scores = scores; a.labels = labels; a.meta = p->d_head_meta; a.max_classes = c.max_classes; a.d = c.d_model;
+  launch_head(a, p->rt, p->last_R, p->last_max_len, p->bf16, p->compute);
   HIP_TRY(p, hipGetLastError());
   return HMI_OK;
 }
@@ -794,9 +781,11 @@ int32_t hmi_plot_aggregate(hmi_pool_t* p, const void* table, int32_t n_entries, 
   if (R < 0 || !table || !frag_ids || !seq_lens || !x || n_entries < 1) return fail(p, HMI_ERR_ARG, "null pointer, empty table or negative request count");
   if (R > c.max_requests) return fail(p, HMI_ERR_SHAPE, "%d requests > max_requests %d", R, c.max_requests);
   int64_t N = 0;
+  int longest = 0;
   for (int r = 0; r < R; ++r) {
     if (seq_lens[r] <= 0) return fail(p, HMI_ERR_SHAPE, "seq_lens[%d] = %d", r, seq_lens[r]);
     N += seq_lens[r];
+    longest = std::max(longest, seq_lens[r]);
     if (N > c.max_tokens) return fail(p, HMI_ERR_SHAPE, "batch has more than max_tokens = %d tokens", c.max_tokens);
   }
   HIP_TRY(p, hipSetDevice(c.device));
@@ -810,7 +799,7 @@ int32_t hmi_plot_aggregate(hmi_pool_t* p, const void* table, int32_t n_entries, 
   PlotArgs a{};
   a.table = static_cast<const char*>(table); a.n_entries = n_entries; a.frag_ids = frag_ids; a.tok_off = h;
   a.x = static_cast<char*>(x); a.d = c.d_model;
-  launch_plot_aggregate(a, R, p->bf16, p->compute);
+  launch_plot_aggregate(a, R, longest, N, p->bf16, p->compute);
   HIP_TRY(p, hipEventRecord(p->idx_ev[bi], p->compute));
   HIP_TRY(p, hipGetLastError());
   return HMI_OK;
@@ -987,8 +976,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   HIP_TRY(p, hipEventRecord(p->idx_ev[bi], s));
   p->last_R = R;
   p->last_distinct.assign(p->distinct.begin(), p->distinct.end());   // within the reserved capacity
-  p->last_n_mtiles[0] = n_mtiles[0]; p->last_n_mtiles[1] = n_mtiles[1];
-  p->last_N = (int)N;
+  p->last_max_len = max_len;
 
   const int d = c.d_model, f = c.d_ff;
   const bool f32 = !p->bf16;  // fp32 pools: "storage" and fp32 coincide
