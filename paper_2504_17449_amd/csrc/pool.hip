@@ -25,6 +25,7 @@ using namespace hmi;
 namespace {
 
 constexpr int kRing = 8;
+constexpr int kIdxRing = 16, kIdxMark = 8;   // pinned index buffers, and how many uses share one event (see index_buffer)
 constexpr size_t kAlign = 256;
 constexpr int kArenaImages = 32;  // pinned host images per hipHostMalloc call
 constexpr int kMaxTenantIds = 1 << 24;   // tenant id space of one pool
@@ -148,9 +149,9 @@ struct hmi_pool {
   int stage_i = 0;
 
   // per-call index staging (pinned) and device index arrays
-  int32_t* h_idx[4] = {};
-  hipEvent_t idx_ev[4] = {};
-  int idx_i = 0;
+  int32_t* h_idx = nullptr;   // kIdxRing of them, 5 * max_requests + 1 apart
+  hipEvent_t idx_ev[kIdxRing / kIdxMark] = {};
+  uint64_t idx_use = 0;
   int32_t* d_idx = nullptr;   // all device int32 routing arrays, one allocation
   Route rt{};
   int last_R = 0;
@@ -275,15 +276,29 @@ void free_all(hmi_pool* p) {
     if (p->stage[i]) (void)hipHostFree(p->stage[i]);
     if (p->stage_ev[i]) (void)hipEventDestroy(p->stage_ev[i]);
   }
-  for (int i = 0; i < 4; ++i) {
-    if (p->h_idx[i]) (void)hipHostFree(p->h_idx[i]);
-    if (p->idx_ev[i]) (void)hipEventDestroy(p->idx_ev[i]);
-  }
+  if (p->h_idx) (void)hipHostFree(p->h_idx);
+  for (auto e : p->idx_ev) if (e) (void)hipEventDestroy(e);
   for (auto& sp : p->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
   p->fwd_done.destroy();
   p->copy_done.destroy();
   if (p->copy) (void)hipStreamDestroy(p->copy);
   delete p;
+}
+
+// The pinned buffer a call's index arrays go through: kernels read it in place, so it is free again once they have run.
+// An event between two kernels costs the stream 5 us (32 % of an adapter-only step with the two it used to have), so one
+// event stands for kIdxMark consecutive uses: it is recorded behind the last of them (index_buffer_used) and waited for
+// before the first use of those buffers kIdxRing uses later, when kIdxMark later uses may still be in flight.
+int32_t index_buffer(hmi_pool* p, int32_t** out) {
+  const uint64_t u = p->idx_use;
+  if (u >= (uint64_t)kIdxRing && u % kIdxMark == 0) HIP_TRY(p, hipEventSynchronize(p->idx_ev[u / kIdxMark % (kIdxRing / kIdxMark)]));
+  *out = p->h_idx + u % kIdxRing * (5 * (size_t)p->cfg.max_requests + 1);
+  return HMI_OK;
+}
+int32_t index_buffer_used(hmi_pool* p) {   // behind the kernel that reads it
+  const uint64_t u = p->idx_use++;
+  if (u % kIdxMark == kIdxMark - 1) HIP_TRY(p, hipEventRecord(p->idx_ev[u / kIdxMark % (kIdxRing / kIdxMark)], p->compute));
+  return HMI_OK;
 }
 
 // Make the copy stream wait until every forward that read `slot` has finished.
@@ -511,10 +526,8 @@ static int32_t create_impl(const hmi_pool_config_t* cfg, hmi_pool_t** out) {
     }
   }
   const int Rm = c.max_requests;
-  for (int i = 0; i < 4; ++i) {
-    CREATE_TRY(hipHostMalloc(&p->h_idx[i], sizeof(int32_t) * 5 * Rm, hipHostMallocDefault));
-    CREATE_TRY(hipEventCreateWithFlags(&p->idx_ev[i], hipEventDisableTiming));
-  }
+  CREATE_TRY(hipHostMalloc(&p->h_idx, sizeof(int32_t) * kIdxRing * (5 * (size_t)Rm + 1), hipHostMallocDefault));
+  for (auto& e : p->idx_ev) CREATE_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
 
   // device routing arrays, one allocation
   const size_t MT = (size_t)c.max_tokens;
@@ -790,17 +803,15 @@ int32_t hmi_plot_aggregate(hmi_pool_t* p, const void* table, int32_t n_entries, 
   }
   HIP_TRY(p, hipSetDevice(c.device));
   // request offsets go through one of the pinned index buffers (the kernel reads them in place)
-  const int bi = p->idx_i;
-  p->idx_i = (p->idx_i + 1) & 3;
-  HIP_TRY(p, hipEventSynchronize(p->idx_ev[bi]));
-  int32_t* h = p->h_idx[bi];
+  int32_t* h = nullptr;
+  if (const int32_t rc = index_buffer(p, &h); rc != HMI_OK) return rc;
   h[0] = 0;
   for (int r = 0; r < R; ++r) h[r + 1] = h[r] + seq_lens[r];
   PlotArgs a{};
   a.table = static_cast<const char*>(table); a.n_entries = n_entries; a.frag_ids = frag_ids; a.tok_off = h;
   a.x = static_cast<char*>(x); a.d = c.d_model;
   launch_plot_aggregate(a, R, longest, N, p->bf16, p->compute);
-  HIP_TRY(p, hipEventRecord(p->idx_ev[bi], p->compute));
+  if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
   HIP_TRY(p, hipGetLastError());
   return HMI_OK;
 }
@@ -938,6 +949,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   // Records the end of the kernels enqueued so far and notes it as the last reader of every slot
   // this batch holds (a swap-in into one of them waits for that event).
   auto mark_slots_read = [&]() {
+    if (!c.host_tier) return;       // nothing is ever swapped in over a slot (and the event would cost the stream 5 us)
     const uint64_t seq = p->fwd_done.record(p->compute);
     for (int t : p->distinct) {
       const int sl = p->slot_of_tenant[t];
@@ -951,10 +963,8 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   }
 
   // ---- index arrays to the device
-  const int bi = p->idx_i;
-  p->idx_i = (p->idx_i + 1) & 3;
-  HIP_TRY(p, hipEventSynchronize(p->idx_ev[bi]));
-  int32_t* h = p->h_idx[bi];
+  int32_t* h = nullptr;
+  if (const int32_t rc = index_buffer(p, &h); rc != HMI_OK) return rc;
   const int Rm = c.max_requests;
   for (int r = 0; r < R; ++r) {
     h[r] = tenant_ids[r];
@@ -968,12 +978,12 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   hipStream_t s = p->compute;
   // The router reads the three index arrays straight from this pinned (device-mapped) host
   // buffer: 3 R words over the host link, instead of a staging copy that costs a copy
-  // engine hand-over (about 15 us) on either side.  The event lets the buffer be reused.
+  // engine hand-over (about 15 us) on either side.
   Route rt = p->rt;
   rt.tenant_ids = h; rt.seq_lens = h + Rm; rt.req_slot = h + 2 * Rm;
   if (kv != KV_NONE) { rt.kv_slot_in = h + 3 * Rm; rt.kv_pos_in = h + 4 * Rm; }
   { ProfSpan ps(p, HMI_KERNEL_ROUTER); launch_router(rt, R, s); }
-  HIP_TRY(p, hipEventRecord(p->idx_ev[bi], s));
+  if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
   p->last_R = R;
   p->last_distinct.assign(p->distinct.begin(), p->distinct.end());   // within the reserved capacity
   p->last_max_len = max_len;
@@ -1264,10 +1274,8 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
     p->compute_waited_copy = need_copy;
   }
   // index arrays: through one of the pool's pinned buffers, read in place by the router
-  const int bi = p->idx_i;
-  p->idx_i = (p->idx_i + 1) & 3;
-  HIP_TRY(p, hipEventSynchronize(p->idx_ev[bi]));
-  int32_t* h = p->h_idx[bi];
+  int32_t* h = nullptr;
+  if (const int32_t rc = index_buffer(p, &h); rc != HMI_OK) return rc;
   const int Rm = c.max_requests;
   for (int r = 0; r < R; ++r) {
     h[r] = tenant_ids[r];
@@ -1295,7 +1303,7 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
   rt.key_bits = p->rt.key_bits;
   rt.n_cu = p->rt.n_cu;
   launch_router(rt, R, s);
-  HIP_TRY(p, hipEventRecord(p->idx_ev[bi], s));
+  if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
   AdapterArgs a{};
   a.X = x; a.Y = y; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
   a.wd_off = p->tl[T_W1].off; a.bd_off = p->tl[T_B1].off;
@@ -1303,8 +1311,6 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
   a.d = c.d_model; a.which_tiles = 1; a.n_tiles128 = n_tiles128;
   a.stream_out = 1;
   launch_adapter_bf16(a, rt, s);
-  const uint64_t seq = p->fwd_done.record(s);
-  for (int t : p->distinct) p->slot_fwd[p->slot_of_tenant[t]] = seq;
   HIP_TRY(p, hipGetLastError());
   return HMI_OK;
 }
