@@ -6,7 +6,6 @@
 
 namespace hmi {
 
-constexpr int kRouterThreads = 1024;
 constexpr int kMaxRequests = 2048;   // router keeps keys/values of one batch in LDS
 constexpr int kDenseSegRows = 1024;  // rows per pseudo-segment of the route for shared parameters
 
@@ -29,7 +28,7 @@ struct Route {
   int32_t* tile_row0[2];      // [tiles] tile -> first sorted row
   int32_t* n_tiles[2];        // [1]
   int32_t tile_m[2];          // tile heights (0 = list unused)
-  int32_t key_bits;           // bits needed for the largest tenant id (radix passes = bits/4)
+  int32_t key_bits;           // bits needed for the largest tenant id
   // scratch of the persistent GEMM: per XCD a tile-claim counter [0..7] and a count of finished
   // workgroups [8..15], then one mailbox per workgroup; all zero between launches
   int32_t* gemm_sched;
@@ -52,7 +51,7 @@ struct Route {
   int32_t n_cu;                 // compute units of the pool's device (host side: sizes the persistent launches)
 };
 constexpr int kGemmSchedInts = 16 + 1024;
-void launch_router(const Route& rt, int R, hipStream_t s);
+void launch_router(const Route& rt, int R, int N, hipStream_t s);   // N: the batch's rows
 
 // Per-device set-up of the kernels that need more than the default dynamic LDS: pool creation
 // calls these once per device, with that device current, before any launch on it.

@@ -387,7 +387,7 @@ void write_image(const hmi_pool* p, char* img, const void* const* tensors) {
 int bits_for(int n) {
   int b = 1;
   while ((1ll << b) < n) ++b;
-  return (b + 3) / 4 * 4;
+  return b;
 }
 
 }  // namespace
@@ -982,7 +982,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   Route rt = p->rt;
   rt.tenant_ids = h; rt.seq_lens = h + Rm; rt.req_slot = h + 2 * Rm;
   if (kv != KV_NONE) { rt.kv_slot_in = h + 3 * Rm; rt.kv_pos_in = h + 4 * Rm; }
-  { ProfSpan ps(p, HMI_KERNEL_ROUTER); launch_router(rt, R, s); }
+  { ProfSpan ps(p, HMI_KERNEL_ROUTER); launch_router(rt, R, (int)N, s); }
   if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
   p->last_R = R;
   p->last_distinct.assign(p->distinct.begin(), p->distinct.end());   // within the reserved capacity
@@ -1302,7 +1302,7 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
   rt.tile_m[0] = kBf16TileM0; rt.tile_m[1] = kBf16TileM1;
   rt.key_bits = p->rt.key_bits;
   rt.n_cu = p->rt.n_cu;
-  launch_router(rt, R, s);
+  launch_router(rt, R, (int)N, s);
   if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
   AdapterArgs a{};
   a.X = x; a.Y = y; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
