@@ -1,10 +1,10 @@
 """Builds libhmi.so (the C-ABI library: HIP kernels + pool) in-tree for gfx950.
 
     python paper_2504_17449_amd/build.py
-    python paper_2504_17449_amd/build.py --lib /tmp/libhmi_x.so --obj-suffix _x -DHMI_ABLATE_MFMA=1
+    python paper_2504_17449_amd/build.py --lib /tmp/libhmi_x.so --obj-suffix _x -g
 
 The second form writes another library (load it with HMI_LIB_PATH=...) from the same sources with extra
-compiler flags: the timing-only ablation builds of the persistent GEMM are made this way.
+compiler flags.
 hipcc cross-compiles without a GPU.  Packed-fp32 code generation is switched off for the
 device pass, as required on the target machines.
 """

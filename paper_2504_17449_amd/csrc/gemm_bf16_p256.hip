@@ -12,7 +12,7 @@
 //     64 different lines costs 64 requests however few bytes it carries.
 //   * The matrix pipe blocks a wavefront's instruction issue for half the duration of an
 //     MFMA; about four other instructions fit behind each one.
-//   * LDS reads run at 256 B/clk, fragment traffic is not a bound for 64 x 128 wavefront tiles.
+//   * LDS reads run at 256 B/clk.
 // Hence
 //   * 256 x 256 tiles: the fewest operand bytes per FLOP the register file allows, held either by
 //     8 wavefronts x 128 accumulator registers (two wavefronts per SIMD) or by 4 wavefronts x 256
@@ -21,9 +21,14 @@
 //     whole cache line, every operand request is a full line;
 //   * all 160 KB of LDS are a ring of 2 activation and 3 weight stages of 32 KB; weight
 //     copies (mostly L2 misses: a weight panel is shared only by the m-tiles of one
-//     tenant) run two stages ahead, activation copies (mostly hits) one.  A wavefront
-//     issues activation copies before weight copies, so with in-order completion "all but
+//     tenant) run further ahead than activation copies (mostly hits).  A wavefront issues a
+//     stage's activation copies before its weight copies, so with in-order completion "all but
 //     the newest weight stage have landed" is exactly the condition for the next stage;
+//   * a compute unit takes 66 bytes per clock through its L1: a stage's copies are spread over its
+//     MFMAs, since a wavefront that issues them faster than that stands still with its products
+//     (all sixteen behind the sixteen MFMAs of one k-step, as before: second FFN GEMM of 65 536 rows
+//     329 us -> 307 with four wavefronts; of 64 tenants' 32 768 rows 209 -> 190; the launches with
+//     eight wavefronts 0 to 1.5 % faster);
 //   * one workgroup per compute unit walks over its share of the tiles.  Copies for the
 //     next tile are issued while the current one finishes, fragment reads are double
 //     buffered in registers one k-step ahead (across stage and tile boundaries), and there
@@ -83,29 +88,6 @@ __device__ __forceinline__ int swz_w(int row) { return ((row >> 1) & 3) | (((row
 // MFMA first-operand position i (0..31) <- weight row perm_w(i) of the 32-row tile, chosen
 // so that output register r of lane half h is column 16 h + r.
 __device__ __forceinline__ int perm_w(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
-
-// Timing-only ablations of the main loop (never set by the build script's defaults; RESULTS ARE WRONG with any of them):
-//   -DHMI_ABLATE_MFMA=1    no MFMA is issued (fragments are still read from LDS)
-//   -DHMI_ABLATE_READS=1   no fragment is read from LDS
-//   -DHMI_ABLATE_COPIES=1  the steady-state stages issue no copy (prologues and tile changes still do)
-//   -DHMI_ABLATE_WAIT=n    a stage waits until all but n (instead of one) operand stages of copies have landed
-// They exist so that the time of each part of a stage can be measured with the launch shapes, addresses
-// and tile order of the real kernel; every access they leave in is one the real kernel makes.
-#ifndef HMI_ABLATE_MFMA
-#define HMI_ABLATE_MFMA 0
-#endif
-#ifndef HMI_ABLATE_READS
-#define HMI_ABLATE_READS 0
-#endif
-#ifndef HMI_ABLATE_COPIES
-#define HMI_ABLATE_COPIES 0
-#endif
-#ifndef HMI_ABLATE_WAIT
-#define HMI_ABLATE_WAIT 1
-#endif
-#if HMI_ABLATE_MFMA || HMI_ABLATE_READS || HMI_ABLATE_COPIES || HMI_ABLATE_WAIT != 1
-#warning "gemm_bf16_p256: timing-only ablation build, results are wrong"
-#endif
 
 // Results leave with the non-temporal hint: nothing in this launch reads them again, and every line of L2 they do not
 // take stays with the operand panels that other workgroups of the XCD are about to ask for (measured: 1-2 % fewer
@@ -232,59 +214,55 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
     fw_base = W_RING + rw * ROW_BYTES + ((lh ^ swz_w(rw)) << 4);
   }
 
-  // Ring bookkeeping (uniform): a_rd / w_rd are the byte offsets of the slots that hold the
-  // stage being multiplied.  Activation stage s+2 and weight stage s+3 are copied into exactly
-  // those slots once stage s is done, so no separate fill position is needed; a stage index
-  // of KT or more means a stage of the next tile (for the last tile: an in-bounds re-read
-  // of its own first stages that nobody consumes).  Needs KT >= 3, so that the copies
-  // never reach the tile after next.
+  // Ring bookkeeping (uniform): a_rd / w_rd are the byte offsets of the slots that hold the stage being multiplied.
+  // Activation stage s+2 goes into that slot once stage s is done, weight stage s+2 into the slot before it; a stage index
+  // of KT or more means a stage of the next tile (for the last tile: an in-bounds re-read of its own first stages that
+  // nobody consumes).  Needs KT >= 3, so that the copies never reach the tile after next.
   int a_rd = 0, w_rd = 0;
-  // Four 1 KB copies of a wavefront's slice (all of it, or half) share one LDS base (one M0 write); the
-  // instruction offset j KB that separates them applies to the global address too, so
-  // the lane offsets carry 3072 - j KB and the uniform base pointer -3072.
-#define HMI_COPY4(SRC, VOFF, SLOT_OFF)                                                            \
+  // Copies FROM .. FROM + COUNT - 1 of a wavefront's slice (1 KB each).  Four in a row share one LDS base (one M0 write);
+  // the instruction offset j KB that separates them applies to the global address too, so the lane offsets carry
+  // 3072 - j KB and the uniform base pointer -3072.
+#define HMI_COPY(SRC, VOFF, SLOT_OFF, FROM, COUNT)                                                \
   {                                                                                               \
     const char* src_ = (SRC) - 3072;                                                              \
-    _Pragma("unroll") for (int q_ = 0; q_ < LD / 4; ++q_) {                                       \
-      lds_ptr_t dst_ = (lds_ptr_t)(smem + (SLOT_OFF) + wave * WAVE_SLICE + q_ * 4096);            \
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[4 * q_ + 0]), dst_, 16, 0, 0);    \
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[4 * q_ + 1]), dst_, 16, 1024, 0); \
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[4 * q_ + 2]), dst_, 16, 2048, 0); \
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[4 * q_ + 3]), dst_, 16, 3072, 0); \
+    _Pragma("unroll") for (int j_ = (FROM); j_ < (FROM) + (COUNT); ++j_) {                        \
+      lds_ptr_t dst_ = (lds_ptr_t)(smem + (SLOT_OFF) + wave * WAVE_SLICE + (j_ / 4) * 4096);      \
+      if ((j_ & 3) == 0) __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 0, 0);         \
+      else if ((j_ & 3) == 1) __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 1024, 0); \
+      else if ((j_ & 3) == 2) __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 2048, 0); \
+      else __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 3072, 0);   \
     }                                                                                             \
   }
-  static_assert(LD % 4 == 0, "HMI_COPY4 issues the copies in groups of four");
+  static_assert(LD % 4 == 0, "HMI_COPY addresses the copies in groups of four");
 
   bf16x8 fx[2][TM], fw[2][TN];
   f32x16 acc[TM][TN];
 
   // loads the MFMA fragments of k-step KS of the stage in slots a_rd / w_rd into register buffer B
 #define HMI_READ_FRAGS(B, KS)                                                                     \
-  if (!HMI_ABLATE_READS) {                                                                                               \
+  {                                                                                               \
     const unsigned char* xa_ = smem + a_rd + (fx_base ^ ((KS) << 5));                             \
     const unsigned char* wa_ = smem + w_rd + (fw_base ^ ((KS) << 5));                             \
     _Pragma("unroll") for (int i = 0; i < TM; ++i) fx[B][i] = *reinterpret_cast<const bf16x8*>(xa_ + i * 32 * ROW_BYTES); \
     _Pragma("unroll") for (int j = 0; j < TN; ++j) fw[B][j] = *reinterpret_cast<const bf16x8*>(wa_ + j * 32 * ROW_BYTES); \
   }
-#if HMI_ABLATE_MFMA
-#define HMI_MFMAS(B)   /* keeps the fragment registers (and so their reads) alive */                  \
-  _Pragma("unroll") for (int i = 0; i < TM; ++i) asm volatile("" :: "v"(fx[B][i]));               \
-  _Pragma("unroll") for (int j = 0; j < TN; ++j) asm volatile("" :: "v"(fw[B][j]));
-#else
 #define HMI_MFMAS(B)                                                                              \
   _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                  \
     _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                \
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[B][j], fx[B][i], acc[i][j], 0, 0, 0);
-#endif
 
-  // scheduling: each of the 6 fragment reads of the next k-step goes behind one MFMA of
-  // this k-step (the wait for this k-step's fragments then comes before any new read)
-#define HMI_SCHED_READS_THEN_MFMAS()                                                              \
+  // scheduling of a k-step: each fragment read of the next k-step goes behind one MFMA of this one (the wait for this
+  // k-step's fragments then comes before any new read), and C copies are spread over the MFMAs that are left
+#define HMI_SCHED_KSTEP(C)                                                                        \
   _Pragma("unroll") for (int z_ = 0; z_ < TM + TN; ++z_) {                                        \
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                            \
     __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                            \
   }                                                                                               \
-  __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);                              \
+  _Pragma("unroll") for (int z_ = 0; z_ < (C); ++z_) {                                            \
+    __builtin_amdgcn_sched_group_barrier(0x008, (TM * TN - TM - TN) / ((C) ? (C) : 1), 0);        \
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                            \
+  }                                                                                               \
+  if ((C) == 0) __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);                \
   __builtin_amdgcn_sched_barrier(0);
 
   // accumulators of a tile start at its bias: lane half h of MFMA tile j holds columns
@@ -301,70 +279,79 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
     _Pragma("unroll") for (int i = 1; i < TM; ++i) acc[i][j] = acc[0][j];                         \
   }
 
-  // One stage.  MODE says where the copies issued after the barrier come from:
-  //   0: activation stage s+2 and weight stage s+3 of the current tile
-  //   1: (s = KT-3) activation stage KT-1 of the current tile, weight stage 0 of the next
-  //   2: (s = KT-2) activation stage 0 and weight stage 1 of the next tile
-  //   3: (s = KT-1) none: the freed slots serve the epilogue first
-#define HMI_STAGE_COPIES(MODE)                                                                    \
-  {                                                                                               \
-    if (MODE == 0 && !HMI_ABLATE_COPIES) { HMI_COPY4(Ab + (s + 2) * ROW_BYTES, cur.a_off, fa_) HMI_COPY4(cur.Wb + (s + 3) * ROW_BYTES, b_off, W_RING + fw_) } \
-    if (MODE == 1) { HMI_COPY4(Ab + (s + 2) * ROW_BYTES, cur.a_off, fa_) HMI_COPY4(nxt.Wb, b_off, W_RING + fw_) }                     \
-    if (MODE == 2) { HMI_COPY4(Ab, nxt.a_off, fa_) HMI_COPY4(nxt.Wb + ROW_BYTES, b_off, W_RING + fw_) }                                \
-  }
+  // One stage.  A wavefront's L1 takes 66 bytes a clock for the whole compute unit, a 1 KB copy every 16 clocks, and a
+  // wavefront that issues them faster stands still with its MFMAs: the copies are spread.  The weights of stage s + 2 go
+  // between the products of k-steps 0 and 1 (into the slot of stage s - 1), the activations of stage s + 2 between those of
+  // k-step 3, behind the barrier that frees the slot of stage s.  Activation copies have three k-steps to land, weight
+  // copies six.  MODE says where they come from:
+  //   0: the current tile (s <= KT-4)
+  //   1: (s = KT-3) the current tile; the tile claimed for the round after next goes into the mailbox
+  //   2: (s = KT-2) the next tile's stage 0; its weights only behind the barrier, so that nothing is in flight in front of it
+  //      and the mailbox store is done
+  //   3: (s = KT-1) the next tile's weight stage 1; no activations: the freed slots serve the epilogue first
 #define HMI_ITER(MODE)                                                                            \
   {                                                                                               \
+    const int wf_ = w_rd == 0 ? (W_STAGES - 1) * STAGE_BYTES : w_rd - STAGE_BYTES;   /* the slot of stage s - 1, and of s + 2 */ \
+    const char* ws_ = (MODE) < 2 ? cur.Wb + (s + 2) * ROW_BYTES : nxt.Wb + ROW_BYTES;             \
+    constexpr int WC = (MODE) == 2 ? 0 : LD / 2;                                                  \
     if (wave_active) {                                                                            \
       HMI_READ_FRAGS(1, 1)                                                                        \
+      HMI_COPY(ws_, b_off, W_RING + wf_, 0, WC)                                                   \
       HMI_MFMAS(0)                                                                                \
-      HMI_SCHED_READS_THEN_MFMAS()                                                                \
+      HMI_SCHED_KSTEP(WC)                                                                         \
       HMI_READ_FRAGS(0, 2)                                                                        \
+      HMI_COPY(ws_, b_off, W_RING + wf_, LD / 2, WC)                                              \
       HMI_MFMAS(1)                                                                                \
-      HMI_SCHED_READS_THEN_MFMAS()                                                                \
+      HMI_SCHED_KSTEP(WC)                                                                         \
       HMI_READ_FRAGS(1, 3)                                                                        \
       HMI_MFMAS(0)                                                                                \
-      HMI_SCHED_READS_THEN_MFMAS()                                                                \
+      HMI_SCHED_KSTEP(0)                                                                          \
+    } else {                                                                                      \
+      HMI_COPY(ws_, b_off, W_RING + wf_, 0, 2 * WC)                                               \
     }                                                                                             \
     HMI_WAIT_LGKMCNT0();          /* this wavefront no longer reads stage s from LDS */           \
-    if (MODE == 2 && wave == 0) { HMI_WAIT_VMCNT(0); }   /* ... and its mailbox store is done */   \
-    else { HMI_WAIT_VMCNT(HMI_ABLATE_WAIT * LD); }  /* its copies of stage s+1 (both operands) have landed */       \
+    if ((MODE) == 2) HMI_WAIT_VMCNT(0);              /* its copies of stage s+1 (both operands) have landed: nothing newer, */ \
+    else HMI_WAIT_VMCNT(LD);                          /* or the weights of stage s+2 */            \
     __builtin_amdgcn_s_barrier(); /* ... everybody's, and nobody reads stage s any more */        \
     __builtin_amdgcn_sched_barrier(0);                                                            \
-    if (MODE == 1 && claimer) __hip_atomic_store(mailbox, claimed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); \
-    if (MODE == 2) mail = __hip_atomic_load(mailbox, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  \
+    if ((MODE) == 1 && claimer) __hip_atomic_store(mailbox, claimed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); \
+    if ((MODE) == 2) mail = __hip_atomic_load(mailbox, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  \
     const int fa_ = a_rd, fw_ = w_rd;                                                             \
     a_rd ^= STAGE_BYTES;                                                                          \
     w_rd = w_rd == (W_STAGES - 1) * STAGE_BYTES ? 0 : w_rd + STAGE_BYTES;                         \
-    if (MODE == 3) {                                                                              \
+    if ((MODE) == 3) {                                                                            \
       patch_a = fa_; patch_w = fw_;                                                               \
       if (wm * WTM < nxt.rows) HMI_READ_FRAGS(0, 0)                                               \
       __builtin_amdgcn_sched_barrier(0);                                                          \
       if (wave_active) { HMI_MFMAS(1) }                                                           \
-    } else if (wave_active) {                                                                     \
-      /* first fragments of stage s+1, then the last k-step's MFMAs with the copies between them */ \
-      HMI_READ_FRAGS(0, 0)                                                                        \
-      HMI_STAGE_COPIES(MODE)                                                                      \
-      HMI_MFMAS(1)                                                                                \
-      __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);                                    \
-      _Pragma("unroll") for (int z_ = 0; z_ < 2 * LD; ++z_) {                                     \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                        \
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                        \
-      }                                                                                           \
     } else {                                                                                      \
-      HMI_STAGE_COPIES(MODE)                                                                      \
+      constexpr int AC = LD, WB = (MODE) == 2 ? LD : 0;                                           \
+      if (wave_active) {                                                                          \
+        /* first fragments of stage s+1, then the last k-step's MFMAs with the copies between them */ \
+        HMI_READ_FRAGS(0, 0)                                                                      \
+        if ((MODE) == 2) { HMI_COPY(Ab, nxt.a_off, fa_, 0, AC) HMI_COPY(nxt.Wb, b_off, W_RING + wf_, 0, WB) } \
+        else HMI_COPY(Ab + (s + 2) * ROW_BYTES, cur.a_off, fa_, 0, AC)                            \
+        HMI_MFMAS(1)                                                                              \
+        __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);                                  \
+        _Pragma("unroll") for (int z_ = 0; z_ < AC + WB; ++z_) {                                  \
+          __builtin_amdgcn_sched_group_barrier(0x008, (MODE) == 2 ? 1 : 2, 0);                    \
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                      \
+        }                                                                                         \
+      } else {                                                                                    \
+        if ((MODE) == 2) { HMI_COPY(Ab, nxt.a_off, fa_, 0, AC) HMI_COPY(nxt.Wb, b_off, W_RING + wf_, 0, WB) } \
+        else HMI_COPY(Ab + (s + 2) * ROW_BYTES, cur.a_off, fa_, 0, AC)                            \
+      }                                                                                           \
     }                                                                                             \
     __builtin_amdgcn_sched_barrier(0);                                                            \
   }
 
-  // ---- prologue of the first tile.  Issue order W(0) A(0) W(1) A(1) W(2) is the steady
-  // state's order, so the same "all but the newest weight stage" wait works from the start.
+  // ---- prologue of the first tile: stages 0 and 1 in the order in which the steady state issues them
   HMI_INIT_ACC(cur)
-  HMI_COPY4(cur.Wb, b_off, W_RING)
-  HMI_COPY4(Ab, cur.a_off, 0)
-  HMI_COPY4(cur.Wb + ROW_BYTES, b_off, W_RING + STAGE_BYTES)
-  HMI_COPY4(Ab + ROW_BYTES, cur.a_off, STAGE_BYTES)
-  HMI_COPY4(cur.Wb + 2 * ROW_BYTES, b_off, W_RING + 2 * STAGE_BYTES)
-  HMI_WAIT_VMCNT(3 * LD);
+  HMI_COPY(cur.Wb, b_off, W_RING, 0, LD)
+  HMI_COPY(Ab, cur.a_off, 0, 0, LD)
+  HMI_COPY(cur.Wb + ROW_BYTES, b_off, W_RING + STAGE_BYTES, 0, LD)
+  HMI_COPY(Ab + ROW_BYTES, cur.a_off, STAGE_BYTES, 0, LD)
+  HMI_WAIT_VMCNT(2 * LD);
   __builtin_amdgcn_s_barrier();
   bool wave_active = wm * WTM < cur.rows;
   if (wave_active) HMI_READ_FRAGS(0, 0)
@@ -498,11 +485,10 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
     cur = nxt;
     wave_active = wm * WTM < cur.rows;
     HMI_INIT_ACC(cur)
-    // the copies that were held back at the last stage (the new tile's activation stage 1
-    // and weight stage 2) go into the slots the epilogue just used; a wavefront's copies
-    // fill only its own slice of a slot, which is its own staging patch: no barrier
-    HMI_COPY4(Ab + ROW_BYTES, cur.a_off, patch_a)
-    HMI_COPY4(cur.Wb + 2 * ROW_BYTES, b_off, W_RING + patch_w)
+    // the copies that were held back at the last stage (the new tile's activation stage 1) go into the slot the epilogue
+    // just used, as its weight stage 2 will in its first stage; a wavefront's copies fill only its own slice of a slot,
+    // which is its own staging patch: no barrier
+    HMI_COPY(Ab + ROW_BYTES, cur.a_off, patch_a, 0, LD)
     load_tile(g, rt, w_next < w_end ? w_next : w, wave, lane, nxt);
   }
   HMI_WAIT_VMCNT(0);   // none of this workgroup's copies may outlive it

@@ -372,6 +372,9 @@ void init_gemm_tile_kernels() {
 // compute unit: its tiles times (stages of 64 k times the time of one stage, plus what a tile costs besides, which the
 // second workgroup of a compute unit hides for the small tiles; the activation adds to that).  Microseconds, measured with
 // d = 768, f = 3072 over 100 to 16 384 rows of one weight set; the estimate's choice was the fastest or within 10 % of it.
+// It says nothing about weights that come from HBM or panels that are fetched again, so a launch that gives the
+// persistent kernel's workgroups more than one and a half tiles each is not weighed at all: it was the faster one for all
+// of those (two encoder layers of 177 tenants, 65 536 rows: 3.1 ms, with 128 x 256 tiles where the estimate is lower 3.4).
 void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
   if (g.n_rows <= 0 || g.n_mtiles_list[1] <= 0) return;
   const int n_cu = rt.n_cu >= kXcds ? rt.n_cu : 256;
@@ -385,6 +388,14 @@ void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
       return launch_gemm_bf16_skinny(a, rt, s);
     }
   }
+  const long long big_tiles = g.n_out % 256 == 0 && g.k >= 192 ? (long long)g.n_mtiles_list[0] * (g.n_out / 256) : 0;
+  auto persistent = [&]() {
+    GemmArgs a = g;
+    a.which_tiles = 0;
+    a.n_mtiles = g.n_mtiles_list[0];
+    launch_gemm_bf16_p256(a, rt, s);
+  };
+  if (2 * big_tiles > 3LL * n_cu) return persistent();
   const double stages = g.k / 64, act = g.epi == EPI_BIAS_GELU ? 1.0 : 0.0;
   auto estimate = [&](long long tiles, double stage, double tile, double gelu) {
     return (double)((tiles + n_cu - 1) / n_cu) * (stages * stage + tile + act * gelu);
@@ -396,19 +407,14 @@ void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
   if (g.n_out % 128 == 0) consider(2, estimate(TileL::tiles(g, rt, 1), 0.50, 2.3, 1.3));
   if (g.n_out % 256 == 0) {
     consider(3, estimate(TileXL::tiles(g, rt, 1), 0.90, 3.2, 2.6));
-    if (g.k >= 192) consider(4, estimate((long long)g.n_mtiles_list[0] * (g.n_out / 256), 1.45, 4.0, 3.0));
+    if (g.k >= 192) consider(4, estimate(big_tiles, 1.45, 4.0, 3.0));
   }
   switch (which) {
     case 0: return TileS::launch(g, rt, 1, s);
     case 1: return TileM::launch(g, rt, 1, s);
     case 2: return TileL::launch(g, rt, 1, s);
     case 3: return TileXL::launch(g, rt, 1, s);
-    default: {
-      GemmArgs a = g;
-      a.which_tiles = 0;
-      a.n_mtiles = g.n_mtiles_list[0];
-      return launch_gemm_bf16_p256(a, rt, s);
-    }
+    default: return persistent();
   }
 }
 
