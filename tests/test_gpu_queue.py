@@ -191,3 +191,38 @@ def test_queue_output_is_the_stack_call_on_the_gathered_batch_bit_for_bit(hmi):
         if q is not None:
             q.close()
         pool.close()
+
+
+@pytest.mark.parametrize("d", [256, 768])
+def test_fetch_copies_whole_rows_to_any_device_address(hmi, d):
+    """Row counts around the copy kernel's workgroup (512 pieces of 16 bytes), buffers that start on and off a 16-byte
+    boundary: the same bytes everywhere, and nothing behind or in front of them."""
+    from paper_2504_17449_amd import harness
+    rows = [1, 2, 5, 6, 15, 16, 17, 31, 32, 33, 64, 131]
+    wl = synth.Workload(name="queue_fetch", block=synth.BLOCK_FFN, dtype="bf16", d_model=d, d_ff=256, n_heads=0, n_layers=1,
+                        n_tenants=2, n_requests=len(rows), seq_min=1, seq_max=131, popularity="uniform", zipf_s=0.0,
+                        ln_eps=1e-12, hbm_slots=2, host_tier=False, seed=11)
+    pool = harness.create_pool(wl, max_requests=len(rows), max_tokens=sum(rows))
+    q = None
+    try:
+        harness.load_tenants(pool, wl)
+        q = hmi.Queue(pool, len(rows), sum(rows))
+        xs = [harness.host_to_device(synth.hidden_states(wl, r, n), "bf16") for r, n in enumerate(rows)]
+        tickets = [q.push(r % 2, x) for r, x in enumerate(xs)]
+        assert q.run() == (0, len(rows))
+        x = torch.cat(xs)
+        want = torch.empty_like(x)
+        pool.stack_forward(0, 1, x, want, np.arange(len(rows), dtype=np.int32) % 2, np.array(rows, np.int32))
+        off = 0
+        for r, n in enumerate(rows):
+            for lead in (64, 65, 68):                                   # 16-byte aligned, 2 and 8 bytes past it
+                room = torch.full((lead + n * d + 64,), 7.0, device="cuda", dtype=torch.bfloat16)
+                q.fetch(tickets[r], room[lead:lead + n * d].view(n, d))
+                got = room.cpu()
+                assert torch.equal(got[lead:lead + n * d].view(n, d).view(torch.int16), want[off:off + n].cpu().view(torch.int16)), (n, lead)
+                assert bool((got[:lead] == 7).all()) and bool((got[lead + n * d:] == 7).all()), (n, lead)
+            off += n
+    finally:
+        if q is not None:
+            q.close()
+        pool.close()
