@@ -24,6 +24,12 @@
 //          bf16 once, as the two-kernel path does between its GEMMs.
 //   Up:    wavefront w owns output columns [w d/8, (w+1) d/8); it adds bias and the
 //          unit's own rows from LDS and writes the rounded sum back in place.
+//
+// Inside a shared layer the block is followed by the layer's LayerNorm over (residual stream + Y): a workgroup has whole
+// rows of Y in LDS, so it does that too (LN_* below), a wavefront four rows of the unit, in the arrangement of the vector
+// LayerNorm kernel and with its arithmetic.  Y itself is then never written.  The first half of a unit's residual
+// rows is asked for a unit ahead, before the copies of the unit after it, so that the wait for those covers it too.
+// Measured: 65 536 rows of d = 768 with an fp32 residual 55 + 75 us as two kernels, 123 as one.
 #include "hmi_kernels.h"
 
 namespace hmi {
@@ -34,6 +40,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
@@ -64,6 +71,15 @@ __device__ __forceinline__ bf16x8 load_w(const bf16x8* p) {
   return *p;
 }
 
+// What happens to the finished rows of a unit.
+enum Out : int { OUT_STREAM, LN_RESID_BF16, LN_RESID_F32 };
+
+// Four columns of a residual row as they are loaded, and as fp32.
+template <bool F32> struct Four { typedef u16x4 type; };
+template <> struct Four<true> { typedef f32x4 type; };
+__device__ __forceinline__ f32x4 to_f32(u16x4 h) { return f32x4{bf2f(h[0]), bf2f(h[1]), bf2f(h[2]), bf2f(h[3])}; }
+__device__ __forceinline__ f32x4 to_f32(f32x4 v) { return v; }
+
 template <int NV>
 struct Shape {
   static constexpr int CH = NV * 32;          // 16-byte chunks of a row (d = 256 NV)
@@ -76,7 +92,8 @@ struct Shape {
   static constexpr int OFF_MID = OFF_PART + PART_BYTES;
   static constexpr int OFF_RS = OFF_MID + MID_BYTES;
   static constexpr int OFF_DESC = OFF_RS + RS_BYTES;
-  static constexpr int LDS = OFF_DESC + DESC_BYTES;
+  static constexpr int OFF_NORM = OFF_DESC + DESC_BYTES;   // LayerNorm gain, then shift, as stored
+  static constexpr int LDS = OFF_NORM + 2 * ROWB;
 };
 
 // LDS layouts (all XOR swizzles act on 16-byte chunk indices, so that the 16 lanes that
@@ -84,17 +101,19 @@ struct Shape {
 //   row buffer   row r, position p holds the row's chunk p ^ (r & 15)
 //   partial sum  [kq][row r][16 chunks of 4 fp32], chunk q at position q ^ (r & 15)
 //   bottleneck   row r is 128 bytes (64 bf16), chunk c at position c ^ ((r >> 1) & 7)
-// ONCE: the tenants' matrices are loaded with the non-temporal hint (load_w above); STREAM: so are the result's stores.
+// ONCE: the tenants' matrices are loaded with the non-temporal hint (load_w above); OUT_STREAM: so are the result's stores.
 // Both are compile-time: a run-time choice between a hinted and a plain access to one address is merged into the plain one.
-template <int NV, bool ONCE, bool STREAM>
+template <int NV, bool ONCE, int OUT>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   using S = Shape<NV>;
+  constexpr bool LN = OUT != OUT_STREAM;
+  typedef typename Four<OUT == LN_RESID_F32>::type four_t;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  int tid = threadIdx.x;
+  int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j = lane & 31, h = lane >> 5;     // MFMA: token row of the unit, k-half
+  int j = lane & 31, h = lane >> 5;           // MFMA: token row of the unit, k-half
   int* desc = reinterpret_cast<int*>(smem + S::OFF_DESC);
   int* rs = reinterpret_cast<int*>(smem + S::OFF_RS);
 
@@ -122,11 +141,6 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   __syncthreads();
   const int m = desc[MAX_UNITS * 4];
   if (m == 0) return;
-  for (int idx = tid; idx < m * RT; idx += NTH) {
-    const int u = idx >> 5, r = idx & 31;
-    rs[idx] = rt.row_src[desc[u * 4] + min(r, desc[u * 4 + 1] - 1)];   // surplus rows of a short unit repeat its last row
-  }
-
   const int cb = wave & 1, kq = wave >> 1;    // down-projection role
   bf16x8 wd[S::KSW], wu[NV][4];
   u32x4 bu[NV][2];   // up-projection bias of my columns, packed bf16 pairs
@@ -180,9 +194,40 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
     }                                                                                              \
   }
 
+  // Asked for in the order in which they are needed (loads return in order): the first sixteen units' rows, the LayerNorm's
+  // parameters, the matrices.
+  auto row_of = [&](int idx) {                        // surplus rows of a short unit repeat its last row
+    const int u = idx >> 5, r = idx & 31;
+    return rt.row_src[desc[u * 4] + min(r, desc[u * 4 + 1] - 1)];
+  };
+  int row0 = 0;
+  if (tid < m * RT) row0 = row_of(tid);
+  u32x4 norm = {};
+  if (LN && tid < 2 * S::CH) norm = reinterpret_cast<const u32x4*>(tid < S::CH ? a.ln_g : a.ln_b)[tid < S::CH ? tid : tid - S::CH];
+  __builtin_amdgcn_sched_barrier(0);
   int cur_slot = desc[2];
-  HMI_LOAD_WD(cur_slot) HMI_LOAD_BD(cur_slot) HMI_LOAD_WU(cur_slot)
+  HMI_LOAD_WD(cur_slot) HMI_LOAD_WU(cur_slot)
+  __builtin_amdgcn_sched_barrier(0);
+  if (tid < m * RT) rs[tid] = row0;
+  for (int idx = tid + NTH; idx < m * RT; idx += NTH) rs[idx] = row_of(idx);
+  if (LN && tid < 2 * S::CH) reinterpret_cast<u32x4*>(smem + S::OFF_NORM)[tid] = norm;
+  HMI_LOAD_BD(cur_slot)
+  // the residual rows of unit UI that this wavefront normalises: two of rows 4 wave .. 4 wave + 3, columns 256 v + 4 lane ..
+  // (the first two are asked for a unit ahead; all four would not fit the registers beside the tenant's matrices)
+  four_t res[LN ? 4 : 1][LN ? NV : 1];
+#define HMI_LOAD_RESID(UI, Q0)                                                                     \
+  {                                                                                                \
+    _Pragma("unroll") for (int q = (Q0); q < (Q0) + 2; ++q) {                                                \
+      const size_t row_ = (size_t)__builtin_amdgcn_readfirstlane(rs[(UI) * RT + wave * 4 + q]) * (S::CH * 8); \
+      _Pragma("unroll") for (int v = 0; v < NV; ++v) {                                             \
+        if (OUT == LN_RESID_F32) res[q][v] = *reinterpret_cast<const four_t*>(static_cast<const float*>(a.resid) + row_ + v * 256 + lane * 4); \
+        else res[q][v] = *reinterpret_cast<const four_t*>(static_cast<const uint16_t*>(a.resid) + row_ + v * 256 + lane * 4); \
+      }                                                                                            \
+    }                                                                                              \
+  }
   __syncthreads();   // rs complete
+  if (LN) HMI_LOAD_RESID(0, 0)
+  __builtin_amdgcn_sched_barrier(0);
   if (wave < 4) {
     HMI_ISSUE_COPIES(0, 0)
     if (m > 1) HMI_ISSUE_COPIES(1, 1)
@@ -191,6 +236,10 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   for (int i = 0; i < m; ++i) {
     const int b = i & 1;
     unsigned char* buf = smem + b * S::BUF;
+    if (LN) {   // the addresses made from the thread's number are made anew for each unit: there are no registers to keep them in
+      asm volatile("" : "+v"(tid));
+      lane = tid & 63; j = lane & 31; h = lane >> 5;
+    }
     const int rows = desc[i * 4 + 1];
     // the tenant of the next unit, if it is another one: its matrices replace this unit's as
     // soon as each has been used for the last time, so that the reads run under the rest of the unit
@@ -270,7 +319,66 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
     }
     if (reload) HMI_LOAD_WU(next_slot)
     cur_slot = next_slot;
+    if (LN && wave < 4 && i + 1 < m) HMI_WAIT_VMCNT(0);   // the next unit's rows, before this unit's stores are in the way
+    if (LN) HMI_LOAD_RESID(i, 2)
     __syncthreads();
+    if (LN) {
+      // ---- LayerNorm of (residual + adapted row), rounded as the separate kernels would pass it on
+#pragma unroll
+      for (int q0 = 0; q0 < 4; q0 += 2) {
+        f32x4 v[2][NV];
+        float sum[2], var[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int r = wave * 4 + q0 + q;
+          sum[q] = 0.0f;
+#pragma unroll
+          for (int c = 0; c < NV; ++c) {
+            const u16x4 y = *reinterpret_cast<const u16x4*>(buf + r * S::ROWB + (((c * 32 + (lane >> 1)) ^ (r & 15)) << 4) + (lane & 1) * 8);
+            v[q][c] = to_f32(res[q0 + q][c]) + to_f32(y);
+            sum[q] += v[q][c][0] + v[q][c][1] + v[q][c][2] + v[q][c][3];
+          }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) sum[q] += __shfl_xor(sum[q], o, 64);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          sum[q] /= (float)(NV * 256);                                 // the mean
+          var[q] = 0.0f;
+#pragma unroll
+          for (int c = 0; c < NV; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { const float z = v[q][c][e] - sum[q]; var[q] += z * z; }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) var[q] += __shfl_xor(var[q], o, 64);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int r = wave * 4 + q0 + q;
+          if (r < rows) {
+            const float rstd = 1.0f / sqrtf(var[q] / (float)(NV * 256) + a.eps);
+            const size_t at = (size_t)__builtin_amdgcn_readfirstlane(rs[i * RT + r]) * (S::CH * 8) + lane * 4;
+#pragma unroll
+            for (int c = 0; c < NV; ++c) {
+              const u16x4* norm = reinterpret_cast<const u16x4*>(smem + S::OFF_NORM) + c * 64 + lane;
+              const f32x4 gg = to_f32(norm[0]), bb = to_f32(norm[NV * 64]);
+              f32x4 y;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) y[e] = (v[q][c][e] - sum[q]) * rstd * gg[e] + bb[e];
+              *reinterpret_cast<f32x4*>(a.x32 + at + c * 256) = a.x32_is_sum ? v[q][c] : y;
+              *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(a.Y) + at + c * 256) = u32x2{pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3])};
+            }
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (i + 1 < m) HMI_LOAD_RESID(i + 1, 0)
+      __builtin_amdgcn_sched_barrier(0);
+    } else
     // ---- wavefronts 4-7 stream the finished rows out; wavefronts 0-3 make sure the next
     //      unit's rows have landed.  After the barrier the buffer is free for unit i + 2.
     if (wave >= 4) {
@@ -287,9 +395,8 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
         for (int r3 = 0; r3 < NV; ++r3)
           if (8 * g + ro[r3] < rows) {
             u32x4* dst = reinterpret_cast<u32x4*>(Y + (size_t)orow[r3] * S::ROWB + (sw[r3] ^ ((g & 1) << 7)));
-            // a result that goes to the caller leaves without taking lines of L2 (the adapter-only block: 4.7 -> 5.0 TB/s);
-            // inside a shared layer the next kernel reads it at once, and there the plain store is the faster one
-            if (STREAM) __builtin_nontemporal_store(v[r3], dst); else *dst = v[r3];
+            // a result that goes to the caller leaves without taking lines of L2 (4.7 -> 5.0 TB/s)
+            __builtin_nontemporal_store(v[r3], dst);
           }
       }
     } else if (i + 1 < m) {
@@ -302,13 +409,19 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
 #undef HMI_LOAD_WD
 #undef HMI_LOAD_BD
 #undef HMI_LOAD_WU
+#undef HMI_LOAD_RESID
+}
+
+template <int NV>
+decltype(&adapter_bf16_kernel<NV, false, OUT_STREAM>) pick(const AdapterArgs& a) {
+  if (a.resid_f32) return a.weights_once ? adapter_bf16_kernel<NV, true, LN_RESID_F32> : adapter_bf16_kernel<NV, false, LN_RESID_F32>;
+  return a.weights_once ? adapter_bf16_kernel<NV, true, LN_RESID_BF16> : adapter_bf16_kernel<NV, false, LN_RESID_BF16>;
 }
 
 template <int NV>
 void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   using S = Shape<NV>;
-  auto kern = a.stream_out ? adapter_bf16_kernel<NV, false, true>
-                           : a.weights_once ? adapter_bf16_kernel<NV, true, false> : adapter_bf16_kernel<NV, false, false>;
+  auto kern = a.stream_out ? adapter_bf16_kernel<NV, false, OUT_STREAM> : pick<NV>(a);
   const int n_cu = rt.n_cu >= 1 ? rt.n_cu : 256;
   const long long U = (long long)a.n_tiles128 * 4;
   if (U <= 0) return;
@@ -320,12 +433,10 @@ void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
 
 template <int NV>
 void allow_lds() {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(adapter_bf16_kernel<NV, false, false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            Shape<NV>::LDS);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(adapter_bf16_kernel<NV, true, false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            Shape<NV>::LDS);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(adapter_bf16_kernel<NV, false, true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            Shape<NV>::LDS);
+  for (auto kern : {adapter_bf16_kernel<NV, false, OUT_STREAM>, adapter_bf16_kernel<NV, false, LN_RESID_BF16>,
+                    adapter_bf16_kernel<NV, true, LN_RESID_BF16>, adapter_bf16_kernel<NV, false, LN_RESID_F32>,
+                    adapter_bf16_kernel<NV, true, LN_RESID_F32>})
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Shape<NV>::LDS);
 }
 
 }  // namespace
@@ -355,7 +466,8 @@ bool adapter_bf16_supported(int d, int rank) { return rank == RANK && d % 256 ==
 
 // Preconditions (checked by the caller): adapter_bf16_supported(d, rank); which_tiles names
 // the list of 128-row m-tiles and n_tiles128 its length; both matrices of every slot in
-// the batch are in MFMA operand order; X and Y are distinct, 16-byte aligned [N, d] arrays.
+// the batch are in MFMA operand order; X, Y, resid and x32 are 16-byte aligned [N, d] arrays, Y apart from X unless ln_g is
+// set (a unit's rows are read before they are written, and no other unit has them).
 void launch_adapter_bf16(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   switch (a.d / 256) {
     case 1: return launch_nv<1>(a, rt, s);

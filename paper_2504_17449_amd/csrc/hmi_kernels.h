@@ -103,13 +103,18 @@ constexpr int kF32TileM = 64;
 // through row_src like the GEMMs.  Both matrices must be stored in MFMA operand order
 // (pack_adapter_operand) inside the slot images.
 struct AdapterArgs {
-  const void* X; void* Y;             // bf16 [N, d], distinct
+  const void* X; void* Y;             // bf16 [N, d]
   const char* pool; size_t slot_stride;
   size_t wd_off, bd_off, wu_off, bu_off;  // byte offsets inside a slot (layer included)
   int d;
   int which_tiles, n_tiles128;        // index and length of the list of 128-row m-tiles
-  int stream_out;                     // 1: Y is not read again soon (the caller's result): stored with the non-temporal hint
+  int stream_out;                     // 1: Y is the caller's result, stored with the non-temporal hint.  0: the LayerNorm below
   int weights_once;                   // 1: a tenant's matrices are read by about one unit of rows (a decode step): loaded with the non-temporal hint
+  // LayerNorm behind the adapter (stream_out = 0): Y = LN(resid + adapted X) in bf16, x32 = the same in fp32 or, with
+  // x32_is_sum, the sum itself; one gain and shift for all rows.
+  const void* resid; int resid_f32;   // [N, d], bf16 or fp32
+  const uint16_t* ln_g; const uint16_t* ln_b; float eps;
+  float* x32; int x32_is_sum;
 };
 bool adapter_bf16_supported(int d, int rank);
 void launch_adapter_bf16(const AdapterArgs& a, const Route& rt, hipStream_t s);

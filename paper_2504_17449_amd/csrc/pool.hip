@@ -1085,22 +1085,29 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
       launch_attention(a, rt, s);
     };
 
-    // the tenant's adapter on the attention output: w_act -> w_ctx, tenant route (composite blocks)
-    auto adapter_step = [&]() {
+    // the tenant's adapter on the attention output w_act, tenant route, and the shared LayerNorm of the sum with the layer's
+    // input (composite blocks): w_act = LN(in_res + a'), w_x1 = that in fp32 or the sum itself
+    auto adapter_norm = [&](int tg, int tb, bool sum) {
       const int r = p->rank;
       if (p->adapter_fused) {
         AdapterArgs a{};
-        a.X = p->w_act; a.Y = p->w_ctx; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
+        a.X = p->w_act; a.Y = p->w_act; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
         a.wd_off = lay + p->tl[T_W1].off; a.bd_off = lay + p->tl[T_B1].off;
         a.wu_off = lay + p->tl[T_W2].off; a.bu_off = lay + p->tl[T_B2].off;
         a.d = d; a.which_tiles = 1; a.n_tiles128 = n_mtiles[1];
         a.weights_once = (long long)N <= 32LL * n_mtiles[1];
+        a.resid = in_res; a.resid_f32 = in_res_f32;
+        a.ln_g = reinterpret_cast<const uint16_t*>(p->d_shared + slay + p->stl[tg].off);
+        a.ln_b = reinterpret_cast<const uint16_t*>(p->d_shared + slay + p->stl[tb].off);
+        a.eps = c.ln_eps; a.x32 = p->w_x1; a.x32_is_sum = sum;
         ProfSpan ps(p, HMI_KERNEL_GEMM);
         launch_adapter_bf16(a, rt, s);
-      } else {
-        gemm(p->w_act, d, T_W1, T_B1, r, d, EPI_BIAS_RELU, p->w_hmid, r, nullptr, 0, false, false, nullptr);
-        gemm(p->w_hmid, r, T_W2, T_B2, d, r, EPI_BIAS_RESID, p->w_ctx, d, p->w_act, d, f32, f32, nullptr);
+        return;
       }
+      gemm(p->w_act, d, T_W1, T_B1, r, d, EPI_BIAS_RELU, p->w_hmid, r, nullptr, 0, false, false, nullptr);
+      gemm(p->w_hmid, r, T_W2, T_B2, d, r, EPI_BIAS_RESID, p->w_ctx, d, p->w_act, d, f32, f32, nullptr);
+      if (sum) slnorm(in_res, in_res_f32, p->w_ctx, nullptr, p->w_act, tg, tb, p->w_x1);
+      else slnorm(in_res, in_res_f32, p->w_ctx, p->w_x1, p->bf16 ? p->w_act : nullptr, tg, tb);
     };
 
     switch (c.block) {
@@ -1143,8 +1150,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
         sgemm(p->w_act, d, A_WQKV, A_BQKV, 3 * d, d, EPI_BIAS, p->w_qkv, 3 * d, nullptr, 0, false, false);
         attention(true);
         sgemm(p->w_ctx, d, A_WO, A_BO, d, d, EPI_BIAS, p->w_act, d, nullptr, 0, false, false);
-        adapter_step();                                                     // w_act -> w_ctx
-        slnorm(in_res, in_res_f32, p->w_ctx, nullptr, p->w_act, A_LN2G, A_LN2B, p->w_x1);   // x1 = x + a', LN2(x1)
+        adapter_norm(A_LN2G, A_LN2B, true);                                 // x1 = x + a', LN2(x1)
         sgemm(p->w_act, d, A_W1, A_B1, f, d, EPI_BIAS_GELU, p->w_hmid, f, nullptr, 0, false, false);
         if (last) sgemm(p->w_hmid, f, A_W2, A_B2, d, f, EPI_BIAS_RESID, y, d, p->w_x1, d, true, f32 || y_f32);
         else sgemm(p->w_hmid, f, A_W2, A_B2, d, f, EPI_BIAS_RESID, p->w_y32, d, p->w_x1, d, true, true);
@@ -1156,8 +1162,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
         sgemm(in_st, d, A_WQKV, A_BQKV, 3 * d, d, EPI_BIAS, p->w_qkv, 3 * d, nullptr, 0, false, false);
         attention(false);
         sgemm(p->w_ctx, d, A_WO, A_BO, d, d, EPI_BIAS, p->w_act, d, nullptr, 0, false, false);
-        adapter_step();                                                     // w_act -> w_ctx
-        slnorm(in_res, in_res_f32, p->w_ctx, p->w_x1, p->bf16 ? p->w_act : nullptr, A_LN1G, A_LN1B);
+        adapter_norm(A_LN1G, A_LN1B, false);
         sgemm(p->bf16 ? (const void*)p->w_act : (const void*)p->w_x1, d, A_W1, A_B1, f, d, EPI_BIAS_GELU,
               p->w_hmid, f, nullptr, 0, false, false);
         sgemm(p->w_hmid, f, A_W2, A_B2, d, f, EPI_BIAS_RESID, p->w_z, d, p->w_x1, d, true, true);
