@@ -39,6 +39,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));   // in the caller's result, which may begin at any float
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
       }
       const size_t off = orow * g.ldc + col;
       if (!BF16 || g.out_f32) {
-        f32x4* cp = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + off);
+        f32x4_any* cp = reinterpret_cast<f32x4_any*>(reinterpret_cast<float*>(g.C) + off);
 #pragma unroll
         for (int q = 0; q < 4; ++q) cp[q] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
       }

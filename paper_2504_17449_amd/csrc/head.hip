@@ -24,6 +24,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));   // the caller's scores may begin at any float
 
 constexpr int kChunkRows = 32;
 constexpr int kInFlight = 6;    // k-steps whose operands a wavefront has in flight (12: half as many workgroups fit a compute unit)
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(256, 4) void head_kernel(HeadArgs a, Route rt) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int c = 32 * b + 16 * lh + 4 * q;
-          if (c < a.max_classes) *reinterpret_cast<f32x4*>(sc + c) = f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]};
+          if (c < a.max_classes) *reinterpret_cast<f32x4_any*>(sc + c) = f32x4{acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]};
         }
     } else {
 #pragma unroll

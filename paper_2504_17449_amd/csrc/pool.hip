@@ -185,6 +185,7 @@ struct hmi_pool {
   char *w_qkv = nullptr, *w_ctx = nullptr, *w_hmid = nullptr, *w_act = nullptr;
   float *w_z = nullptr, *w_x1 = nullptr, *w_y32 = nullptr;
   char* w_yst = nullptr;       // inter-layer activations of a multi-layer call
+  char* w_x = nullptr;         // a batch whose x is not 16-byte aligned (made for the first of them)
 
   // host scratch, sized at creation: the forward calls allocate nothing
   std::vector<uint32_t> mark;       // [tenant] epoch when last seen in a batch
@@ -268,6 +269,7 @@ void free_all(hmi_pool* p) {
   (void)hipFree(p->d_head_meta);
   (void)hipFree(p->d_kv);
   (void)hipFree(p->d_idx);
+  (void)hipFree(p->w_x);
   (void)hipFree(p->w_qkv); (void)hipFree(p->w_ctx); (void)hipFree(p->w_hmid);
   (void)hipFree(p->w_act); (void)hipFree(p->w_z); (void)hipFree(p->w_x1);
   (void)hipFree(p->w_y32); (void)hipFree(p->w_yst);
@@ -960,6 +962,14 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   {
     int32_t rc = make_resident(layer_begin, true, &need_copy);
     if (rc != HMI_OK) return rc;
+  }
+
+  // The kernels read rows in 16-byte pieces, the GEMMs by direct-to-LDS copies: rows that begin elsewhere are moved first.
+  if (reinterpret_cast<uintptr_t>(x) % 16) {
+    const size_t row = (size_t)c.d_model * p->esize;
+    if (!p->w_x) HIP_TRY(p, hipMalloc(&p->w_x, (size_t)c.max_tokens * row));
+    HIP_TRY(p, hipMemcpyAsync(p->w_x, x, (size_t)N * row, hipMemcpyDeviceToDevice, p->compute));
+    x = p->w_x;
   }
 
   // ---- index arrays to the device
