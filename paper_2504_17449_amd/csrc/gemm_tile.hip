@@ -273,7 +273,7 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
           for (int e = 0; e < 16; ++e) v[e] = gelu_poly(v[e]);
         } else {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) v[e] = gelu_f32(v[e]);
+          for (int e = 0; e < 16; ++e) v[e] = BF16 ? gelu_f32(v[e]) : gelu_erf(v[e]);
         }
       } else if (g.epi == EPI_BIAS_RELU) {
 #pragma unroll
