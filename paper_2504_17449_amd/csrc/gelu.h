@@ -9,8 +9,9 @@ namespace hmi {
 // Ten fp32 vector-ALU operations (40 clocks a wavefront), no transcendental: for the epilogues of large bf16 launches,
 // where the matrix cores wait for it.  (The same polynomial in packed fp16 is 1.5 % of a launch faster, but its rounding
 // lifts the error to 5e-4 near x = -3.8, where the result itself is only -2e-4: not used.)
+// GELU(+inf) = +inf; a NaN stays one: the clamp is the minimum that hands NaN on, one instruction like fminf's.
 __device__ __forceinline__ float gelu_poly(float x) {
-  const float a = fminf(fabsf(x), 4.0f);
+  const float a = __builtin_elementwise_minimum(fabsf(x), 4.0f);
   const float u = fmaf(a, 0.5f, -1.0f);
   float q = -0.0411399369f;
   q = fmaf(q, u, 0.0706263031f);
@@ -25,10 +26,12 @@ __device__ __forceinline__ float gelu_poly(float x) {
 // Phi(-a) = exp(-a^2 / 2) t P(t), t = 1 / (1 + 0.3 a): exp(a^2 / 2) Phi(-a) is smooth in t, and the degree-7 P was fitted
 // (least squares, reweighted towards equal relative errors) to 1.5e-7 relative over [0, 14], beyond which exp underflows.
 // For results that are rounded to bf16 behind it: errors of 1e-6 of the value down to x = -4, and small in the negative tail
-// too, where 0.5 x (1 + erf(x / sqrt 2)) cancels (2.7e-6 down to -8, 8e-6 to -13, from rounding exp2's argument).  Twelve operations and two
-// transcendentals (80 clocks a wavefront; erff takes about twice that).
+// too, where 0.5 x (1 + erf(x / sqrt 2)) cancels (2.7e-6 down to -8, 8e-6 to -13, from rounding exp2's argument).
+// Fourteen operations and two transcendentals (88 clocks a wavefront; erff takes about twice that).
+// What is not finite comes out as x Phi(x) has it: +inf for +inf, NaN for -inf (infinity times zero) and NaN.  Hence a is
+// |x| only below 14: above, where nothing is taken off x any more, an infinite a would meet t = 0.
 __device__ __forceinline__ float gelu_f32(float x) {
-  const float a = fabsf(x);
+  const float a = __builtin_elementwise_maximum(-x, __builtin_elementwise_minimum(x, 14.0f));   // both hand NaN on
   const float t = __builtin_amdgcn_rcpf(fmaf(0.3f, a, 1.0f));
   float p = 0.03567523509263992f;
   p = fmaf(p, t, -0.15720497071743011f);
