@@ -19,7 +19,9 @@
 //     line) by direct-to-LDS copies into a ring of STAGES, one barrier per stage.
 //   * A 16-byte chunk of a row is one fragment read: one v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32
 //     (element e of the two lane halves' chunks is one k-step of two; the k order inside a stage is the same for both
-//     operands, so it does not matter that it is not ascending).
+//     operands, so it does not matter that it is not ascending).  fp32 products go to two accumulators in turn: a sum of half
+//     as many, whose rounding errors are 0.7 of one chain's (in one chain fp32 layers were 1.3 % further from 64 bits than
+//     the vector ALU's fused chain, at the same speed).
 //   * Weights are the MFMA's first operand, in a permuted row order, so that a lane ends up with 16 consecutive columns
 //     of one row of C: the epilogue reads residuals and writes results straight from the accumulators in 16-byte pieces.
 //     Accumulators start at the bias.
@@ -65,13 +67,16 @@ __device__ __forceinline__ int swz_w(int row) { return ((row >> 1) & 3) | (((row
 __device__ __forceinline__ int perm_w(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
 
 template <bool BF16>
-__device__ __forceinline__ void mfma_chunk(const u32x4& w, const u32x4& x, f32x16& acc) {
+__device__ __forceinline__ void mfma_chunk(const u32x4& w, const u32x4& x, f32x16& acc, f32x16& acc2) {
   if (BF16) {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
   } else {
     const f32x4 wf = __builtin_bit_cast(f32x4, w), xf = __builtin_bit_cast(f32x4, x);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[e], xf[e], acc, 0, 0, 0);
+    for (int e = 0; e < 4; e += 2) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[e], xf[e], acc, 0, 0, 0);
+      acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[e + 1], xf[e + 1], acc2, 0, 0, 0);
+    }
   }
 }
 
@@ -179,6 +184,7 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
   const int fx_base = rx * ROW_BYTES + ((lh ^ swz_a(rx)) << 4);       // fragment offsets inside a stage (k-step ks: XOR ks << 5)
   const int fw_base = BM * ROW_BYTES + rw * ROW_BYTES + ((lh ^ swz_w(rw)) << 4);
   f32x16 acc[TM][TN];                       // start at the bias
+  f32x16 acc2[TM][TN];                      // fp32: every other product's sum, from zero
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int col = min(n0 + wn * WTN + j * 32 + 16 * lh, g.n_out - 16);   // a lane's 16 columns exist or do not as a whole
@@ -200,6 +206,8 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
     }
 #pragma unroll
     for (int i = 1; i < TM; ++i) acc[i][j] = acc[0][j];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) acc2[i][j] = f32x16{};
   }
   int out_row[TM];                          // where this lane's rows of the tile go in C
 #pragma unroll
@@ -220,7 +228,7 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
 #define HMI_MULTIPLY(KS)                                                                           \
   {                                                                                                \
     _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                 \
-      _Pragma("unroll") for (int j = 0; j < TN; ++j) mfma_chunk<BF16>(fw[KS][j], fx[KS][i], acc[i][j]); \
+      _Pragma("unroll") for (int j = 0; j < TN; ++j) mfma_chunk<BF16>(fw[KS][j], fx[KS][i], acc[i][j], acc2[i][j]); \
     __builtin_amdgcn_sched_barrier(0);                                                             \
   }
   // Fragments are read two to three k-steps ahead of their products.  The barrier of a stage stands in the middle of the
@@ -267,6 +275,7 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
       const int col = n0 + wn * WTN + j * 32 + 16 * lh;
       if (col >= g.n_out) continue;
       f32x16 v = acc[i][j];
+      if (!BF16) v += acc2[i][j];
       if (g.epi == EPI_BIAS_GELU) {
         if (BF16 && g.gelu_poly) {
 #pragma unroll
