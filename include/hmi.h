@@ -126,6 +126,8 @@ int32_t hmi_pool_load_shared(hmi_pool_t* pool, int32_t layer, const void* const*
 /* The hot path (Sec. 6.3): y[rows of request r] = block_{tenant_ids[r]}(x[rows of request r]).
  * x, y: DEVICE, [N, d_model] packed in request order (request r owns rows
  * tok_off[r] .. tok_off[r]+seq_lens[r]), pool dtype, x != y, x is not modified.
+ * They may begin at any element; an x off a 16-byte boundary is copied to a buffer of the pool
+ * first (allocated in the first such call).
  * tenant_ids, seq_lens: HOST int32[n_requests]; copied before return.
  * Work is enqueued on compute_stream and the call returns without waiting for it.
  * Errors are detected before anything is enqueued, so y is untouched on error:
@@ -142,6 +144,7 @@ int32_t hmi_layer_forward(hmi_pool_t* pool, int32_t layer, const void* x, void* 
  * the kernels work from (request order, segment offsets, row map, tile lists) live in a static
  * device array of the library (0.17 MB per GPU, held until the process ends) instead of the pool's
  * own allocation, and the call itself allocates and frees nothing, on the device or the host.
+ * An x off a 16-byte boundary is copied to y first, which then has to be on one (else HMI_ERR_ARG).
  * Limits: a bf16 ADAPTER pool without host_tier whose forward is one kernel (rank d_ff = 64,
  * d_model 256 / 512 / 768, n_layers = 1), else HMI_ERR_ARG; n_requests <= 256 and at most 32 768
  * tokens (and the pool's own bounds), else HMI_ERR_SHAPE.  Other arguments, errors (y untouched)

@@ -466,8 +466,8 @@ bool adapter_bf16_supported(int d, int rank) { return rank == RANK && d % 256 ==
 
 // Preconditions (checked by the caller): adapter_bf16_supported(d, rank); which_tiles names
 // the list of 128-row m-tiles and n_tiles128 its length; both matrices of every slot in
-// the batch are in MFMA operand order; X, Y, resid and x32 are 16-byte aligned [N, d] arrays, Y apart from X unless ln_g is
-// set (a unit's rows are read before they are written, and no other unit has them).
+// the batch are in MFMA operand order; X, resid and x32 are 16-byte aligned [N, d] arrays, and so is Y where ln_g is set.  Y may
+// be X (a unit's rows are in LDS before they are written, and no other unit has them), else they do not overlap.
 void launch_adapter_bf16(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   switch (a.d / 256) {
     case 1: return launch_nv<1>(a, rt, s);

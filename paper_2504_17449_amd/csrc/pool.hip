@@ -185,9 +185,9 @@ struct hmi_pool {
   char *w_qkv = nullptr, *w_ctx = nullptr, *w_hmid = nullptr, *w_act = nullptr;
   float *w_z = nullptr, *w_x1 = nullptr, *w_y32 = nullptr;
   char* w_yst = nullptr;       // inter-layer activations of a multi-layer call
-  char* w_x = nullptr;         // a batch whose x is not 16-byte aligned (made for the first of them)
+  char* w_x = nullptr;         // a batch whose x is not 16-byte aligned (made in the first such call)
 
-  // host scratch, sized at creation: the forward calls allocate nothing
+  // host scratch, sized at creation: the forward calls allocate nothing (but w_x above, once)
   std::vector<uint32_t> mark;       // [tenant] epoch when last seen in a batch
   std::vector<int32_t> tok_count;   // [tenant]
   std::vector<int32_t> distinct;    // capacity max_requests
@@ -1257,6 +1257,11 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
                                 "(rank 64, d_model 256 / 512 / 768, one layer)");
   if (R < 0 || !x || !y || !tenant_ids || !seq_lens) return fail(p, HMI_ERR_ARG, "null pointer or negative request count");
   if (x == y) return fail(p, HMI_ERR_ARG, "x and y must be different buffers");
+  // The kernel copies rows of x to LDS in 16-byte pieces.  A batch that begins elsewhere is moved to y first and adapted there
+  // (the call may not allocate, and y is the only other room for it).
+  const bool move_x = reinterpret_cast<uintptr_t>(x) % 16 != 0;
+  if (move_x && reinterpret_cast<uintptr_t>(y) % 16)
+    return fail(p, HMI_ERR_ARG, "x and y both begin off a 16-byte boundary");
   if (layer != 0) return fail(p, HMI_ERR_ARG, "layer %d outside [0,1)", layer);
   if (R > c.max_requests || R > kStaticMaxRequests)
     return fail(p, HMI_ERR_SHAPE, "%d requests > limit %d", R, std::min(c.max_requests, kStaticMaxRequests));
@@ -1319,6 +1324,10 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
   rt.n_cu = p->rt.n_cu;
   launch_router(rt, R, (int)N, s);
   if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
+  if (move_x) {
+    HIP_TRY(p, hipMemcpyAsync(y, x, (size_t)N * c.d_model * p->esize, hipMemcpyDeviceToDevice, s));
+    x = y;
+  }
   AdapterArgs a{};
   a.X = x; a.Y = y; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
   a.wd_off = p->tl[T_W1].off; a.bd_off = p->tl[T_B1].off;

@@ -17,9 +17,10 @@ def shifted(t, lead):
 
 @pytest.mark.parametrize("block,dtype,d,lead", [
     (synth.BLOCK_FFN, "f32", 64, 1), (synth.BLOCK_DEC_PRELN, "f32", 128, 3), (synth.BLOCK_ENC_ADAPTER, "f32", 64, 2),
-    (synth.BLOCK_FFN, "bf16", 64, 2), (synth.BLOCK_ENC_POSTLN, "bf16", 256, 1)])
+    (synth.BLOCK_FFN, "bf16", 64, 2), (synth.BLOCK_ENC_POSTLN, "bf16", 256, 1),
+    (synth.BLOCK_ADAPTER, "bf16", 256, 1), (synth.BLOCK_ADAPTER, "bf16", 320, 4)])   # one kernel; two GEMMs
 def test_hidden_states_from_any_address(hmi, block, dtype, d, lead):
-    wl = small(block, dtype, d_model=d, d_ff=4 * d, n_heads=d // 64, seq_max=70, n_requests=9)
+    wl = small(block, dtype, d_model=d, d_ff=64 if block == synth.BLOCK_ADAPTER else 4 * d, n_heads=d // 64, seq_max=70, n_requests=9)
     ids, lens, x = harness.batch_to_device(wl)
     pool = harness.create_pool(wl)
     try:
@@ -57,5 +58,33 @@ def test_fp32_results_and_scores_to_any_float(hmi, max_classes):
             assert torch.equal(y, y_off) and torch.equal(scores, s_off)
             for room, size in ((y_room, y.numel()), (s_room, scores.numel())):
                 assert bool((room[:lead] == 7).all()) and bool((room[lead + size:] == 7).all())
+    finally:
+        pool.close()
+
+
+@pytest.mark.parametrize("d", [256, 512, 768])
+def test_static_call_from_any_address(hmi, d):
+    """hmi_layer_forward_static may not allocate: such an x goes through y, and is refused where y begins elsewhere too.  Several
+    units of 32 rows a workgroup, short ones among them, are adapted in place."""
+    wl = small(synth.BLOCK_ADAPTER, "bf16", d_model=d, d_ff=64, n_requests=130, seq_max=200)
+    ids, lens, x = harness.batch_to_device(wl)
+    pool = harness.create_pool(wl)
+    call = lambda a, b: hmi.hmi_layer_forward_static(pool.h, 0, a.data_ptr(), b.data_ptr(), ids, lens)
+    try:
+        harness.load_tenants(pool, wl)
+        y, y_off = torch.empty_like(x), torch.empty_like(x)
+        assert call(x, y) == hmi.HMI_OK
+        for lead in (1, 4):
+            x_off, _ = shifted(x, lead)
+            x_off.copy_(x)
+            y_off.fill_(3.0)
+            assert call(x_off, y_off) == hmi.HMI_OK
+            torch.cuda.synchronize()
+            assert torch.equal(y.view(torch.int16), y_off.view(torch.int16)) and torch.equal(x, x_off)
+            y_odd, y_room = shifted(y, 2)
+            y_odd.fill_(5.0)
+            assert call(x_off, y_odd) == hmi.HMI_ERR_ARG
+            torch.cuda.synchronize()
+            assert bool((y_odd == 5).all())
     finally:
         pool.close()
