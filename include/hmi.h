@@ -145,6 +145,8 @@ int32_t hmi_layer_forward(hmi_pool_t* pool, int32_t layer, const void* x, void* 
  * device array of the library (0.17 MB per GPU, held until the process ends) instead of the pool's
  * own allocation, and the call itself allocates and frees nothing, on the device or the host.
  * An x off a 16-byte boundary is copied to y first, which then has to be on one (else HMI_ERR_ARG).
+ * Captured into a graph, the call leaves its index arrays there: a replay repeats it whatever calls the
+ * pool has had in between (the tenants' weights are read where they lie when it runs).
  * Limits: a bf16 ADAPTER pool without host_tier whose forward is one kernel (rank d_ff = 64,
  * d_model 256 / 512 / 768, n_layers = 1), else HMI_ERR_ARG; n_requests <= 256 and at most 32 768
  * tokens (and the pool's own bounds), else HMI_ERR_SHAPE.  Other arguments, errors (y untouched)

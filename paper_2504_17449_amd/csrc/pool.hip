@@ -152,6 +152,9 @@ struct hmi_pool {
   int32_t* h_idx = nullptr;   // kIdxRing of them, 5 * max_requests + 1 apart
   hipEvent_t idx_ev[kIdxRing / kIdxMark] = {};
   uint64_t idx_use = 0;
+  bool capturing = false;     // the call under way is recorded into a graph:
+  std::vector<int32_t> cap_idx;   // its index arrays on the host, before index_publish() puts them into the graph ...
+  int32_t* d_cap_idx = nullptr;   // ... and where the graph writes them
   int32_t* d_idx = nullptr;   // all device int32 routing arrays, one allocation
   Route rt{};
   int last_R = 0;
@@ -287,17 +290,46 @@ void free_all(hmi_pool* p) {
   delete p;
 }
 
-// The pinned buffer a call's index arrays go through: kernels read it in place, so it is free again once they have run.
-// An event between two kernels costs the stream 5 us (32 % of an adapter-only step with the two it used to have), so one
-// event stands for kIdxMark consecutive uses: it is recorded behind the last of them (index_buffer_used) and waited for
-// before the first use of those buffers kIdxRing uses later, when kIdxMark later uses may still be in flight.
+// A call's index arrays (at most 5 * max_requests of them, or max_requests + 1): the caller fills the buffer of
+// index_buffer(), the kernels read what index_publish() returns, index_buffer_used() comes behind the kernel that does.
+//
+// Outside a graph that is a pinned buffer which kernels read in place, so it is free again once they have run.  An event
+// between two kernels costs the stream 5 us (32 % of an adapter-only step with the two it used to have), so one event stands
+// for kIdxMark consecutive uses: it is recorded behind the last of them (index_buffer_used) and waited for before the first
+// use of those buffers kIdxRing uses later, when kIdxMark later uses may still be in flight.
+//
+// A call that is being captured may neither wait for an event nor record one (the event would never happen, and calls outside
+// the graph would rely on it), and its replays may come at any time: it has no buffer of the ring.  Small kernels whose
+// arguments are the numbers themselves write them to d_cap_idx; the graph keeps the arguments.
+constexpr int kPutInts = 768;   // 3 of the 4 KB that kernel arguments may take
+struct PutInts { int32_t v[kPutInts]; };
+__global__ __launch_bounds__(256) void put_ints_kernel(PutInts from, int32_t* to, int n) {
+  for (int i = threadIdx.x; i < n; i += 256) to[i] = from.v[i];
+}
+
 int32_t index_buffer(hmi_pool* p, int32_t** out) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  // (the null stream cannot be captured; asking about another one costs a call 0.15 us)
+  if (p->compute) HIP_TRY(p, hipStreamIsCapturing(p->compute, &status));
+  p->capturing = status == hipStreamCaptureStatusActive;
+  if (p->capturing) { *out = p->cap_idx.data(); return HMI_OK; }
   const uint64_t u = p->idx_use;
   if (u >= (uint64_t)kIdxRing && u % kIdxMark == 0) HIP_TRY(p, hipEventSynchronize(p->idx_ev[u / kIdxMark % (kIdxRing / kIdxMark)]));
   *out = p->h_idx + u % kIdxRing * (5 * (size_t)p->cfg.max_requests + 1);
   return HMI_OK;
 }
-int32_t index_buffer_used(hmi_pool* p) {   // behind the kernel that reads it
+const int32_t* index_publish(hmi_pool* p, const int32_t* h, int n) {
+  if (!p->capturing) return h;
+  for (int i = 0; i < n; i += kPutInts) {
+    PutInts part;
+    const int m = std::min(n - i, kPutInts);
+    memcpy(part.v, h + i, sizeof(int32_t) * m);
+    hipLaunchKernelGGL(put_ints_kernel, dim3(1), dim3(256), 0, p->compute, part, p->d_cap_idx + i, m);
+  }
+  return p->d_cap_idx;
+}
+int32_t index_buffer_used(hmi_pool* p) {
+  if (p->capturing) return HMI_OK;
   const uint64_t u = p->idx_use++;
   if (u % kIdxMark == kIdxMark - 1) HIP_TRY(p, hipEventRecord(p->idx_ev[u / kIdxMark % (kIdxRing / kIdxMark)], p->compute));
   return HMI_OK;
@@ -520,6 +552,7 @@ static int32_t create_impl(const hmi_pool_config_t* cfg, hmi_pool_t** out) {
   p->distinct.reserve(c.max_requests);
   p->last_distinct.reserve(c.max_requests);
   p->ones.assign(c.max_requests, 1);
+  p->cap_idx.assign(5 * (size_t)c.max_requests + 1, 0);
 
   if (!c.host_tier) {
     for (int i = 0; i < 2; ++i) {
@@ -535,7 +568,8 @@ static int32_t create_impl(const hmi_pool_config_t* cfg, hmi_pool_t** out) {
   const size_t MT = (size_t)c.max_tokens;
   const size_t max_tiles0 = MT / p->tile_m[0] + Rm + 1;
   const size_t max_tiles1 = p->tile_m[1] ? MT / p->tile_m[1] + Rm + 1 : 0;
-  size_t n_i32 = 3 * (size_t)Rm            // ids, lens, req_slot
+  size_t n_i32 = 3 * (size_t)Rm            // (empty)
+                 + 5 * (size_t)Rm + 1      // index arrays of a captured call (index_publish)
                  + 3 * (size_t)Rm          // req_tenant, kv_slot, kv_pos
                  + Rm + (Rm + 1)           // perm, tok_off
                  + 2 * (size_t)Rm          // seg_tenant, seg_slot
@@ -549,10 +583,10 @@ static int32_t create_impl(const hmi_pool_config_t* cfg, hmi_pool_t** out) {
   if (dense) n_i32 += 2 * dense_segs + 1 + MT + 2 * (dense_tiles0 + dense_tiles1);
   CREATE_TRY(hipMalloc(&p->d_idx, n_i32 * sizeof(int32_t)));
   CREATE_TRY(hipMemset(p->d_idx, 0, n_i32 * sizeof(int32_t)));
-  int32_t* q = p->d_idx;
+  // (3 Rm words in front stay empty: where the arrays lie in their cache lines makes 25.2 or 25.4 us of a call of 8 requests)
+  int32_t* q = p->d_idx + 3 * (size_t)Rm;
   auto take = [&](size_t n) { int32_t* r = q; q += n; return r; };
   Route& rt = p->rt;
-  rt.tenant_ids = take(Rm); rt.seq_lens = take(Rm); rt.req_slot = take(Rm);
   rt.req_tenant = take(Rm); rt.kv_slot = take(Rm); rt.kv_pos = take(Rm);
   rt.perm = take(Rm); rt.tok_off = take(Rm + 1);
   rt.seg_tenant = take(Rm); rt.seg_slot = take(Rm);
@@ -563,6 +597,7 @@ static int32_t create_impl(const hmi_pool_config_t* cfg, hmi_pool_t** out) {
   rt.tile_row0[1] = max_tiles1 ? take(max_tiles1) : nullptr;
   rt.n_segments = take(1); rt.n_tiles[0] = take(1); rt.n_tiles[1] = take(1);
   rt.gemm_sched = take(kGemmSchedInts);
+  p->d_cap_idx = take(5 * (size_t)Rm + 1);
   rt.tile_m[0] = p->tile_m[0]; rt.tile_m[1] = p->tile_m[1];
   rt.key_bits = bits_for(c.max_tenants);
   rt.n_cu = n_cu;
@@ -810,7 +845,7 @@ int32_t hmi_plot_aggregate(hmi_pool_t* p, const void* table, int32_t n_entries, 
   h[0] = 0;
   for (int r = 0; r < R; ++r) h[r + 1] = h[r] + seq_lens[r];
   PlotArgs a{};
-  a.table = static_cast<const char*>(table); a.n_entries = n_entries; a.frag_ids = frag_ids; a.tok_off = h;
+  a.table = static_cast<const char*>(table); a.n_entries = n_entries; a.frag_ids = frag_ids; a.tok_off = index_publish(p, h, R + 1);
   a.x = static_cast<char*>(x); a.d = c.d_model;
   launch_plot_aggregate(a, R, longest, N, p->bf16, p->compute);
   if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
@@ -975,14 +1010,13 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   // ---- index arrays to the device
   int32_t* h = nullptr;
   if (const int32_t rc = index_buffer(p, &h); rc != HMI_OK) return rc;
-  const int Rm = c.max_requests;
   for (int r = 0; r < R; ++r) {
     h[r] = tenant_ids[r];
-    h[Rm + r] = seq_lens[r];
-    h[2 * Rm + r] = p->slot_of_tenant[tenant_ids[r]];
+    h[R + r] = seq_lens[r];
+    h[2 * R + r] = p->slot_of_tenant[tenant_ids[r]];
     if (kv != KV_NONE) {
-      h[3 * Rm + r] = seq_slots[r];
-      h[4 * Rm + r] = kv == KV_PREFILL ? 0 : p->kv_len[seq_slots[r]];
+      h[3 * R + r] = seq_slots[r];
+      h[4 * R + r] = kv == KV_PREFILL ? 0 : p->kv_len[seq_slots[r]];
     }
   }
   hipStream_t s = p->compute;
@@ -990,8 +1024,9 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
   // buffer: 3 R words over the host link, instead of a staging copy that costs a copy
   // engine hand-over (about 15 us) on either side.
   Route rt = p->rt;
-  rt.tenant_ids = h; rt.seq_lens = h + Rm; rt.req_slot = h + 2 * Rm;
-  if (kv != KV_NONE) { rt.kv_slot_in = h + 3 * Rm; rt.kv_pos_in = h + 4 * Rm; }
+  const int32_t* idx = index_publish(p, h, (kv != KV_NONE ? 5 : 3) * R);
+  rt.tenant_ids = idx; rt.seq_lens = idx + R; rt.req_slot = idx + 2 * R;
+  if (kv != KV_NONE) { rt.kv_slot_in = idx + 3 * R; rt.kv_pos_in = idx + 4 * R; }
   { ProfSpan ps(p, HMI_KERNEL_ROUTER); launch_router(rt, R, (int)N, s); }
   if (const int32_t rc = index_buffer_used(p); rc != HMI_OK) return rc;
   p->last_R = R;
@@ -1293,14 +1328,13 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
     HIP_TRY(p, hipStreamWaitEvent(s, p->copy_done.at_least(need_copy), 0));
     p->compute_waited_copy = need_copy;
   }
-  // index arrays: through one of the pool's pinned buffers, read in place by the router
+  // index arrays: through one of the pool's pinned buffers, read in place by the router, or as part of the graph
   int32_t* h = nullptr;
   if (const int32_t rc = index_buffer(p, &h); rc != HMI_OK) return rc;
-  const int Rm = c.max_requests;
   for (int r = 0; r < R; ++r) {
     h[r] = tenant_ids[r];
-    h[Rm + r] = seq_lens[r];
-    h[2 * Rm + r] = p->slot_of_tenant[tenant_ids[r]];
+    h[R + r] = seq_lens[r];
+    h[2 * R + r] = p->slot_of_tenant[tenant_ids[r]];
   }
   // routing arrays: fixed places inside this device's copy of `scratch`; the router writes every
   // entry the adapter kernel reads, so nothing has to be cleared between calls
@@ -1308,7 +1342,8 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
   auto take = [&](size_t n) { int32_t* r = q; q += n; return r; };
   constexpr size_t SR = kStaticMaxRequests;
   Route rt{};
-  rt.tenant_ids = h; rt.seq_lens = h + Rm; rt.req_slot = h + 2 * Rm;
+  const int32_t* idx = index_publish(p, h, 3 * R);
+  rt.tenant_ids = idx; rt.seq_lens = idx + R; rt.req_slot = idx + 2 * R;
   rt.req_tenant = take(SR); rt.kv_slot = take(SR); rt.kv_pos = take(SR);
   rt.perm = take(SR); rt.tok_off = take(SR + 1);
   rt.seg_tenant = take(SR); rt.seg_slot = take(SR);
