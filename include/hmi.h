@@ -126,8 +126,7 @@ int32_t hmi_pool_load_shared(hmi_pool_t* pool, int32_t layer, const void* const*
 /* The hot path (Sec. 6.3): y[rows of request r] = block_{tenant_ids[r]}(x[rows of request r]).
  * x, y: DEVICE, [N, d_model] packed in request order (request r owns rows
  * tok_off[r] .. tok_off[r]+seq_lens[r]), pool dtype, x != y, x is not modified.
- * They may begin at any element; an x off a 16-byte boundary is copied to a buffer of the pool
- * first (allocated in the first such call).
+ * An x off a 16-byte boundary is copied to a buffer of the pool first (allocated in the first such call).
  * tenant_ids, seq_lens: HOST int32[n_requests]; copied before return.
  * Work is enqueued on compute_stream and the call returns without waiting for it.
  * Errors are detected before anything is enqueued, so y is untouched on error:

@@ -385,46 +385,47 @@ void init_gemm_tile_kernels() {
 // It says nothing about weights that come from HBM or panels that are fetched again, so a launch that gives the
 // persistent kernel's workgroups more than one and a half tiles each is not weighed at all: it was the faster one for all
 // of those (two encoder layers of 177 tenants, 65 536 rows: 3.1 ms, with 128 x 256 tiles where the estimate is lower 3.4).
-void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
-  if (g.n_rows <= 0 || g.n_mtiles_list[1] <= 0) return;
+GemmKernel pick_gemm_bf16(const GemmArgs& g, const Route& rt) {
   const int n_cu = rt.n_cu >= kXcds ? rt.n_cu : 256;
   if (g.n_out % 32 == 0) {
     const bool few_rows = g.n_rows <= 32LL * g.n_mtiles_list[1];
     const long long items = (few_rows ? g.n_mtiles_list[1] : (g.n_rows + 31) / 32) * (long long)(g.n_out / 32);
-    if ((few_rows && !rt.identity) || (items <= n_cu && g.k >= 1536 && g.k % 256 == 0)) {
-      GemmArgs a = g;
-      a.which_tiles = 1;
-      a.n_mtiles = g.n_mtiles_list[1];
-      return launch_gemm_bf16_skinny(a, rt, s);
-    }
+    if ((few_rows && !rt.identity) || (items <= n_cu && g.k >= 1536 && g.k % 256 == 0)) return GEMM_STREAM;
   }
   const long long big_tiles = g.n_out % 256 == 0 && g.k >= 192 ? (long long)g.n_mtiles_list[0] * (g.n_out / 256) : 0;
-  auto persistent = [&]() {
-    GemmArgs a = g;
-    a.which_tiles = 0;
-    a.n_mtiles = g.n_mtiles_list[0];
-    launch_gemm_bf16_p256(a, rt, s);
-  };
-  if (2 * big_tiles > 3LL * n_cu) return persistent();
+  if (2 * big_tiles > 3LL * n_cu) return GEMM_PERSISTENT;
   const double stages = g.k / 64, act = g.epi == EPI_BIAS_GELU ? 1.0 : 0.0;
   auto estimate = [&](long long tiles, double stage, double tile, double gelu) {
     return (double)((tiles + n_cu - 1) / n_cu) * (stages * stage + tile + act * gelu);
   };
   double best = estimate(TileS::tiles(g, rt, 1), 0.20, 0.2, 0.4);
-  int which = 0;
-  auto consider = [&](int id, double t) { if (t < best) { best = t; which = id; } };
-  consider(1, estimate(TileM::tiles(g, rt, 1), 0.32, 0.3, 0.4));
-  if (g.n_out % 128 == 0) consider(2, estimate(TileL::tiles(g, rt, 1), 0.50, 2.3, 1.3));
+  GemmKernel which = GEMM_64x64;
+  auto consider = [&](GemmKernel id, double t) { if (t < best) { best = t; which = id; } };
+  consider(GEMM_128x64, estimate(TileM::tiles(g, rt, 1), 0.32, 0.3, 0.4));
+  if (g.n_out % 128 == 0) consider(GEMM_128x128, estimate(TileL::tiles(g, rt, 1), 0.50, 2.3, 1.3));
   if (g.n_out % 256 == 0) {
-    consider(3, estimate(TileXL::tiles(g, rt, 1), 0.90, 3.2, 2.6));
-    if (g.k >= 192) consider(4, estimate(big_tiles, 1.45, 4.0, 3.0));
+    consider(GEMM_128x256, estimate(TileXL::tiles(g, rt, 1), 0.90, 3.2, 2.6));
+    if (g.k >= 192) consider(GEMM_PERSISTENT, estimate(big_tiles, 1.45, 4.0, 3.0));
   }
-  switch (which) {
-    case 0: return TileS::launch(g, rt, 1, s);
-    case 1: return TileM::launch(g, rt, 1, s);
-    case 2: return TileL::launch(g, rt, 1, s);
-    case 3: return TileXL::launch(g, rt, 1, s);
-    default: return persistent();
+  return which;
+}
+
+void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
+  if (g.n_rows <= 0 || g.n_mtiles_list[1] <= 0) return;
+  GemmArgs a = g;
+  switch (pick_gemm_bf16(g, rt)) {
+    case GEMM_STREAM:
+      a.which_tiles = 1;
+      a.n_mtiles = g.n_mtiles_list[1];
+      return launch_gemm_bf16_skinny(a, rt, s);
+    case GEMM_64x64: return TileS::launch(g, rt, 1, s);
+    case GEMM_128x64: return TileM::launch(g, rt, 1, s);
+    case GEMM_128x128: return TileL::launch(g, rt, 1, s);
+    case GEMM_128x256: return TileXL::launch(g, rt, 1, s);
+    case GEMM_PERSISTENT:
+      a.which_tiles = 0;
+      a.n_mtiles = g.n_mtiles_list[0];
+      return launch_gemm_bf16_p256(a, rt, s);
   }
 }
 
@@ -434,3 +435,16 @@ void launch_gemm_f32(const GemmArgs& g, const Route& rt, hipStream_t s) {
 }
 
 }  // namespace hmi
+
+// The rule alone, for the tests: which kernel (GemmKernel) a bf16 launch of these sizes gets.  tiles256, tiles128: m-tiles of
+// 256 and 128 rows, summed over the batch's tenants (or of all rows, where the weights are shared).
+extern "C" int32_t hmi_internal_gemm_kernel(int32_t n_rows, int32_t tiles256, int32_t tiles128, int32_t n_out, int32_t k,
+                                            int32_t gelu, int32_t shared, int32_t n_cu) {
+  hmi::GemmArgs g{};
+  g.n_rows = n_rows; g.n_out = n_out; g.k = k; g.epi = gelu ? hmi::EPI_BIAS_GELU : hmi::EPI_BIAS;
+  g.n_mtiles_list[0] = tiles256; g.n_mtiles_list[1] = tiles128;
+  hmi::Route rt{};
+  rt.tile_m[0] = hmi::kBf16TileM0; rt.tile_m[1] = hmi::kBf16TileM1;
+  rt.identity = shared; rt.n_cu = n_cu;
+  return hmi::pick_gemm_bf16(g, rt);
+}

@@ -88,6 +88,9 @@ struct GemmArgs {
   int gelu_poly;                      // set by the launcher: which form of GELU the tile kernel's epilogue takes (gelu.h)
 };
 
+// The kernels a bf16 launch can get, and the rule that picks one (gemm_tile.hip).
+enum GemmKernel : int { GEMM_STREAM = 0, GEMM_64x64, GEMM_128x64, GEMM_128x128, GEMM_128x256, GEMM_PERSISTENT };
+GemmKernel pick_gemm_bf16(const GemmArgs& g, const Route& rt);
 void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s);
 void launch_gemm_f32(const GemmArgs& g, const Route& rt, hipStream_t s);
 // Persistent 256 x 256 tiles, 64-wide k-stages; needs n_out % 256 == 0, k % 64 == 0, k >= 192 and

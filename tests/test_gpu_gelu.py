@@ -7,6 +7,7 @@ import torch
 import synth
 from oracle import hmi_oracle as O
 from paper_2504_17449_amd import harness
+from tests.gemm_rule import kernel
 from tests.test_gpu_parity import small
 
 pytestmark = pytest.mark.gpu
@@ -46,26 +47,27 @@ def test_fp32_hidden_values_of_the_usual_size(hmi, spread):
 
 # the kernels that have a GELU; the polynomial's error bound holds for -inf as for every x below -4 (the limit is 0), the other
 # forms have x Phi(x) = -inf * 0 there
-FORMS = [("f32 tiles", "f32", 64, 128, 40, False), ("weight stream", "bf16", 256, 256, 3, False),
-         ("tiles, exact form", "bf16", 256, 256, 300, False), ("tiles, polynomial", "bf16", 256, 256, 2000, True),
-         ("persistent tiles", "bf16", 256, 4096, 6500, True)]
+FORMS = [("f32 tiles", "f32", 64, 128, 40, None, False), ("weight stream", "bf16", 256, 256, 3, "stream", False),
+         ("tiles, exact form", "bf16", 256, 256, 300, "64x64", False), ("tiles, polynomial", "bf16", 256, 256, 2000, "64x64", True),
+         ("persistent tiles", "bf16", 256, 4096, 6500, "persistent", True)]
 
 
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
-@pytest.mark.parametrize("what,dtype,d,f,rows,poly", FORMS, ids=[c[0] for c in FORMS])
-def test_one_hidden_value_that_is_not_finite(hmi, what, dtype, d, f, rows, poly, value):
+@pytest.mark.parametrize("dtype,d,f,rows,want,poly", [c[1:] for c in FORMS], ids=[c[0] for c in FORMS])
+def test_one_hidden_value_that_is_not_finite(hmi, dtype, d, f, rows, want, poly, value):
     """One infinity or NaN in the first tenant's b1, W2 = 1: every column of its rows is the sum of GELU(b1); the second tenant's
     three rows know nothing of it."""
     lens = [min(rows, 100)] * (rows // min(rows, 100)) + [3]
     ids = [0] * (len(lens) - 1) + [1]
+    assert want is None or kernel(ids, lens, f, d, gelu=True) == want
     b1 = np.zeros((2, f), np.float32)
     b1[0, 5], b1[1, 5] = value, 2.0
     y = activation(dtype, d, f, lens, ids, b1, np.ones((d, f), np.float32))
     with np.errstate(invalid="ignore"):
-        want = float(O.gelu(np.array([value]))[0])
+        gelu = float(O.gelu(np.array([value]))[0])
     if poly and value == -np.inf:
         assert np.abs(y[:-3]).max() <= 2e-4
     else:
-        np.testing.assert_array_equal(y[:-3], np.full_like(y[:-3], want))
+        np.testing.assert_array_equal(y[:-3], np.full_like(y[:-3], gelu))
     # 2e-4 of the polynomial, twice half a bf16 unit (the hidden value and the result)
     np.testing.assert_allclose(y[-3:], O.gelu(np.array([2.0]))[0], rtol=2.0 ** -8, atol=2e-4)

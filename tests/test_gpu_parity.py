@@ -7,6 +7,7 @@ import torch
 
 import synth
 from oracle import hmi_oracle as O
+from tests.gemm_rule import kernel
 from tests.oracle_side import compare, oracle_forward, rows_of
 
 pytestmark = pytest.mark.gpu
@@ -109,34 +110,38 @@ def test_layer_stack_in_one_call(hmi, block, dtype):
 @pytest.mark.parametrize("block", [synth.BLOCK_FFN, synth.BLOCK_ENC_POSTLN, synth.BLOCK_DEC_PRELN,
                                    synth.BLOCK_ENC_ADAPTER, synth.BLOCK_DEC_ADAPTER])
 def test_wide_bf16_blocks_ragged_every_row(hmi, block):
-    """Widths that are multiples of 256 with k >= 192 take the persistent 256 x 256 GEMM: ragged
-    segments of 1..300 rows (short tiles, clamped rows, several tiles per segment), every output
-    row compared.  d = 256 makes k = 256 (4 stages), f = 512 makes k = 512 and two n-tiles."""
+    """Widths that are multiples of 256, ragged segments of 1..300 rows (short tiles, clamped rows, several tiles per
+    segment), every output row compared.  Too few of them for the persistent GEMM (test_gpu_persistent.py): 128 x 64 tiles."""
     run_case(hmi, small(block, "bf16", d_model=256, d_ff=512, n_heads=4, n_requests=28, n_tenants=7,
                         hbm_slots=7, n_layers=2 if block == synth.BLOCK_FFN else 1))
 
 
-def test_persistent_gemm_more_tiles_than_workgroups(hmi):
-    """Hundreds of one-request tenants: ~1700 tiles for 256 workgroups, so every workgroup claims
-    tiles at run time beyond its two fixed ones; k = 192 is the shortest reduction the kernel takes."""
-    wl = small(synth.BLOCK_FFN, "bf16", d_model=192, d_ff=1024, n_requests=640, n_tenants=900,
-               hbm_slots=900, seq_min=1, seq_max=9, popularity="uniform")
+@pytest.mark.parametrize("requests,lo,hi,want", [(640, 1, 9, "stream"), (420, 34, 60, "persistent")])
+def test_hundreds_of_tenants(hmi, requests, lo, hi, want):
+    """Hundreds of tenants, most with one request: of 1..9 rows (their weights are streamed), of 34..60 rows (340 tiles of 256 x
+    256 in each of four column panels for 256 persistent workgroups, so every workgroup claims tiles at run time beyond its two
+    fixed ones; k = 192 is the shortest reduction that kernel takes)."""
+    wl = small(synth.BLOCK_FFN, "bf16", d_model=192, d_ff=1024, n_requests=requests, n_tenants=900,
+               hbm_slots=900, seq_min=lo, seq_max=hi, popularity="uniform")
+    assert kernel(*synth.batch_ids_lens(wl, 0), 1024, 192, gelu=True) == want
     run_case(hmi, wl)
     # the counters reset themselves: a second forward on a fresh pool object of another shape works as well
     run_case(hmi, small(synth.BLOCK_FFN, "bf16", d_model=256, d_ff=768, n_requests=300, n_tenants=300,
                         hbm_slots=300, seq_min=1, seq_max=5, popularity="uniform"), batch=1)
 
 
+@pytest.mark.parametrize("f,want", [(768, "128x64"), (6144, "persistent")])
 @pytest.mark.parametrize("seed", [15, 10])
-def test_persistent_gemm_long_segments_in_blocks_of_m_tiles(hmi, seed):
+def test_long_segments_in_blocks_of_m_tiles(hmi, seed, f, want):
     """Two tenants with thousands of rows each.  The persistent GEMM walks a long segment in blocks of
     eight m-tiles of 256 rows; seed 15 gives segments of 8 and 11 m-tiles (exactly one block; one block and a
     short one of three), seed 10 gives 16 and 5 (two full blocks; less than one), each with a ragged last
-    tile.  Every row compared."""
-    wl = small(synth.BLOCK_FFN, "bf16", d_model=256, d_ff=768, n_requests=24, n_tenants=2, hbm_slots=2,
+    tile.  f = 768 is too few tiles for it.  Every row compared."""
+    wl = small(synth.BLOCK_FFN, "bf16", d_model=256, d_ff=f, n_requests=24, n_tenants=2, hbm_slots=2,
                seq_min=100, seq_max=300, popularity="uniform", seed=seed)
     ids, lens = synth.batch_ids_lens(wl, 0)
     assert sorted(-(-int(lens[ids == t].sum()) // 256) for t in range(2)) == {15: [8, 11], 10: [5, 16]}[seed]
+    assert kernel(ids, lens, f, 256, gelu=True) == want
     run_case(hmi, wl)
 
 
@@ -214,8 +219,8 @@ def test_bf16_adapter_rank_64(hmi):
 def test_adapter_as_two_gemms(hmi, block, kw):
     """Where the one-kernel adapter does not apply (d = 1024: its rows do not fit LDS twice; an adapter-only pool of
     several layers: fp32 between the layers) the adapter runs as two grouped GEMMs; the up-projection has k = rank
-    = 64 or 128, below what the persistent kernel takes, so it goes to the general 256 x 256 kernel with direct-to-LDS
-    copies.  A few thousand rows (more than the small-batch kernel takes), every row compared."""
+    = 64 or 128, below what the persistent kernel takes: one or two stages of k for the kernel with a workgroup per
+    tile.  A few thousand rows (more than the weight-streaming kernel takes), every row compared."""
     run_case(hmi, small(block, "bf16", n_tenants=12, hbm_slots=12, n_requests=40, seq_min=1, seq_max=300, **kw))
 
 
@@ -610,28 +615,30 @@ def round_to_bf16(a) -> np.ndarray:
     return u.astype(np.uint32).view(np.float32)
 
 
-def test_gelu_of_the_persistent_gemm_alone_on_a_grid(hmi):
-    """The persistent bf16 GEMM evaluates GELU with a polynomial instead of erf.  This isolates it
+@pytest.mark.parametrize("d,requests,want", [(256, 12, "64x64"), (1024, 100, "persistent")])
+def test_gelu_polynomial_alone_on_a_grid(hmi, d, requests, want):
+    """Bf16 launches of more than 1 024 rows evaluate GELU with a polynomial instead of erf.  This isolates it
     through the C ABI: a pre-LN decoder pool whose attention weights, W1 and all biases but b1 are zero and whose
     W2 is the identity gives, for x = 0, y[row, j] = GELU(b1[j]) exactly as the kernel stored it (one non-zero
-    product per output, so nothing else rounds).  b1 is a grid over [-9, 9] (four tenants, 1 024 values, bf16
-    exact), beyond the point |x| = 4 where the polynomial is clamped.  Held to the polynomial's stated bound:
+    product per output, so nothing else rounds).  The tenants' b1 are a grid over [-9, 9] (four tenants, 1 024 values in
+    all, or in each tenant with every value in another column panel; bf16 exact), beyond the point |x| = 4 where the polynomial is clamped.  Held to the polynomial's stated bound:
     |error| <= 2e-4 from the fit, plus the bf16 rounding of the stored value (one ulp allowed)."""
     from paper_2504_17449_amd import harness
-    d = 256
-    wl = small(synth.BLOCK_DEC_PRELN, "bf16", d_model=d, d_ff=d, n_heads=4, n_tenants=4, hbm_slots=4)
+    wl = small(synth.BLOCK_DEC_PRELN, "bf16", d_model=d, d_ff=d, n_heads=d // 64, n_tenants=4, hbm_slots=4)
     grid = round_to_bf16(np.concatenate([np.linspace(-9.0, 9.0, 1000), [-4.0, 4.0, 0.0, -0.0], np.linspace(-0.02, 0.02, 20)])
                          .astype(np.float32))
-    assert grid.size == 4 * d
+    assert grid.size == 1024
+    grids = [np.roll(grid, -256 * t)[:d] for t in range(4)]
     zeros = lambda *shape: np.zeros(shape, np.float32)
-    ids = np.repeat(np.arange(4, dtype=np.int32), 3)            # 12 requests of 256 rows: enough rows for the persistent kernel
-    lens = np.full(12, 256, np.int32)
-    pool = harness.create_pool(wl, max_requests=12, max_tokens=int(lens.sum()))
+    ids = np.repeat(np.arange(4, dtype=np.int32), requests // 4)
+    lens = np.full(requests, 256, np.int32)
+    assert kernel(ids, lens, d, d, gelu=True) == want
+    pool = harness.create_pool(wl, max_requests=requests, max_tokens=int(lens.sum()))
     weights = {}
     try:
         for t in range(4):
             w = {"wqkv": zeros(3 * d, d), "bqkv": zeros(3 * d), "wo": zeros(d, d), "bo": zeros(d),
-                 "ln1_g": np.ones(d, np.float32), "ln1_b": zeros(d), "w1": zeros(d, d), "b1": grid[t * d:(t + 1) * d],
+                 "ln1_g": np.ones(d, np.float32), "ln1_b": zeros(d), "w1": zeros(d, d), "b1": grids[t],
                  "w2": np.eye(d, dtype=np.float32), "b2": zeros(d), "ln2_g": np.ones(d, np.float32), "ln2_b": zeros(d)}
             weights[t] = w
             names = [n for n, _, _ in synth.tensor_specs(wl)]
@@ -643,20 +650,21 @@ def test_gelu_of_the_persistent_gemm_alone_on_a_grid(hmi):
         y_gpu = harness.device_to_f64(y)
     finally:
         pool.close()
+    # one row of the oracle per tenant (= GELU(b1[j])): all rows of a tenant are the same
     wof = lambda t: {k: v.astype(np.float64) for k, v in weights[t].items()}
-    y_ref = O.layer_forward(wl.block, np.zeros((int(lens.sum()), d)), ids, lens, wof, wl.n_heads, wl.ln_eps)
-    g = y_ref                                                    # = GELU(b1[j]) in every row of the tenant
-    np.testing.assert_allclose(y_ref[0], O.gelu(grid[:d].astype(np.float64)), rtol=0, atol=1e-12)
-    err = np.abs(y_gpu - y_ref)
+    g = O.layer_forward(wl.block, np.zeros((4, d)), np.arange(4, dtype=np.int32), np.ones(4, np.int32), wof, wl.n_heads, wl.ln_eps)
+    np.testing.assert_allclose(g, O.gelu(np.array(grids).astype(np.float64)), rtol=0, atol=1e-12)
+    y_gpu = y_gpu.reshape(4, -1, d)
+    assert np.array_equal(y_gpu, np.broadcast_to(y_gpu[:, :1], y_gpu.shape))
+    err = np.abs(y_gpu[:, 0] - g)
     bound = 2e-4 + 2.0 ** -8 * np.abs(g) + 1e-6                  # fit + bf16 rounding (one ulp) + fp32 evaluation
-    worst = int(np.argmax(err - bound))
+    worst = np.unravel_index(int(np.argmax(err - bound)), err.shape)
     print(f"  GELU grid: max |error| {err.max():.3e}, worst excess over the bound {(err - bound).max():.3e} "
-          f"at x = {grid[(ids[worst // d // 256] * d) + worst % d]:.4f}", flush=True)
+          f"at x = {grids[worst[0]][worst[1]]:.4f}", flush=True)
     assert (err <= bound).all()
-    # rows of one tenant are identical, and the negative tail is not flushed to zero before the clamp
-    assert np.array_equal(y_gpu[0], y_gpu[255])
+    # the negative tail is not flushed to zero before the clamp
     i3 = int(np.argmin(np.abs(grid + 3.0)))                      # GELU(-3) = -4.05e-3
-    assert y_gpu[(i3 // d) * 3 * 256, i3 % d] < -3.5e-3
+    assert y_gpu[i3 // 256, 0, i3 % 256] < -3.5e-3
 
 
 def test_bert_ffn_full_size_every_request(hmi):
@@ -774,7 +782,7 @@ def test_tenant_ids_up_to_four_million(hmi):
 @pytest.mark.parametrize("block", [synth.BLOCK_ENC_POSTLN, synth.BLOCK_DEC_PRELN])
 def test_one_request_of_4096_tokens(hmi, block):
     """One sequence of 4 096 tokens: 64 key blocks per query block in the attention kernel (32 query blocks of 128),
-    one segment of 16 m-tiles in the GEMMs; bidirectional and causal, every row compared."""
+    one segment in the GEMMs (64 x 64 and 128 x 64 tiles); bidirectional and causal, every row compared."""
     run_case(hmi, small(block, "bf16", d_model=256, d_ff=512, n_heads=4, n_tenants=1, hbm_slots=1, n_requests=1,
                         seq_min=4096, seq_max=4096))
 
