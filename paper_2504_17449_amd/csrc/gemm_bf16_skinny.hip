@@ -1,15 +1,16 @@
 // Grouped bf16 GEMM for batches with few rows per weight matrix: decode steps (one new token per
-// request, so a tenant's segment is a handful of rows) and any launch whose 256 x 256 tiles would
-// leave most of the chip idle.  Such a launch is bound by streaming the weights once, so the work
-// is cut into many small independent items that keep every compute unit's memory pipe full:
+// request, so a tenant's segment is a handful of rows).  Such a launch is bound by streaming the
+// weights once, so the work is cut into many small independent items that keep every compute unit's
+// memory pipe full:
 //
-//   item = (32 rows of one segment) x (32 output columns) x (all of k), one WAVEFRONT per item,
-//   five items per workgroup (three in small launches, see Ring), no workgroup barriers.
+//   item = (the up to 128 rows of an m-tile, 32 at a time) x (32 output columns) x (all of k), one WAVEFRONT
+//   per item, five items per workgroup (three in small launches, see Ring), no workgroup barriers.
 //
-// A launch with so few items that they would not even give every compute unit one workgroup (a decode
-// step through parameters that all tenants share: a few hundred rows in all) is bound by the latency of
-// one wavefront's walk over k instead; there an item goes to a workgroup of four wavefronts that take
-// a quarter of k each and add their partial sums through LDS in a fixed order.
+// A launch with so few items that they would not even give every compute unit one workgroup (a step of a
+// handful of tenants; the second FFN GEMM of a few hundred rows through weights that all tenants share) is
+// bound by the latency of one wavefront's walk over k instead; there an item is one 32-row block, a
+// workgroup of four wavefronts that take a quarter of k each and add their partial sums through LDS in a
+// fixed order.
 //
 // A wavefront streams its 32 weight rows and its 32 activation rows (gathered through row_src) through a
 // private LDS ring of four to six stages of 64 k (direct-to-LDS copies of full 128-byte lines, all but one stage in
@@ -22,7 +23,6 @@
 #include "hmi_kernels.h"
 
 #include "gelu.h"
-
 
 namespace hmi {
 namespace {
@@ -38,11 +38,12 @@ constexpr int SK = 32;                    // rows and columns of an item
 constexpr int STAGE_BYTES = SK * 128;                      // per operand: 32 rows of 64 k
 constexpr int KSPLIT = 4;                                  // wavefronts that share the k of one item in the split variant
 // Ring depth and wavefronts per workgroup (always 160 KB of LDS, or all the split variant can use):
-//   4 stages x 5 wavefronts: launches with many items (per-tenant decode steps), bound by streaming the weights;
-//   6 stages x 3 wavefronts (the split variant keeps 4 stages: 5 were 3 % slower): launches with at most kDeepMaxItems items (shared layers,
-//   a few hundred rows): there a launch lasts as long as one wavefront's walk over k, a chain of
-//   k / 64 / (stages in flight) round trips to L2 or beyond, so more stages in flight shorten it (a decode step
-//   through six shared layers: 0.699 -> 0.670 ms; 8 or 9 stages x 2 wavefronts: 0.72-0.74, 5 x 4: 0.679).
+//   4 stages x 5 wavefronts: launches with many items, bound by streaming the weights;
+//   6 stages x 3 wavefronts: launches with at most kDeepMaxItems items (a step of up to ten tenants or so).  Such a launch lasts
+//   as long as one wavefront's walk over k, a chain of k / 64 / (stages in flight) round trips to HBM, so more stages in flight
+//   shorten it: 16 decode steps of 3 and 5 tenants through a layer of d = 1024 each 1.29 -> 1.20 and 1.59 -> 1.47 ms with the
+//   prompts, FFN blocks (d = 768) of 3 and 6 tenants 39 -> 36 and 48 -> 45 us; of 10 tenants (some 900 items) 58 -> 61.
+//   The split variant keeps 4 stages: 5 were 3 % slower.
 constexpr int kAuxNonTemporal = 2;   // cache-policy operand of the direct-to-LDS copy: the nt bit
 
 template <bool SPLIT, bool DEEP>
@@ -56,8 +57,6 @@ struct Ring {
   static_assert(LDS_BYTES <= 163840 && 8 * (INFL - 1) < 64, "ring");
 };
 constexpr int kDeepMaxItems = 1024;
-constexpr int kSplitMaxItems = 256;                        // one round of workgroups: 192 items 25 -> 9 us per launch; 288 items are a second
-                                                           // round (13.6 us, 64 x 64 tiles 12.1)
 
 #define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
@@ -76,19 +75,17 @@ __device__ __forceinline__ int swz_a(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int swz_w(int row) { return ((row >> 1) & 3) | (((row >> 4) & 1) << 2); }
 __device__ __forceinline__ int perm_w(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
 
-// row_split: an item is one 32-row block of a 128-row tile (launches with full tiles but few of them);
-// otherwise an item is a whole tile and its wavefront takes the tile's row blocks one after the other
-// (decode steps: nearly every tile holds a single, short row block).
-//
-// SPLIT: the workgroup is KSPLIT wavefronts that share one item (one row block: row_split); wavefront w
-// multiplies the w-th quarter of k.  Everything that decides whether a wavefront leaves early is the same
-// for the whole workgroup, so all of them reach the barrier in front of the sum.
-// WNT: the weights are per-tenant matrices that this launch reads once and the next one does not find in any cache
-// (a decode step streams every present tenant's layer: gigabytes): their copies carry the non-temporal hint, which
-// moves them 5 % faster (config 4's decode step 0.806 -> 0.764 ms).  Shared weights are read by every row block and again
-// in the next step; with the hint that launch is 12 % slower, so the route for shared parameters keeps plain copies.
-template <bool SPLIT, bool DEEP, bool WNT>
-__global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_skinny_kernel(GemmArgs g, Route rt, int n_items, int row_split) {
+// An item is a whole tile and its wavefront takes the tile's row blocks one after the other (decode steps: nearly every tile
+// holds a single, short row block); with SPLIT it is one of the tile's four row blocks, and the workgroup is KSPLIT wavefronts
+// that share it: wavefront w multiplies the w-th quarter of k.  Everything that decides whether a wavefront leaves early is the
+// same for the whole workgroup, so all of them reach the barrier in front of the sum.
+// SHARED: the route of the parameters that all tenants share (SPLIT only).  Per-tenant matrices are read once by this launch and
+// not found in any cache by the next one (a decode step streams every present tenant's layer: gigabytes): their copies carry the
+// non-temporal hint, which moves them 5 % faster (a decode step of 256 requests over 2 000 tenants' layers 0.806 -> 0.764 ms).  Shared weights are
+// read by every row block and again in the next step: plain copies (with the hint 12 % slower).
+template <bool SPLIT, bool DEEP, bool SHARED>
+__global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_skinny_kernel(GemmArgs g, Route rt, int n_items) {
+  static_assert(SPLIT || !SHARED, "whole tiles are per-tenant");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   using R = Ring<SPLIT, DEEP>;
   constexpr int STAGES = R::STAGES, WAVES = R::WAVES, X_RING = R::X_RING, WAVE_LDS = R::WAVE_LDS, INFL = R::INFL;
@@ -98,14 +95,13 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
   if (item >= n_items) return;
   // item = (tile * NB + column block) [* 4 + row block of the 128-row tile]
   const int NB = g.n_out / SK;
-  const int q = row_split ? item >> 2 : item;
+  const int q = SPLIT ? item >> 2 : item;
   const int nb = q % NB, t = q / NB;
-  const int sub_begin = row_split ? (item & 3) : 0, sub_end = row_split ? sub_begin + 1 : 4;
+  const int sub_begin = SPLIT ? (item & 3) : 0, sub_end = SPLIT ? sub_begin + 1 : 4;
   // the route of the shared parameters needs no lookups: tiles in row order, identity row map, slot 0
-  const bool ident = rt.identity != 0;
   int seg_end, tile_row0;
   size_t slot_base = 0;
-  if (ident) {
+  if (SHARED) {
     tile_row0 = t * rt.tile_m[g.which_tiles];
     seg_end = min(g.n_rows, (tile_row0 / kDenseSegRows + 1) * kDenseSegRows);
   } else {
@@ -136,10 +132,10 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
     const int row = 8 * i + (lane >> 3);
     w_off[i] = (uint32_t)row * (uint32_t)kb + (((lane & 7) ^ swz_w(row)) << 4);
     const int xr = row0 + min(row, rows - 1);
-    x_off[i] = (uint32_t)(ident ? xr : rt.row_src[xr]) * (uint32_t)(g.lda * 2) + (((lane & 7) ^ swz_a(row)) << 4);
+    x_off[i] = (uint32_t)(SHARED ? xr : rt.row_src[xr]) * (uint32_t)(g.lda * 2) + (((lane & 7) ^ swz_a(row)) << 4);
   }
   unsigned char* ring = smem + wave * WAVE_LDS;
-  const int my_row = ident ? row0 + min(l32, rows - 1) : rt.row_src[row0 + min(l32, rows - 1)];
+  const int my_row = SHARED ? row0 + min(l32, rows - 1) : rt.row_src[row0 + min(l32, rows - 1)];
   const int rw = perm_w(l32);
   const int fw_base = rw * 128 + ((lh ^ swz_w(rw)) << 4);
   const int fx_base = X_RING + l32 * 128 + ((lh ^ swz_a(l32)) << 4);
@@ -152,7 +148,7 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
     const char* xs_ = Ap + st_ * 128;                                                              \
     unsigned char* dst_ = ring + ((S) % STAGES) * STAGE_BYTES;                                     \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                  \
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(ws_ + w_off[i]), (lds_ptr_t)(dst_ + i * 1024), 16, 0, WNT ? kAuxNonTemporal : 0); \
+      __builtin_amdgcn_global_load_lds((glb_ptr_t)(ws_ + w_off[i]), (lds_ptr_t)(dst_ + i * 1024), 16, 0, SHARED ? 0 : kAuxNonTemporal); \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                  \
       __builtin_amdgcn_global_load_lds((glb_ptr_t)(xs_ + x_off[i]), (lds_ptr_t)(dst_ + X_RING + i * 1024), 16, 0, 0); \
   }
@@ -251,44 +247,39 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
 
 }  // namespace
 
-template <bool SPLIT, bool DEEP>
+template <bool SPLIT, bool DEEP, bool SHARED>
 static void allow_ring() {
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_skinny_kernel<SPLIT, DEEP, false>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, Ring<SPLIT, DEEP>::LDS_BYTES);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_skinny_kernel<SPLIT, DEEP, true>),
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_skinny_kernel<SPLIT, DEEP, SHARED>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, Ring<SPLIT, DEEP>::LDS_BYTES);
 }
 
 void init_gemm_bf16_skinny_kernels() {
-  allow_ring<false, false>(); allow_ring<false, true>(); allow_ring<true, true>();
+  allow_ring<false, false, false>(); allow_ring<false, true, false>(); allow_ring<true, true, false>(); allow_ring<true, true, true>();
 }
 
-template <bool SPLIT, bool DEEP>
-static void launch_ring(const GemmArgs& g, const Route& rt, hipStream_t s, long long n_items, int row_split) {
+template <bool SPLIT, bool DEEP, bool SHARED>
+static void launch_ring(const GemmArgs& g, const Route& rt, hipStream_t s, long long n_items) {
   using R = Ring<SPLIT, DEEP>;
   const unsigned blocks = SPLIT ? (unsigned)n_items : (unsigned)((n_items + R::WAVES - 1) / R::WAVES);
-  if (rt.identity)
-    hipLaunchKernelGGL((gemm_bf16_skinny_kernel<SPLIT, DEEP, false>), dim3(blocks), dim3(64 * R::WAVES), R::LDS_BYTES, s,
-                       g, rt, (int)n_items, row_split);
-  else
-    hipLaunchKernelGGL((gemm_bf16_skinny_kernel<SPLIT, DEEP, true>), dim3(blocks), dim3(64 * R::WAVES), R::LDS_BYTES, s,
-                       g, rt, (int)n_items, row_split);
+  hipLaunchKernelGGL((gemm_bf16_skinny_kernel<SPLIT, DEEP, SHARED>), dim3(blocks), dim3(64 * R::WAVES), R::LDS_BYTES, s,
+                     g, rt, (int)n_items);
 }
 
-// Preconditions (checked by the caller): k % 64 == 0, n_out % 32 == 0, which_tiles names the list of
-// 128-row m-tiles and n_mtiles its length, all operands 16-byte aligned (lda, ldc, ldr multiples of 8).
+// Preconditions (checked by the caller): k % 64 == 0, n_out % 32 == 0, which_tiles names the list of 128-row m-tiles and
+// n_mtiles its length, all operands 16-byte aligned (lda, ldc, ldr multiples of 8).  Launches with more than 32 rows per
+// m-tile, and those of shared weights, fit the split form: at most kSplitMaxItems row blocks times column blocks, k % 256 == 0.
 void launch_gemm_bf16_skinny(const GemmArgs& g, const Route& rt, hipStream_t s) {
-  const int row_split = g.n_rows > 32LL * g.n_mtiles ? 1 : 0;
   const long long n_panels = (long long)g.n_mtiles * (g.n_out / SK);
-  const long long n_items = n_panels * (row_split ? 4 : 1);
-  if (n_items <= 0) return;
-  // few items, long k: one workgroup per item with k shared by its wavefronts (an item is always one row block there: of a
-  // tile's four workgroups those without rows leave at once, and are not counted where most tiles are one short row block)
-  const long long n_busy = row_split ? (g.n_rows + SK - 1) / SK * (g.n_out / SK) : n_panels;
-  if (n_busy <= kSplitMaxItems && g.k % (64 * KSPLIT) == 0 && g.k >= 64 * KSPLIT * 2)
-    return launch_ring<true, true>(g, rt, s, n_panels * 4, 1);
-  if (n_items <= kDeepMaxItems) return launch_ring<false, true>(g, rt, s, n_items, row_split);
-  launch_ring<false, false>(g, rt, s, n_items, row_split);
+  if (n_panels <= 0) return;
+  // few items, long k: one workgroup per item with k shared by its wavefronts (of a tile's four workgroups those without rows
+  // leave at once, and are not counted where most tiles are one short row block)
+  const long long n_busy = g.n_rows > 32LL * g.n_mtiles ? (g.n_rows + SK - 1) / SK * (g.n_out / SK) : n_panels;
+  if (n_busy <= kSplitMaxItems && g.k % (64 * KSPLIT) == 0 && g.k >= 64 * KSPLIT * 2) {
+    if (rt.identity) return launch_ring<true, true, true>(g, rt, s, n_panels * 4);
+    return launch_ring<true, true, false>(g, rt, s, n_panels * 4);
+  }
+  if (n_panels <= kDeepMaxItems) return launch_ring<false, true, false>(g, rt, s, n_panels);
+  launch_ring<false, false, false>(g, rt, s, n_panels);
 }
 
 }  // namespace hmi

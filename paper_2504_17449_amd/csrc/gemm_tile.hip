@@ -34,6 +34,8 @@
 
 #include "gelu.h"
 
+#include <algorithm>
+
 namespace hmi {
 namespace {
 
@@ -390,7 +392,7 @@ GemmKernel pick_gemm_bf16(const GemmArgs& g, const Route& rt) {
   if (g.n_out % 32 == 0) {
     const bool few_rows = g.n_rows <= 32LL * g.n_mtiles_list[1];
     const long long items = (few_rows ? g.n_mtiles_list[1] : (g.n_rows + 31) / 32) * (long long)(g.n_out / 32);
-    if ((few_rows && !rt.identity) || (items <= n_cu && g.k >= 1536 && g.k % 256 == 0)) return GEMM_STREAM;
+    if ((few_rows && !rt.identity) || (items <= std::min(n_cu, kSplitMaxItems) && g.k >= 1536 && g.k % 256 == 0)) return GEMM_STREAM;
   }
   const long long big_tiles = g.n_out % 256 == 0 && g.k >= 192 ? (long long)g.n_mtiles_list[0] * (g.n_out / 256) : 0;
   if (2 * big_tiles > 3LL * n_cu) return GEMM_PERSISTENT;

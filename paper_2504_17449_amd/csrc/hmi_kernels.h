@@ -91,6 +91,9 @@ struct GemmArgs {
 // The kernels a bf16 launch can get, and the rule that picks one (gemm_tile.hip).
 enum GemmKernel : int { GEMM_STREAM = 0, GEMM_64x64, GEMM_128x64, GEMM_128x128, GEMM_128x256, GEMM_PERSISTENT };
 GemmKernel pick_gemm_bf16(const GemmArgs& g, const Route& rt);
+// Items (32 rows x 32 columns) of a GEMM_STREAM launch up to which four wavefronts share one's k: a round of workgroups.  192
+// items 25 -> 9 us per launch; 288 are a second round (13.6 us, 64 x 64 tiles 12.1).
+constexpr int kSplitMaxItems = 256;
 void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s);
 void launch_gemm_f32(const GemmArgs& g, const Route& rt, hipStream_t s);
 // Persistent 256 x 256 tiles, 64-wide k-stages; needs n_out % 256 == 0, k % 64 == 0, k >= 192 and

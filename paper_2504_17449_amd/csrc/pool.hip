@@ -1075,8 +1075,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
       g.w_off = lay + p->tl[tw].off; g.b_off = lay + p->tl[tb].off;
       g.n_out = n_out; g.k = k; g.n_rows = (int)N; g.epi = epi;
       g.n_mtiles_list[0] = n_mtiles[0]; g.n_mtiles_list[1] = n_mtiles[1];
-      g.which_tiles = 0; g.n_mtiles = n_mtiles[0];
-          ProfSpan ps(p, HMI_KERNEL_GEMM);
+      ProfSpan ps(p, HMI_KERNEL_GEMM);
       if (p->bf16) launch_gemm_bf16(g, rt, s); else launch_gemm_f32(g, rt, s);
     };
     auto lnorm = [&](const void* in, bool in_f32, float* out_f32, void* out_st, int tg, int tb) {
@@ -1100,8 +1099,7 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
       g.n_out = n_out; g.k = k; g.n_rows = (int)N; g.epi = epi;
       g.n_mtiles_list[0] = (int)((N + p->tile_m[0] - 1) / p->tile_m[0]);
       g.n_mtiles_list[1] = p->tile_m[1] ? (int)((N + p->tile_m[1] - 1) / p->tile_m[1]) : 0;
-      g.which_tiles = 0; g.n_mtiles = g.n_mtiles_list[0];
-          ProfSpan ps(p, HMI_KERNEL_GEMM);
+      ProfSpan ps(p, HMI_KERNEL_GEMM);
       if (p->bf16) launch_gemm_bf16(g, p->rt_dense, s); else launch_gemm_f32(g, p->rt_dense, s);
     };
     auto slnorm = [&](const void* in, bool in_f32, const void* in2, float* out_f32, void* out_st, int tg, int tb,
