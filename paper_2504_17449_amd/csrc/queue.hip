@@ -39,38 +39,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const void* const* src
   for (size_t i = threadIdx.x; i < pieces; i += 256) to[i] = from[i];
 }
 
-// One request's rows, from the batch's result to the caller's buffer.  A request is 0.02 to 1 MB and a batch has hundreds of
-// them, one after the other on the compute stream: what counts is how soon a copy starts and ends, hence two pieces a
-// thread and as many workgroups as that makes.  hipMemcpyAsync's own copy of 200 KB takes 4.7 us of the stream, this one 2.5.
-constexpr int kCopyPieces = 512;            // 16-byte pieces per workgroup
-
-__global__ __launch_bounds__(256) void copy_rows_kernel(const uint4* from, uint4* to, size_t pieces) {
-  const size_t i = (size_t)blockIdx.x * kCopyPieces + threadIdx.x, j = i + 256;
-  if (j < pieces) {
-    const uint4 v = from[i], w = from[j];
-    to[i] = v;
-    to[j] = w;
-  } else if (i < pieces) {
-    to[i] = from[i];
-  }
-}
-
-// Whether the kernel may write [p, p + bytes): device memory of this GPU, aligned to its pieces, inside one allocation.
-// Everything else (host memory, another GPU's, odd addresses, a buffer that is too small) stays hipMemcpyAsync's matter,
-// with the results and the errors that it gives.
-bool copy_kernel_fits(void* p, size_t bytes, int device) {
-  if (reinterpret_cast<uintptr_t>(p) % 16) return false;
-  hipPointerAttribute_t attr;
-  hipDeviceptr_t base = nullptr;
-  size_t size = 0;
-  if (hipPointerGetAttributes(&attr, p) != hipSuccess || hipMemGetAddressRange(&base, &size, p) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  const size_t before = static_cast<size_t>(static_cast<char*>(p) - static_cast<char*>(base));
-  return attr.type == hipMemoryTypeDevice && attr.device == device && before <= size && bytes <= size - before;
-}
-
 }  // namespace
 
 struct hmi_queue {
@@ -248,20 +216,9 @@ int32_t hmi_queue_fetch(hmi_queue_t* q, int64_t ticket, void* y_rows) {
   Batch* b = find(q, seq);
   if (!b || b->state != RAN || r >= b->n_req)
     return qfail(q, HMI_ERR_ARG, "batch %lld has not run yet or its results are no longer held", (long long)seq);
-  if (hipSetDevice(q->cfg.device) != hipSuccess) return qfail(q, HMI_ERR_DEVICE, "hipSetDevice failed");
-  const char* from = b->y + (size_t)b->tok_off[r] * q->row_bytes;
-  const size_t bytes = (size_t)b->lens[r] * q->row_bytes;
-  hipStream_t s = hmi_internal_compute_stream(q->pool);
-  hipError_t rc;
-  if (q->row_bytes % 16 == 0 && copy_kernel_fits(y_rows, bytes, q->cfg.device)) {
-    const size_t pieces = bytes / 16;
-    hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)((pieces + kCopyPieces - 1) / kCopyPieces)), dim3(256), 0, s,
-                       reinterpret_cast<const uint4*>(from), static_cast<uint4*>(y_rows), pieces);
-    rc = hipGetLastError();
-  } else {
-    rc = hipMemcpyAsync(y_rows, from, bytes, hipMemcpyDeviceToDevice, s);
-  }
-  if (rc != hipSuccess)
+  if (hipSetDevice(q->cfg.device) != hipSuccess ||
+      hipMemcpyAsync(y_rows, b->y + (size_t)b->tok_off[r] * q->row_bytes, (size_t)b->lens[r] * q->row_bytes,
+                     hipMemcpyDeviceToDevice, hmi_internal_compute_stream(q->pool)) != hipSuccess)
     return qfail(q, HMI_ERR_DEVICE, "copy of the result rows failed");
   return HMI_OK;
 }

@@ -195,8 +195,8 @@ def test_queue_output_is_the_stack_call_on_the_gathered_batch_bit_for_bit(hmi):
 
 @pytest.mark.parametrize("d", [256, 768])
 def test_fetch_copies_whole_rows_to_any_device_address(hmi, d):
-    """Row counts around the copy kernel's workgroup (512 pieces of 16 bytes), buffers that start on and off a 16-byte
-    boundary: the same bytes everywhere, and nothing behind or in front of them."""
+    """Requests of one row and of some, buffers that start on and off a 16-byte boundary: the same bytes everywhere, and nothing
+    behind or in front of them."""
     from paper_2504_17449_amd import harness
     rows = [1, 2, 5, 6, 15, 16, 17, 31, 32, 33, 64, 131]
     wl = synth.Workload(name="queue_fetch", block=synth.BLOCK_FFN, dtype="bf16", d_model=d, d_ff=256, n_heads=0, n_layers=1,
