@@ -81,8 +81,8 @@ __device__ __forceinline__ int perm_w(int i) { return ((i >> 2) & 1) * 16 + (i >
 // same for the whole workgroup, so all of them reach the barrier in front of the sum.
 // SHARED: the route of the parameters that all tenants share (SPLIT only).  Per-tenant matrices are read once by this launch and
 // not found in any cache by the next one (a decode step streams every present tenant's layer: gigabytes): their copies carry the
-// non-temporal hint, which moves them 5 % faster (a decode step of 256 requests over 2 000 tenants' layers 0.806 -> 0.764 ms).  Shared weights are
-// read by every row block and again in the next step: plain copies (with the hint 12 % slower).
+// non-temporal hint, which moves them 5 % faster (a decode step of 256 requests over 2 000 tenants' layers 0.806 -> 0.764 ms).
+// Shared weights are read by every row block and again in the next step: plain copies (with the hint 12 % slower).
 template <bool SPLIT, bool DEEP, bool SHARED>
 __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_skinny_kernel(GemmArgs g, Route rt, int n_items) {
   static_assert(SPLIT || !SHARED, "whole tiles are per-tenant");
