@@ -26,11 +26,19 @@
 //          unit's own rows from LDS and writes the rounded sum back in place.
 //
 // Inside a shared layer the block is followed by the layer's LayerNorm over (residual stream + Y): a workgroup has whole
-// rows of Y in LDS, so it does that too (LN_* below), a wavefront four rows of the unit, in the arrangement of the vector
-// LayerNorm kernel and with its arithmetic.  Y itself is then never written.  The first half of a unit's residual
-// rows is asked for a unit ahead, before the copies of the unit after it, so that the wait for those covers it too.
-// Measured: 65 536 rows of d = 768 with an fp32 residual 55 + 75 us as two kernels, 123 as one.
+// rows of Y in LDS, so it does that too (LN_* below), with the arithmetic of the vector LayerNorm kernel, to the bit: a wavefront
+// takes rows w, w + 8, .. of the unit, as far as there are any.  Y itself is then never written.  Half of a unit's residual
+// rows are asked for a unit ahead, the others behind the down-projection.
+// Measured: 65 536 rows of d = 768 with an fp32 residual 55 + 75 us as two kernels, 120 as one.
+//
+// In small launches (a unit a workgroup, ONE below) it is a chain of latencies on top of the 0.2 MB of matrices, which take a
+// compute unit 1.4 us.  The chain is kept short: each wavefront finds its unit by itself, from the segments' ends; everything
+// is asked for before anything is waited for; sums over a wavefront stay in registers.  141 rows of two tenants with LayerNorm
+// 13.4 -> 8.3 us, a decode step's 7 rows 13.3 -> 9.6 and 256 rows of 137 tenants 15.8 -> 12.7 (their 27 MB come from HBM),
+// 2 664 rows 15.5 -> 13.1.
 #include "hmi_kernels.h"
+
+#include "wave_sum.h"
 
 namespace hmi {
 namespace {
@@ -44,15 +52,25 @@ typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
-constexpr int RT = 32;            // rows of a unit
+constexpr int RT = 32;            // rows of a unit at most
 constexpr int RANK = 64;          // bottleneck width
 constexpr int NTH = 512;
 constexpr int MAX_UNITS = 64;     // units one workgroup may be handed
+constexpr int MAX_SEGS = 256;     // tenants of a launch whose units are counted exactly (four per lane)
 constexpr int PART_BYTES = 4 * RT * RANK * 4;   // four partial sums of the 32 x 64 bottleneck, fp32
 constexpr int MID_BYTES = RT * RANK * 2;
 constexpr int RS_BYTES = MAX_UNITS * RT * 4;
 constexpr int DESC_BYTES = (MAX_UNITS * 4 + 4) * 4;
 
+// What the wavefronts pass on through LDS before a barrier; direct-to-LDS copies are waited for where their rows are due
+// (__syncthreads would wait for all of them, and for the stores, at the first barrier behind them).
+#define HMI_BARRIER()                                                                              \
+  {                                                                                                \
+    asm volatile("" ::: "memory");                                                                 \
+    __builtin_amdgcn_s_waitcnt(0xC07F);                                                            \
+    __builtin_amdgcn_s_barrier();                                                                  \
+    asm volatile("" ::: "memory");                                                                 \
+  }
 #define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
 __device__ __forceinline__ float bf2f(uint32_t u16) { return __uint_as_float(u16 << 16); }
@@ -69,6 +87,17 @@ template <bool ONCE>
 __device__ __forceinline__ bf16x8 load_w(const bf16x8* p) {
   if (ONCE) return __builtin_nontemporal_load(p);
   return *p;
+}
+
+// Inclusive prefix sum over the 64 lanes (rows of 16 by row shifts, then across rows by row broadcasts).
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
 }
 
 // What happens to the finished rows of a unit.
@@ -93,7 +122,9 @@ struct Shape {
   static constexpr int OFF_RS = OFF_MID + MID_BYTES;
   static constexpr int OFF_DESC = OFF_RS + RS_BYTES;
   static constexpr int OFF_NORM = OFF_DESC + DESC_BYTES;   // LayerNorm gain, then shift, as stored
-  static constexpr int LDS = OFF_NORM + 2 * ROWB;
+  static constexpr int OFF_BIAS = OFF_NORM + 2 * ROWB;     // the tenant's up-projection bias
+  static constexpr int LDS = OFF_BIAS + ROWB;
+  static_assert(LDS <= 163840, "LDS");
 };
 
 // LDS layouts (all XOR swizzles act on 16-byte chunk indices, so that the 16 lanes that
@@ -103,7 +134,10 @@ struct Shape {
 //   bottleneck   row r is 128 bytes (64 bf16), chunk c at position c ^ ((r >> 1) & 7)
 // ONCE: the tenants' matrices are loaded with the non-temporal hint (load_w above); OUT_STREAM: so are the result's stores.
 // Both are compile-time: a run-time choice between a hinted and a plain access to one address is merged into the plain one.
-template <int NV, bool ONCE, int OUT>
+// ONE: a workgroup is one unit (a launch of at most as many units as compute units).  It is straight code then, in
+// which the compiler waits for each load where it is needed; in the loop of the general form, where waits hold for all turns, the
+// matrices have to be there before the first one.
+template <int NV, bool ONCE, int OUT, bool ONE>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   using S = Shape<NV>;
@@ -117,34 +151,56 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   int* desc = reinterpret_cast<int*>(smem + S::OFF_DESC);
   int* rs = reinterpret_cast<int*>(smem + S::OFF_RS);
 
-  // ---- which units are mine, which of them hold rows, and where those rows live
-  const int U = a.n_tiles128 * 4;
-  const int u_begin = (int)((long long)blockIdx.x * U / gridDim.x);
-  const int u_end = (int)((long long)(blockIdx.x + 1) * U / gridDim.x);
-  if (wave == 0) {
-    const int u = u_begin + lane;
+  // ---- which units are mine and where their rows live.  Every wavefront finds out by itself (a barrier less in a chain of
+  //      them); the first one writes it down.
+  int m = 1, first_row, first_rows, cur_slot;
+  if (ONE) {
+    // unit blockIdx.x of the segments' units in order: a lane counts those of four segments
+    int cut[5], units = 0;
+#pragma unroll
+    for (int e = 0; e < 5; ++e) cut[e] = rt.seg_tok_off[min(4 * lane + e, a.n_segs)];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) units += (cut[e + 1] - cut[e] + a.unit_rows - 1) >> a.unit_shift;
+    const int upto = wave_incl_scan(units), b = blockIdx.x;
+    const int l0 = __builtin_ctzll(__ballot(upto > b));       // (the launch has exactly as many workgroups as there are units)
+    int u = b - (upto - units), seg = 4 * lane, row0 = 0, rows = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int n = (cut[e + 1] - cut[e] + a.unit_rows - 1) >> a.unit_shift;
+      if (u >= 0 && u < n) { seg = 4 * lane + e; row0 = cut[e] + (u << a.unit_shift); rows = min(a.unit_rows, cut[e + 1] - row0); }
+      u -= n;
+    }
+    first_row = __builtin_amdgcn_readlane(row0, l0);
+    first_rows = __builtin_amdgcn_readlane(rows, l0);
+    cur_slot = rt.seg_slot[__builtin_amdgcn_readlane(seg, l0)];
+  } else {
+    const int* const tile_seg = rt.tile_seg[a.which_tiles];
+    const int* const tile_row0 = rt.tile_row0[a.which_tiles];
+    const int u_begin = blockIdx.x * a.units_each + min((int)blockIdx.x, a.units_more);
+    const int n_units = a.units_each + ((int)blockIdx.x < a.units_more);
     int row0 = 0, rows = 0, slot = 0;
-    if (u < u_end) {
-      const int t = u >> 2;
-      const int seg = rt.tile_seg[a.which_tiles][t];
-      row0 = rt.tile_row0[a.which_tiles][t] + (u & 3) * RT;
+    if (lane < n_units) {
+      const int u = u_begin + lane, t = u >> 2, seg = tile_seg[t];
+      row0 = tile_row0[t] + (u & 3) * RT;
       rows = min(RT, rt.seg_tok_off[seg + 1] - row0);
       slot = rt.seg_slot[seg];
     }
     const unsigned long long mask = __ballot(rows > 0);
-    if (rows > 0) {
+    if (mask == 0) return;
+    m = __popcll(mask);
+    if (wave == 0 && rows > 0) {
       const int pos = __popcll(mask & ((1ull << lane) - 1ull));
       desc[pos * 4 + 0] = row0; desc[pos * 4 + 1] = rows; desc[pos * 4 + 2] = slot;
     }
-    if (lane == 0) desc[MAX_UNITS * 4] = __popcll(mask);
+    const int l0 = __builtin_ctzll(mask);
+    first_row = __builtin_amdgcn_readlane(row0, l0);
+    first_rows = __builtin_amdgcn_readlane(rows, l0);
+    cur_slot = __builtin_amdgcn_readlane(slot, l0);
   }
-  __syncthreads();
-  const int m = desc[MAX_UNITS * 4];
-  if (m == 0) return;
   const int cb = wave & 1, kq = wave >> 1;    // down-projection role
   bf16x8 wd[S::KSW], wu[NV][4];
-  u32x4 bu[NV][2];   // up-projection bias of my columns, packed bf16 pairs
-  f32x4 bd4;
+  u32x4 bu = {};     // up-projection bias of my 32 NV columns, packed: eight of them in each of the first 4 NV lanes
+  u32x2 bd;          // down-projection bias of my four bottleneck columns, packed
 
   // copies unit ui into row buffer b (wavefronts 0-3; a lane moves NJ chunks of 16 bytes)
   const char* X = reinterpret_cast<const char*>(a.X);
@@ -178,59 +234,79 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
       wd[s] = load_w<ONCE>(pwd + ((s >> 1) * 8 + (s & 1)) * 64);   /* k-step 8 (s / 2) + 2 kq + s % 2 */ \
   }
 #define HMI_LOAD_BD(SLOT)                                                                          \
-  {                                                                                                \
-    const u32x2 d2 = *reinterpret_cast<const u32x2*>(a.pool + (size_t)(SLOT) * a.slot_stride + a.bd_off + (tid & 15) * 8); \
-    bd4 = f32x4{bf2f(d2[0] & 0xFFFFu), bf2f(d2[0] >> 16), bf2f(d2[1] & 0xFFFFu), bf2f(d2[1] >> 16)}; \
-  }
+  bd = *reinterpret_cast<const u32x2*>(a.pool + (size_t)(SLOT) * a.slot_stride + a.bd_off + (tid & 15) * 8);
 #define HMI_LOAD_WU(SLOT)                                                                          \
   {                                                                                                \
     const char* base = a.pool + (size_t)(SLOT) * a.slot_stride;                                    \
     const bf16x8* pwu = reinterpret_cast<const bf16x8*>(base + a.wu_off) + (wave * NV * 4 * 64 + lane); \
     _Pragma("unroll") for (int c = 0; c < NV; ++c)                                                 \
       _Pragma("unroll") for (int s = 0; s < 4; ++s) wu[c][s] = load_w<ONCE>(pwu + (c * 4 + s) * 64); \
-    _Pragma("unroll") for (int c = 0; c < NV; ++c) {                                               \
-      const u32x4* pb = reinterpret_cast<const u32x4*>(base + a.bu_off + ((wave * NV + c) * 32 + h * 16) * 2); \
-      bu[c][0] = pb[0]; bu[c][1] = pb[1];                                                          \
-    }                                                                                              \
+    if (lane < 4 * NV) bu = *reinterpret_cast<const u32x4*>(base + a.bu_off + (wave * 4 * NV + lane) * 16); \
   }
 
-  // Asked for in the order in which they are needed (loads return in order): the first sixteen units' rows, the LayerNorm's
-  // parameters, the matrices.
-  auto row_of = [&](int idx) {                        // surplus rows of a short unit repeat its last row
-    const int u = idx >> 5, r = idx & 31;
-    return rt.row_src[desc[u * 4] + min(r, desc[u * 4 + 1] - 1)];
-  };
-  int row0 = 0;
-  if (tid < m * RT) row0 = row_of(tid);
+  // A compute unit takes 66 bytes a clock, and a unit's matrices are most of its bytes (1.4 us of them): they are asked for as
+  // early as may be, in the order in which they are needed (loads return in order): Down, the first unit's rows (through
+  // registers, so that nothing behind them has to be waited for with them), its residual rows, Up.
+  const int my_src = rt.row_src[first_row + min(lane & 31, first_rows - 1)];
+  HMI_LOAD_WD(cur_slot)
+  __builtin_amdgcn_sched_barrier(0);
+  u32x4 x0[2 * NV];
+#pragma unroll
+  for (int jj = 0; jj < 2 * NV; ++jj) {
+    const int c = jj * NTH + tid, row = c / S::CH;
+    const int src = __shfl(my_src, row, 64);
+    if (row < first_rows) x0[jj] = *reinterpret_cast<const u32x4*>(X + (size_t)src * S::ROWB + (c % S::CH) * 16);
+  }
   u32x4 norm = {};
   if (LN && tid < 2 * S::CH) norm = reinterpret_cast<const u32x4*>(tid < S::CH ? a.ln_g : a.ln_b)[tid < S::CH ? tid : tid - S::CH];
   __builtin_amdgcn_sched_barrier(0);
-  int cur_slot = desc[2];
-  HMI_LOAD_WD(cur_slot) HMI_LOAD_WU(cur_slot)
-  __builtin_amdgcn_sched_barrier(0);
-  if (tid < m * RT) rs[tid] = row0;
-  for (int idx = tid + NTH; idx < m * RT; idx += NTH) rs[idx] = row_of(idx);
-  if (LN && tid < 2 * S::CH) reinterpret_cast<u32x4*>(smem + S::OFF_NORM)[tid] = norm;
-  HMI_LOAD_BD(cur_slot)
-  // the residual rows of unit UI that this wavefront normalises: two of rows 4 wave .. 4 wave + 3, columns 256 v + 4 lane ..
-  // (the first two are asked for a unit ahead; all four would not fit the registers beside the tenant's matrices)
+  // The residual rows that this wavefront normalises: rows wave + 8 q of a unit, as far as it has them, columns 256 v + 4 lane
+  // .. (q = 0, 1 are asked for a unit ahead, the others behind the down-projection; all four ahead do not fit the registers)
   four_t res[LN ? 4 : 1][LN ? NV : 1];
-#define HMI_LOAD_RESID(UI, Q0)                                                                     \
+#define HMI_LOAD_RESID_ROW(Q, ROW)                                                                 \
   {                                                                                                \
-    _Pragma("unroll") for (int q = (Q0); q < (Q0) + 2; ++q) {                                                \
-      const size_t row_ = (size_t)__builtin_amdgcn_readfirstlane(rs[(UI) * RT + wave * 4 + q]) * (S::CH * 8); \
-      _Pragma("unroll") for (int v = 0; v < NV; ++v) {                                             \
-        if (OUT == LN_RESID_F32) res[q][v] = *reinterpret_cast<const four_t*>(static_cast<const float*>(a.resid) + row_ + v * 256 + lane * 4); \
-        else res[q][v] = *reinterpret_cast<const four_t*>(static_cast<const uint16_t*>(a.resid) + row_ + v * 256 + lane * 4); \
-      }                                                                                            \
+    const size_t row_ = (size_t)__builtin_amdgcn_readfirstlane(ROW) * (S::CH * 8);                 \
+    _Pragma("unroll") for (int v = 0; v < NV; ++v) {                                               \
+      if (OUT == LN_RESID_F32) res[Q][v] = *reinterpret_cast<const four_t*>(static_cast<const float*>(a.resid) + row_ + v * 256 + lane * 4); \
+      else res[Q][v] = *reinterpret_cast<const four_t*>(static_cast<const uint16_t*>(a.resid) + row_ + v * 256 + lane * 4); \
     }                                                                                              \
   }
-  __syncthreads();   // rs complete
-  if (LN) HMI_LOAD_RESID(0, 0)
+#define HMI_LOAD_RESID(UI, Q0, ROWS)                                                               \
+  _Pragma("unroll") for (int q = (Q0); q < (Q0) + 2; ++q)                                          \
+    if (wave + 8 * q < (ROWS)) HMI_LOAD_RESID_ROW(q, rs[(UI) * RT + wave + 8 * q])
+  if (LN) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (wave + 8 * q < first_rows) HMI_LOAD_RESID_ROW(q, __builtin_amdgcn_readlane(my_src, wave + 8 * q))
+  }
+  HMI_LOAD_BD(cur_slot)
+  HMI_LOAD_WU(cur_slot)
   __builtin_amdgcn_sched_barrier(0);
-  if (wave < 4) {
-    HMI_ISSUE_COPIES(0, 0)
-    if (m > 1) HMI_ISSUE_COPIES(1, 1)
+  // the units' row numbers and the LayerNorm's parameters to LDS, then the first unit's rows
+  if (wave == 0 && lane < RT) rs[lane] = my_src;
+  if (LN && tid < 2 * S::CH) reinterpret_cast<u32x4*>(smem + S::OFF_NORM)[tid] = norm;
+#pragma unroll
+  for (int jj = 0; jj < 2 * NV; ++jj) {
+    const int c = jj * NTH + tid, row = c / S::CH;
+    if (row < first_rows) *reinterpret_cast<u32x4*>(smem + row * S::ROWB + (((c % S::CH) ^ (row & 15)) << 4)) = x0[jj];
+  }
+  HMI_BARRIER();
+  if (!ONE) {
+#pragma unroll
+    for (int s = 0; s < S::KSW; ++s) asm volatile("" :: "v"(wd[s]));       // (waited for here)
+#pragma unroll
+    for (int c = 0; c < NV; ++c)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) asm volatile("" :: "v"(wu[c][s]));
+    asm volatile("" :: "v"(bu), "v"(bd));
+  }
+  if (m > 1) {
+    for (int idx = RT + tid; idx < m * RT; idx += NTH) {   // surplus rows of a short unit repeat its last row
+      const int u = idx >> 5, r = idx & 31;
+      rs[idx] = rt.row_src[desc[u * 4] + min(r, desc[u * 4 + 1] - 1)];
+    }
+    HMI_BARRIER();
+    if (wave < 4) HMI_ISSUE_COPIES(1, 1)
   }
 
   for (int i = 0; i < m; ++i) {
@@ -240,16 +316,11 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
       asm volatile("" : "+v"(tid));
       lane = tid & 63; j = lane & 31; h = lane >> 5;
     }
-    const int rows = desc[i * 4 + 1];
+    const int rows = ONE ? first_rows : desc[i * 4 + 1];
     // the tenant of the next unit, if it is another one: its matrices replace this unit's as
     // soon as each has been used for the last time, so that the reads run under the rest of the unit
     const int next_slot = i + 1 < m ? desc[(i + 1) * 4 + 2] : cur_slot;
     const bool reload = next_slot != cur_slot;   // same for the whole workgroup
-    if (i == 0) {   // the first unit's rows must have landed (later units: see the end of the loop)
-      if (wave < 4) { if (m > 1) { HMI_WAIT_VMCNT(S::NJ); } else { HMI_WAIT_VMCNT(0); } }
-      __syncthreads();
-    }
-
     // ---- Down: partial[kq] = X[32, my quarter of d] * Down[cb block, same quarter]^T
     {
       // my k-steps are 8 a + 2 kq + e (a = 0 .. KS/8 - 1, e = 0, 1): the row chunks 16 a + 4 kq + 2 e + h,
@@ -271,7 +342,8 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
       }
     }
     if (reload) HMI_LOAD_WD(next_slot)
-    __syncthreads();
+    if (LN) { HMI_LOAD_RESID(i, 2, rows) }
+    HMI_BARRIER();
     // ---- bottleneck: sum of the four quarters + bias, ReLU, one rounding to bf16
     {
       const int row = tid >> 4, q = tid & 15;
@@ -279,16 +351,18 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
       f32x4 v = *reinterpret_cast<const f32x4*>(pr);
 #pragma unroll
       for (int k = 1; k < 4; ++k) v += *reinterpret_cast<const f32x4*>(pr + k * (RT * RANK * 4));
-      v += bd4;
+      v += f32x4{bf2f(bd[0] & 0xFFFFu), bf2f(bd[0] >> 16), bf2f(bd[1] & 0xFFFFu), bf2f(bd[1] >> 16)};
       u32x2 o;
       o[0] = pack_bf16(fmaxf(v[0], 0.0f), fmaxf(v[1], 0.0f));
       o[1] = pack_bf16(fmaxf(v[2], 0.0f), fmaxf(v[3], 0.0f));
       *reinterpret_cast<u32x2*>(smem + S::OFF_MID + row * 128 + (((q >> 1) ^ ((row >> 1) & 7)) << 4) + (q & 1) * 8) = o;
     }
     if (reload) HMI_LOAD_BD(next_slot)
-    __syncthreads();
+    HMI_BARRIER();
     // ---- Up: my d/8 output columns, added to the unit's rows in place
     {
+      u32x4* const my_bias = reinterpret_cast<u32x4*>(smem + S::OFF_BIAS) + wave * 4 * NV;   // only this wavefront's
+      if (lane < 4 * NV) my_bias[lane] = bu;
       bf16x8 mf[4];
       const unsigned char* mr = smem + S::OFF_MID + j * 128;
 #pragma unroll
@@ -297,10 +371,11 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
 #pragma unroll
       for (int c = 0; c < NV; ++c) {
         f32x16 acc;
+        const u32x4 b0 = my_bias[c * 4 + h * 2], b1 = my_bias[c * 4 + h * 2 + 1];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          acc[2 * e] = bf2f(bu[c][0][e] & 0xFFFFu); acc[2 * e + 1] = bf2f(bu[c][0][e] >> 16);
-          acc[8 + 2 * e] = bf2f(bu[c][1][e] & 0xFFFFu); acc[8 + 2 * e + 1] = bf2f(bu[c][1][e] >> 16);
+          acc[2 * e] = bf2f(b0[e] & 0xFFFFu); acc[2 * e + 1] = bf2f(b0[e] >> 16);
+          acc[8 + 2 * e] = bf2f(b1[e] & 0xFFFFu); acc[8 + 2 * e + 1] = bf2f(b1[e] >> 16);
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wu[c][s], mf[s], acc, 0, 0, 0);
@@ -319,18 +394,17 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
     }
     if (reload) HMI_LOAD_WU(next_slot)
     cur_slot = next_slot;
-    if (LN && wave < 4 && i + 1 < m) HMI_WAIT_VMCNT(0);   // the next unit's rows, before this unit's stores are in the way
-    if (LN) HMI_LOAD_RESID(i, 2)
-    __syncthreads();
+    HMI_BARRIER();
     if (LN) {
       // ---- LayerNorm of (residual + adapted row), rounded as the separate kernels would pass it on
 #pragma unroll
       for (int q0 = 0; q0 < 4; q0 += 2) {
+        if (q0 && wave + 8 * q0 >= rows) break;
         f32x4 v[2][NV];
         float sum[2], var[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          const int r = wave * 4 + q0 + q;
+          const int r = wave + 8 * (q0 + q);
           sum[q] = 0.0f;
 #pragma unroll
           for (int c = 0; c < NV; ++c) {
@@ -340,9 +414,7 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
           }
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) sum[q] += __shfl_xor(sum[q], o, 64);
+        for (int q = 0; q < 2; ++q) sum[q] = wave_sum(sum[q]);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           sum[q] /= (float)(NV * 256);                                 // the mean
@@ -353,12 +425,12 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
             for (int e = 0; e < 4; ++e) { const float z = v[q][c][e] - sum[q]; var[q] += z * z; }
         }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) var[q] += __shfl_xor(var[q], o, 64);
+        for (int q = 0; q < 2; ++q) var[q] = wave_sum(var[q]);
+        // the next unit's rows and its tenant's matrices, before this unit's stores are in the way
+        if (!ONE && q0 == 0) HMI_WAIT_VMCNT(0);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          const int r = wave * 4 + q0 + q;
+          const int r = wave + 8 * (q0 + q);
           if (r < rows) {
             const float rstd = 1.0f / sqrtf(var[q] / (float)(NV * 256) + a.eps);
             const size_t at = (size_t)__builtin_amdgcn_readfirstlane(rs[i * RT + r]) * (S::CH * 8) + lane * 4;
@@ -376,12 +448,13 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (i + 1 < m) HMI_LOAD_RESID(i + 1, 0)
+      if (i + 1 < m) { HMI_LOAD_RESID(i + 1, 0, desc[(i + 1) * 4 + 1]) }
       __builtin_amdgcn_sched_barrier(0);
     } else
     // ---- wavefronts 4-7 stream the finished rows out; wavefronts 0-3 make sure the next
     //      unit's rows have landed.  After the barrier the buffer is free for unit i + 2.
     if (wave >= 4) {
+      if (!ONE) HMI_WAIT_VMCNT(0);        // (the next tenant's matrices, as above)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         u32x4 v[NV];
@@ -402,7 +475,7 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
     } else if (i + 1 < m) {
       HMI_WAIT_VMCNT(0);
     }
-    __syncthreads();
+    HMI_BARRIER();
     if (wave < 4 && i + 2 < m) HMI_ISSUE_COPIES(i + 2, b)
   }
 #undef HMI_ISSUE_COPIES
@@ -410,38 +483,57 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
 #undef HMI_LOAD_BD
 #undef HMI_LOAD_WU
 #undef HMI_LOAD_RESID
+#undef HMI_LOAD_RESID_ROW
 }
 
-template <int NV>
-decltype(&adapter_bf16_kernel<NV, false, OUT_STREAM>) pick(const AdapterArgs& a) {
-  if (a.resid_f32) return a.weights_once ? adapter_bf16_kernel<NV, true, LN_RESID_F32> : adapter_bf16_kernel<NV, false, LN_RESID_F32>;
-  return a.weights_once ? adapter_bf16_kernel<NV, true, LN_RESID_BF16> : adapter_bf16_kernel<NV, false, LN_RESID_BF16>;
+template <int NV, bool ONE>
+decltype(&adapter_bf16_kernel<NV, false, OUT_STREAM, ONE>) pick(const AdapterArgs& a) {
+  if (a.stream_out) return adapter_bf16_kernel<NV, false, OUT_STREAM, ONE>;
+  if (a.resid_f32) return a.weights_once ? adapter_bf16_kernel<NV, true, LN_RESID_F32, ONE> : adapter_bf16_kernel<NV, false, LN_RESID_F32, ONE>;
+  return a.weights_once ? adapter_bf16_kernel<NV, true, LN_RESID_BF16, ONE> : adapter_bf16_kernel<NV, false, LN_RESID_BF16, ONE>;
 }
 
 template <int NV>
 void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   using S = Shape<NV>;
-  auto kern = a.stream_out ? adapter_bf16_kernel<NV, false, OUT_STREAM> : pick<NV>(a);
   const int n_cu = rt.n_cu >= 1 ? rt.n_cu : 256;
+  if (a.n_tiles128 <= 0) return;
+  AdapterArgs b = a;
+  // While there is a compute unit for each, the units are as small as may be: what one costs is then the traffic of its rows
+  // through one of them, besides its matrices' (two requests of 101 and 40 rows with LayerNorm: 12.4 us in units of 32 rows, up
+  // to 0.49 MB each, 8.3 in units of 8), and they are counted exactly (a decode step of 256 rows, the most popular tenant with 34
+  // of them: 14.5 us with four units for each 128-row tile, most of them empty, 12.7 with these).
+  if (a.n_segs <= MAX_SEGS)
+    for (int k = 0; k < 3; ++k)
+      if (a.units[k] <= n_cu) {
+        b.unit_shift = 3 + k;
+        b.unit_rows = 8 << k;
+        hipLaunchKernelGGL((pick<NV, true>(a)), dim3(a.units[k]), dim3(NTH), S::LDS, s, b, rt);
+        return;
+      }
   const long long U = (long long)a.n_tiles128 * 4;
-  if (U <= 0) return;
   long long grid = U < n_cu ? U : n_cu;                               // one workgroup per compute unit ...
   const long long need = (U + MAX_UNITS - 1) / MAX_UNITS;            // ... unless that hands a workgroup
   if (grid < need) grid = need;                                       //     more units than it can list
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTH), S::LDS, s, a, rt);
+  b.units_each = (int)(U / grid);
+  b.units_more = (int)(U % grid);
+  hipLaunchKernelGGL((pick<NV, false>(a)), dim3((unsigned)grid), dim3(NTH), S::LDS, s, b, rt);
 }
 
-template <int NV>
+template <int NV, bool ONE>
 void allow_lds() {
-  for (auto kern : {adapter_bf16_kernel<NV, false, OUT_STREAM>, adapter_bf16_kernel<NV, false, LN_RESID_BF16>,
-                    adapter_bf16_kernel<NV, true, LN_RESID_BF16>, adapter_bf16_kernel<NV, false, LN_RESID_F32>,
-                    adapter_bf16_kernel<NV, true, LN_RESID_F32>})
+  for (auto kern : {adapter_bf16_kernel<NV, false, OUT_STREAM, ONE>, adapter_bf16_kernel<NV, false, LN_RESID_BF16, ONE>,
+                    adapter_bf16_kernel<NV, true, LN_RESID_BF16, ONE>, adapter_bf16_kernel<NV, false, LN_RESID_F32, ONE>,
+                    adapter_bf16_kernel<NV, true, LN_RESID_F32, ONE>})
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Shape<NV>::LDS);
 }
 
 }  // namespace
 
-void init_adapter_bf16_kernels() { allow_lds<1>(); allow_lds<2>(); allow_lds<3>(); }
+void init_adapter_bf16_kernels() {
+  allow_lds<1, false>(); allow_lds<2, false>(); allow_lds<3, false>();
+  allow_lds<1, true>(); allow_lds<2, true>(); allow_lds<3, true>();
+}
 
 // Operand order: 1 KB blocks, one per (32-row block, 16-wide k-step), k-steps innermost.
 // Lane l of a block holds the 8 elements [16 s + 8 (l / 32), +8) of the block's row

@@ -114,6 +114,9 @@ struct AdapterArgs {
   size_t wd_off, bd_off, wu_off, bu_off;  // byte offsets inside a slot (layer included)
   int d;
   int which_tiles, n_tiles128;        // index and length of the list of 128-row m-tiles
+  int n_segs;                         // tenants of the batch
+  int units[3];                       // units of at most 8, 16 and 32 rows of one tenant that the batch comes to
+  int unit_rows, unit_shift, units_each, units_more;   // set by the launcher: the size of a unit, or how many a workgroup has
   int stream_out;                     // 1: Y is the caller's result, stored with the non-temporal hint.  0: the LayerNorm below
   int weights_once;                   // 1: a tenant's matrices are read by about one unit of rows (a decode step): loaded with the non-temporal hint
   // LayerNorm behind the adapter (stream_out = 0): Y = LN(resid + adapted X) in bf16, x32 = the same in fp32 or, with

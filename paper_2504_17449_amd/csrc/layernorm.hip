@@ -6,17 +6,13 @@
 // An optional second input is added first (residual stream + adapted attention output).
 #include "hmi_kernels.h"
 
+#include "wave_sum.h"
+
 namespace hmi {
 namespace {
 
 __device__ __forceinline__ float bf2f(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 constexpr int kMaxPerLane = 32;  // d <= 2048
 

@@ -951,8 +951,9 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
 
   // ---- residency of the first layer: hits first (so they cannot be chosen as victims)
   const uint64_t now = ++p->clock;
-  int n_mtiles[2] = {0, 0};
+  int n_mtiles[2] = {0, 0}, n_units[3] = {0, 0, 0};
   for (int t : p->distinct) {
+    for (int k = 0; k < 3; ++k) n_units[k] += (p->tok_count[t] + (8 << k) - 1) >> (3 + k);
     n_mtiles[0] += (p->tok_count[t] + p->tile_m[0] - 1) / p->tile_m[0];
     if (p->tile_m[1]) n_mtiles[1] += (p->tok_count[t] + p->tile_m[1] - 1) / p->tile_m[1];
     const int s = p->slot_of_tenant[t];
@@ -1137,7 +1138,8 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
         a.X = p->w_act; a.Y = p->w_act; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
         a.wd_off = lay + p->tl[T_W1].off; a.bd_off = lay + p->tl[T_B1].off;
         a.wu_off = lay + p->tl[T_W2].off; a.bu_off = lay + p->tl[T_B2].off;
-        a.d = d; a.which_tiles = 1; a.n_tiles128 = n_mtiles[1];
+        a.d = d; a.which_tiles = 1; a.n_tiles128 = n_mtiles[1]; a.n_segs = G;
+        std::copy(n_units, n_units + 3, a.units);
         a.weights_once = (long long)N <= 32LL * n_mtiles[1];
         a.resid = in_res; a.resid_f32 = in_res_f32;
         a.ln_g = reinterpret_cast<const uint16_t*>(p->d_shared + slay + p->stl[tg].off);
@@ -1165,7 +1167,8 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
           a.X = x; a.Y = y; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
           a.wd_off = lay + p->tl[T_W1].off; a.bd_off = lay + p->tl[T_B1].off;
           a.wu_off = lay + p->tl[T_W2].off; a.bu_off = lay + p->tl[T_B2].off;
-          a.d = d; a.which_tiles = 1; a.n_tiles128 = n_mtiles[1];
+          a.d = d; a.which_tiles = 1; a.n_tiles128 = n_mtiles[1]; a.n_segs = G;
+          std::copy(n_units, n_units + 3, a.units);
           a.stream_out = 1;
           ProfSpan ps(p, HMI_KERNEL_GEMM);
           launch_adapter_bf16(a, rt, s);
@@ -1315,10 +1318,11 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
   HIP_TRY(p, hipSetDevice(c.device));
   int32_t* const base = g_scratch_ptr[c.device];
   if (!base) return fail(p, HMI_ERR_DEVICE, "the static routing arrays of device %d were never resolved", c.device);
-  int n_tiles128 = 0;
+  int n_tiles128 = 0, n_units[3] = {0, 0, 0};
   uint64_t need_copy = 0;
   for (int t : p->distinct) {
     n_tiles128 += (p->tok_count[t] + kBf16TileM1 - 1) / kBf16TileM1;
+    for (int k = 0; k < 3; ++k) n_units[k] += (p->tok_count[t] + (8 << k) - 1) >> (3 + k);
     need_copy = std::max(need_copy, p->slot_copy[p->slot_of_tenant[t]]);
   }
   hipStream_t s = p->compute;
@@ -1365,7 +1369,8 @@ int32_t hmi_layer_forward_static(hmi_pool_t* p, int32_t layer, const void* x, vo
   a.X = x; a.Y = y; a.pool = p->d_pool; a.slot_stride = p->slot_stride;
   a.wd_off = p->tl[T_W1].off; a.bd_off = p->tl[T_B1].off;
   a.wu_off = p->tl[T_W2].off; a.bu_off = p->tl[T_B2].off;
-  a.d = c.d_model; a.which_tiles = 1; a.n_tiles128 = n_tiles128;
+  a.d = c.d_model; a.which_tiles = 1; a.n_tiles128 = n_tiles128; a.n_segs = (int)p->distinct.size();
+  std::copy(n_units, n_units + 3, a.units);
   a.stream_out = 1;
   launch_adapter_bf16(a, rt, s);
   HIP_TRY(p, hipGetLastError());
