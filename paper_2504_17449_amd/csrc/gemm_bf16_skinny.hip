@@ -31,11 +31,13 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
 constexpr int SK = 32;                    // rows and columns of an item
 constexpr int STAGE_BYTES = SK * 128;                      // per operand: 32 rows of 64 k
+constexpr int kXcds = 8;
 constexpr int KSPLIT = 4;                                  // wavefronts that share the k of one item in the split variant
 // Ring depth and wavefronts per workgroup (always 160 KB of LDS, or all the split variant can use):
 //   4 stages x 5 wavefronts: launches with many items, bound by streaming the weights;
@@ -58,6 +60,14 @@ struct Ring {
 };
 constexpr int kDeepMaxItems = 1024;
 
+// what a wavefront wrote to LDS is there for the others behind it
+#define HMI_BARRIER()                                                                              \
+  {                                                                                                \
+    asm volatile("" ::: "memory");                                                                 \
+    __builtin_amdgcn_s_waitcnt(0xC07F);                                                            \
+    __builtin_amdgcn_s_barrier();                                                                  \
+    asm volatile("" ::: "memory");                                                                 \
+  }
 #define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
 __device__ __forceinline__ float bf2f(uint32_t u) { return __uint_as_float(u << 16); }
@@ -91,13 +101,24 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
   constexpr int STAGES = R::STAGES, WAVES = R::WAVES, X_RING = R::X_RING, WAVE_LDS = R::WAVE_LDS, INFL = R::INFL;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int item = SPLIT ? (int)blockIdx.x : (int)blockIdx.x * WAVES + wave;
-  if (item >= n_items) return;
-  // item = (tile * NB + column block) [* 4 + row block of the 128-row tile]
+  // item = tile * NB + column block [, and one of the 128-row tile's four row blocks]
   const int NB = g.n_out / SK;
-  const int q = SPLIT ? item >> 2 : item;
-  const int nb = q % NB, t = q / NB;
-  const int sub_begin = SPLIT ? (item & 3) : 0, sub_end = SPLIT ? sub_begin + 1 : 4;
+  int nb, t, sub_begin = 0, sub_end = 4;
+  if (SHARED) {
+    // the row blocks of a column block go to one XCD, whose L2 fetches its weights for all of them (workgroups are dealt to
+    // the XCDs round robin; 141 rows x 768 columns x k = 3072 as neighbours, on as many XCDs: 9.4 us, now 8.0, of which 0.6 are the residuals asked for early)
+    const int row_blocks = (g.n_rows + SK - 1) / SK, local = (int)blockIdx.x / kXcds, c = local / row_blocks, rb = local - c * row_blocks;
+    nb = c * kXcds + (int)blockIdx.x % kXcds;
+    if (nb >= NB) return;
+    t = rb >> 2;
+    sub_begin = rb & 3; sub_end = sub_begin + 1;
+  } else {
+    const int item = SPLIT ? (int)blockIdx.x : (int)blockIdx.x * WAVES + wave;
+    if (item >= n_items) return;
+    const int q = SPLIT ? item >> 2 : item;
+    nb = q % NB; t = q / NB;
+    if (SPLIT) { sub_begin = item & 3; sub_end = sub_begin + 1; }
+  }
   // the route of the shared parameters needs no lookups: tiles in row order, identity row map, slot 0
   int seg_end, tile_row0;
   size_t slot_base = 0;
@@ -123,6 +144,7 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
   const int KT = SPLIT ? g.k / 64 / KSPLIT : g.k / 64;
   const int k_first = SPLIT ? wave * KT : 0;
 
+  const int nx = (rows + 7) >> 3;                       // split form: copies of activation rows that there are
   // copies: instruction i moves rows 8 i .. 8 i + 7 of a stage; lane l fills position (row 8 i + l / 8,
   // chunk l % 8) with the row's chunk (l % 8) ^ swizzle(row).  Rows past the end of a short row block
   // repeat its last row.
@@ -150,7 +172,20 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                  \
       __builtin_amdgcn_global_load_lds((glb_ptr_t)(ws_ + w_off[i]), (lds_ptr_t)(dst_ + i * 1024), 16, 0, SHARED ? 0 : kAuxNonTemporal); \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                  \
-      __builtin_amdgcn_global_load_lds((glb_ptr_t)(xs_ + x_off[i]), (lds_ptr_t)(dst_ + X_RING + i * 1024), 16, 0, 0); \
+      if (!SPLIT || i < nx)                                                                        \
+        __builtin_amdgcn_global_load_lds((glb_ptr_t)(xs_ + x_off[i]), (lds_ptr_t)(dst_ + X_RING + i * 1024), 16, 0, 0); \
+  }
+
+  // split form: the four columns this lane brings to their end, their bias and residuals asked for in front of all else
+  const int c4 = n0 + 16 * lh + 4 * wave;
+  u32x2 bias = {}, resid16 = {};
+  f32x4 resid32 = {};
+  if (SPLIT) {
+    bias = *reinterpret_cast<const u32x2*>(g.pool + slot_base + g.b_off + (size_t)c4 * 2);
+    if (g.epi == EPI_BIAS_RESID) {
+      if (g.resid_f32) resid32 = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.resid) + (size_t)my_row * g.ldr + c4);
+      else resid16 = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(g.resid) + (size_t)my_row * g.ldr + c4);
+    }
   }
 
   f32x16 acc;
@@ -160,7 +195,11 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
 #pragma unroll
   for (int p = 0; p < INFL; ++p) HMI_COPY_STAGE(p)
   for (int s = 0; s < KT; ++s) {
-    HMI_WAIT_VMCNT(8 * (INFL - 1));          // stage s has landed; the copies of the INFL - 1 stages after it may be in flight
+    // stage s has landed; the copies of the INFL - 1 stages after it may be in flight
+    if (!SPLIT || nx == 4) { HMI_WAIT_VMCNT(8 * (INFL - 1)); }
+    else if (nx == 3) { HMI_WAIT_VMCNT(7 * (INFL - 1)); }
+    else if (nx == 2) { HMI_WAIT_VMCNT(6 * (INFL - 1)); }
+    else { HMI_WAIT_VMCNT(5 * (INFL - 1)); }
     __builtin_amdgcn_sched_barrier(0);
     const unsigned char* sb = ring + (s % STAGES) * STAGE_BYTES;
     bf16x8 fw[4], fx[4];
@@ -177,20 +216,34 @@ __global__ __launch_bounds__((64 * Ring<SPLIT, DEEP>::WAVES)) void gemm_bf16_ski
 #undef HMI_COPY_STAGE
   HMI_WAIT_VMCNT(0);                         // the trailing copies must have landed before the LDS is handed on
   if (SPLIT) {
-    // partial sums of wavefronts 1.. go through their own (now idle) rings; wavefront 0 adds them in order
-    float* red = reinterpret_cast<float*>(ring);
-    if (wave != 0) {
+    // Partial sums meet in the (now idle) rings: wavefront w adds up quads w of every lane's four, in the order of k, and brings
+    // them to their end, four columns of a row a lane.
+    f32x4* const part = reinterpret_cast<f32x4*>(smem);
+    HMI_BARRIER();                           // everybody is done with its ring
 #pragma unroll
-      for (int r = 0; r < 16; ++r) red[r * 64 + lane] = acc[r];
+    for (int q = 0; q < 4; ++q) part[(wave * 4 + q) * 64 + lane] = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    HMI_BARRIER();
+    f32x4 v = part[wave * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < KSPLIT; ++w) v += part[(w * 4 + wave) * 64 + lane];
+    if (l32 >= rows) return;
+    v += f32x4{bf2f(bias[0] & 0xFFFFu), bf2f(bias[0] >> 16), bf2f(bias[1] & 0xFFFFu), bf2f(bias[1] >> 16)};
+    if (g.epi == EPI_BIAS_GELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = gelu_f32(v[e]);
+    } else if (g.epi == EPI_BIAS_RELU) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.0f);
+    } else if (g.epi == EPI_BIAS_RESID) {
+      if (g.resid_f32) v += resid32;
+      else v += f32x4{bf2f(resid16[0] & 0xFFFFu), bf2f(resid16[0] >> 16), bf2f(resid16[1] & 0xFFFFu), bf2f(resid16[1] >> 16)};
     }
-    __syncthreads();
-    if (wave != 0) return;
-#pragma unroll
-    for (int w = 1; w < KSPLIT; ++w) {
-      const float* part = reinterpret_cast<const float*>(smem + w * WAVE_LDS);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] += part[r * 64 + lane];
-    }
+    const u32x2 h = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    const size_t o = (size_t)my_row * g.ldc + c4;
+    if (g.out_f32) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + o) = v;
+    else *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + o) = h;
+    if (g.C2) *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C2) + o) = h;
+    return;
   }
 
   // ---- epilogue: lane (row l32, half lh) holds columns n0 + 16 lh + r, r = 0..15
@@ -275,7 +328,7 @@ void launch_gemm_bf16_skinny(const GemmArgs& g, const Route& rt, hipStream_t s) 
   // leave at once, and are not counted where most tiles are one short row block)
   const long long n_busy = g.n_rows > 32LL * g.n_mtiles ? (g.n_rows + SK - 1) / SK * (g.n_out / SK) : n_panels;
   if (n_busy <= kSplitMaxItems && g.k % (64 * KSPLIT) == 0 && g.k >= 64 * KSPLIT * 2) {
-    if (rt.identity) return launch_ring<true, true, true>(g, rt, s, n_panels * 4);
+    if (rt.identity) return launch_ring<true, true, true>(g, rt, s, (long long)((g.n_rows + SK - 1) / SK) * ((g.n_out / SK + kXcds - 1) / kXcds * kXcds));
     return launch_ring<true, true, false>(g, rt, s, n_panels * 4);
   }
   if (n_panels <= kDeepMaxItems) return launch_ring<false, true, false>(g, rt, s, n_panels);

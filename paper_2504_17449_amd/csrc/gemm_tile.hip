@@ -25,16 +25,23 @@
 //   * Weights are the MFMA's first operand, in a permuted row order, so that a lane ends up with 16 consecutive columns
 //     of one row of C: the epilogue reads residuals and writes results straight from the accumulators in 16-byte pieces.
 //     Accumulators start at the bias.
-//   * Workgroup ids are folded so that each of the 8 XCDs (which get workgroups round robin) works on a contiguous range
-//     of tiles, m-tile by m-tile: an activation panel is fetched by one XCD.
-// Measured (d = 768, f = 3072, one weight set; persistent tiles before, this kernel now): 2 664 rows: QKV 22.1 -> 15.6 us,
-// output projection 20.6 -> 7.0, FFN1 25.6 -> 23, FFN2 71.7 -> 21.9; 8 192 rows: FFN2 75 -> 50.6.  fp32
-// (before: products on the vector ALU): 1 728 rows of eight tenants, two encoder layers with their attention: 1.28 -> 0.67 ms.
+//   * What the launch fetches is what the XCDs' L2s fetch, each for itself: m-tile by m-tile a launch of a few of them reads
+//     the weights once for each.  So the tiles of shared weights are shared out among the XCDs in blocks of rows and columns
+//     (xcd_rows below); with a tenant's own weights an XCD has a contiguous range of tiles, m-tile by m-tile.
+//   * A stage costs a consumer one trip to LDS, one barrier and its products, and only the last grows with it: the small tiles
+//     take two lines of k a stage where k allows (64 x 64, 64 k a stage: 490 clocks, of which 160 are products).
+// Measured, us (d = 768, f = 3072, one weight set; with the persistent tiles, with one line of k a stage, now):
+//   2 664 rows  QKV 22.1, 15.6 - 17.2, 17.2;  output projection 20.6, 8.2, 7.7;  FFN1 25.6, 21.5, 21.2;  FFN2 71.7, 22.8, 19.9
+//   756 rows    output projection and FFN2 together -, 19.7, 18.7
+//   141 rows    QKV -, 6.0, 5.0;  output projection -, 5.6, 4.2
+//   7 rows      QKV -, 5.5, 4.4;  output projection -, 5.4, 4.3;  FFN1 -, 6.6, 5.2
+// fp32 (before: products on the vector ALU): 1 728 rows of eight tenants, two encoder layers with their attention: 1.28 -> 0.67 ms.
 #include "hmi_kernels.h"
 
 #include "gelu.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace hmi {
 namespace {
@@ -43,12 +50,12 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef f32x4 f32x4_any __attribute__((aligned(4)));   // in the caller's result, which may begin at any float
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
 constexpr int kXcds = 8;
-constexpr int NW = 4;                     // consumer wavefronts
 constexpr int ROW_BYTES = 128;            // k bytes of a row and stage
 
 #define HMI_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(0xC07F)
@@ -82,36 +89,56 @@ __device__ __forceinline__ void mfma_chunk(const u32x4& w, const u32x4& x, f32x1
   }
 }
 
-template <bool BF16, int BM, int BN, int WM, int WN, int STAGES, int NP>
-__global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, Route rt, int total, int tiles_per_entry) {
-  static_assert(WM * WN == NW, "four wavefronts");
+// 16 bytes of residual (four columns, fp32 or bf16) as they are loaded, and added.
+union Resid { f32x4 f; u32x2 h; };
+
+// BM x BN: the tile; WM x WN consumers; a stage is U lines of k; STAGES of them in the ring; NP producers.  The epilogue is a
+// parameter too: small launches feel its instructions (as a run-time choice the compiler evaluated GELU for all of them, 0.8 us).
+template <bool BF16, int BM, int BN, int WM, int WN, int U, int STAGES, int NP, int EPI>
+__global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs g, Route rt, int total, int tiles_per_entry, int xcd_rows) {
+  constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
-  constexpr int A_LD = BM / 8 / NP, W_LD = BN / 8 / NP;      // 1 KB copies (8 rows) per producer and stage
-  constexpr int LD = A_LD + W_LD;
-  constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
+  constexpr int A_LD = BM / 8 / NP, W_LD = BN / 8 / NP;      // 1 KB copies (8 rows) per producer and line of k
+  constexpr int LINE_BYTES = (BM + BN) * ROW_BYTES, STAGE_BYTES = U * LINE_BYTES;
   constexpr int ES = BF16 ? 2 : 4;
-  static_assert(LD * (STAGES - 1) < 64, "vmcnt range");
+  constexpr int KS = 4 * U;                                  // k-steps of a stage
+  static_assert(U * (A_LD + W_LD) * (STAGES - 1) < 64, "vmcnt range");
+  static_assert(BF16 || U == 1, "fp32 shapes may leave half a line");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-  // ---- which tile: m-tile by m-tile, an entry of the route's list holds tiles_per_entry tiles of BM rows
+  // ---- which tile.  Workgroups go to the XCDs round robin.
   const int nt_n = (g.n_out + BN - 1) / BN;
-  const int per = (total + kXcds - 1) / kXcds;
-  const int local = blockIdx.x / kXcds;
-  const int w = (blockIdx.x % kXcds) * per + local;
-  if (local >= per || w >= total) return;
-  const int mt = w / nt_n, n0 = (w - mt * nt_n) * BN;
-  const bool ident = rt.identity != 0;      // the shared parameters' route: tiles in row order, identity row map, slot 0
-  int row0, row_end;
+  const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
+  int row0, row_end, n0;
   size_t slot_base = 0;
-  if (ident) {
-    row0 = mt * BM;
+  const bool ident = rt.identity != 0;      // the shared parameters' route: tiles in row order, identity row map, slot 0
+  if (xcd_rows > 0) {
+    // the XCDs share out the tiles as xcd_rows x (8 / xcd_rows) blocks of whole tiles; inside one, panel of weights by panel
+    const int nt_m = total / nt_n, xm = xcd & (xcd_rows - 1), xn = xcd / xcd_rows, xcd_cols = kXcds / xcd_rows;
+    const int m_lo = nt_m * xm / xcd_rows, m_cnt = nt_m * (xm + 1) / xcd_rows - m_lo;
+    const int n_lo = nt_n * xn / xcd_cols, n_cnt = nt_n * (xn + 1) / xcd_cols - n_lo;
+    if (local >= m_cnt * n_cnt) return;
+    const int in = local / m_cnt;
+    row0 = (m_lo + local - in * m_cnt) * BM;
+    n0 = (n_lo + in) * BN;
     row_end = g.n_rows;
   } else {
-    const int entry = mt / tiles_per_entry;
-    const int seg = rt.tile_seg[g.which_tiles][entry];
-    row0 = rt.tile_row0[g.which_tiles][entry] + (mt - entry * tiles_per_entry) * BM;
-    row_end = rt.seg_tok_off[seg + 1];
-    slot_base = (size_t)rt.seg_slot[seg] * g.slot_stride;
+    // m-tile by m-tile, a contiguous range for each XCD; an entry of the route's list holds tiles_per_entry tiles of BM rows
+    const int per = (total + kXcds - 1) / kXcds;
+    const int w = xcd * per + local;
+    if (local >= per || w >= total) return;
+    const int mt = w / nt_n;
+    n0 = (w - mt * nt_n) * BN;
+    if (ident) {
+      row0 = mt * BM;
+      row_end = g.n_rows;
+    } else {
+      const int entry = mt / tiles_per_entry;
+      const int seg = rt.tile_seg[g.which_tiles][entry];
+      row0 = rt.tile_row0[g.which_tiles][entry] + (mt - entry * tiles_per_entry) * BM;
+      row_end = rt.seg_tok_off[seg + 1];
+      slot_base = (size_t)rt.seg_slot[seg] * g.slot_stride;
+    }
   }
   const int rows = min(BM, row_end - row0);
   if (rows <= 0) return;
@@ -119,7 +146,7 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kbytes = g.k * ES;
-  const int KT = kbytes / ROW_BYTES;        // whole stages; fp32 shapes may leave half a stage (64 bytes) behind
+  const int KT = kbytes / (U * ROW_BYTES);  // whole stages; fp32 shapes may leave half a stage (64 bytes) behind
   const bool half_stage = !BF16 && kbytes % ROW_BYTES != 0;
 
   if (wave >= NW) {
@@ -139,43 +166,55 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
       const int row = (pw * W_LD + j) * 8 + (lane >> 3);
       w_off[j] = (uint32_t)min(n0 + row, g.n_out - 1) * (uint32_t)(g.k * ES) + (((lane & 7) ^ swz_w(row)) << 4);
     }
-    const char* a_next = reinterpret_cast<const char*>(g.A);   // the stage of k that is copied next (uniform)
+    const char* a_next = reinterpret_cast<const char*>(g.A);   // the line of k that is copied next (uniform)
     const char* w_next = g.pool + slot_base + g.w_off;
-    auto copy_stage = [&](int slot_off) {
-      unsigned char* dst = smem + slot_off;
+    // ROWS: this producer's activation rows exist (of a tile of a few rows the others are not copied: nobody looks at what
+    // the products make of them)
+    auto produce = [&](auto with_rows) {
+      constexpr bool ROWS = decltype(with_rows)::value;
+      constexpr int LD = U * (W_LD + (ROWS ? A_LD : 0));
+      auto copy_stage = [&](int slot_off) {
 #pragma unroll
-      for (int j = 0; j < A_LD; ++j)
-        __builtin_amdgcn_global_load_lds((glb_ptr_t)(a_next + a_off[j]), (lds_ptr_t)(dst + (pw * A_LD + j) * 1024), 16, 0, 0);
+        for (int u = 0; u < U; ++u) {
+          unsigned char* dst = smem + slot_off + u * LINE_BYTES;
+          if (ROWS) {
 #pragma unroll
-      for (int j = 0; j < W_LD; ++j)
-        __builtin_amdgcn_global_load_lds((glb_ptr_t)(w_next + w_off[j]), (lds_ptr_t)(dst + BM * ROW_BYTES + (pw * W_LD + j) * 1024), 16, 0, 0);
-      a_next += ROW_BYTES; w_next += ROW_BYTES;
-    };
+            for (int j = 0; j < A_LD; ++j)
+              __builtin_amdgcn_global_load_lds((glb_ptr_t)(a_next + a_off[j]), (lds_ptr_t)(dst + (pw * A_LD + j) * 1024), 16, 0, 0);
+          }
 #pragma unroll
-    for (int p = 0; p < STAGES - 1; ++p)
-      if (p < KT) copy_stage(p * STAGE_BYTES);
-    int fill = (STAGES - 1) * STAGE_BYTES;
-    for (int s = 0; s < KT; ++s) {
-      // stage s has landed: only the STAGES - 2 stages behind it may be in flight
-      if (s + STAGES - 1 <= KT) HMI_WAIT_VMCNT(LD * (STAGES - 2)); else HMI_WAIT_VMCNT(0);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      if (s + STAGES - 1 < KT) {            // into the slot of stage s - 1, which nobody reads any more
-        copy_stage(fill);
-        fill = fill == (STAGES - 1) * STAGE_BYTES ? 0 : fill + STAGE_BYTES;
+          for (int j = 0; j < W_LD; ++j)
+            __builtin_amdgcn_global_load_lds((glb_ptr_t)(w_next + w_off[j]), (lds_ptr_t)(dst + BM * ROW_BYTES + (pw * W_LD + j) * 1024), 16, 0, 0);
+          a_next += ROW_BYTES; w_next += ROW_BYTES;
+        }
+      };
+#pragma unroll
+      for (int p = 0; p < STAGES - 1; ++p)
+        if (p < KT) copy_stage(p * STAGE_BYTES);
+      int fill = (STAGES - 1) * STAGE_BYTES;
+      for (int s = 0; s < KT; ++s) {
+        // stage s has landed: only the STAGES - 2 stages behind it may be in flight
+        if (s + STAGES - 1 <= KT) HMI_WAIT_VMCNT(LD * (STAGES - 2)); else HMI_WAIT_VMCNT(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + STAGES - 1 < KT) {            // into the slot of stage s - 1, which nobody reads any more
+          copy_stage(fill);
+          fill = fill == (STAGES - 1) * STAGE_BYTES ? 0 : fill + STAGE_BYTES;
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (half_stage) {                       // chunks 0-3 of the rows, and again instead of chunks 4-7 past the row's end
+      if (half_stage) {                       // chunks 0-3 of the rows, and again instead of chunks 4-7 past the row's end
 #pragma unroll
-      for (int j = 0; j < A_LD; ++j) a_off[j] -= (((lane & 7) ^ swz_a((pw * A_LD + j) * 8 + (lane >> 3))) & 4) << 4;
+        for (int j = 0; j < A_LD; ++j) a_off[j] -= (((lane & 7) ^ swz_a((pw * A_LD + j) * 8 + (lane >> 3))) & 4) << 4;
 #pragma unroll
-      for (int j = 0; j < W_LD; ++j) w_off[j] -= (((lane & 7) ^ swz_w((pw * W_LD + j) * 8 + (lane >> 3))) & 4) << 4;
-      __builtin_amdgcn_s_barrier();         // everybody has read the last whole stage
-      copy_stage(0);
-      HMI_WAIT_VMCNT(0);
-      __builtin_amdgcn_s_barrier();
-    }
+        for (int j = 0; j < W_LD; ++j) w_off[j] -= (((lane & 7) ^ swz_w((pw * W_LD + j) * 8 + (lane >> 3))) & 4) << 4;
+        __builtin_amdgcn_s_barrier();         // everybody has read the last whole stage
+        copy_stage(0);
+        HMI_WAIT_VMCNT(0);
+        __builtin_amdgcn_s_barrier();
+      }
+    };
+    if (BM == 32 && pw * A_LD * 8 >= rows) produce(std::false_type{}); else produce(std::true_type{});
     return;
   }
 
@@ -183,7 +222,7 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
   const int l32 = lane & 31, lh = lane >> 5;
   const int wm = wave / WN, wn = wave % WN;
   const int rx = wm * WTM + l32, rw = wn * WTN + perm_w(l32);
-  const int fx_base = rx * ROW_BYTES + ((lh ^ swz_a(rx)) << 4);       // fragment offsets inside a stage (k-step ks: XOR ks << 5)
+  const int fx_base = rx * ROW_BYTES + ((lh ^ swz_a(rx)) << 4);       // fragment offsets inside a line of k (k-step ks: XOR ks << 5)
   const int fw_base = BM * ROW_BYTES + rw * ROW_BYTES + ((lh ^ swz_w(rw)) << 4);
   f32x16 acc[TM][TN];                       // start at the bias
   f32x16 acc2[TM][TN];                      // fp32: every other product's sum, from zero
@@ -219,41 +258,77 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
   }
   const bool wave_active = wm * WTM < rows && n0 + wn * WTN < g.n_out;
 
-  u32x4 fx[4][TM], fw[4][TN];               // one fragment buffer per k-step of a stage
-  int rd = 0;                               // byte offset of the slot that is read
-#define HMI_READ_FRAGS(KS)                                                                         \
-  {                                                                                                \
-    const unsigned char* sb_ = smem + rd;                                                          \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i) fx[KS][i] = *reinterpret_cast<const u32x4*>(sb_ + (fx_base ^ ((KS) << 5)) + i * 32 * ROW_BYTES); \
-    _Pragma("unroll") for (int j = 0; j < TN; ++j) fw[KS][j] = *reinterpret_cast<const u32x4*>(sb_ + (fw_base ^ ((KS) << 5)) + j * 32 * ROW_BYTES); \
+  // fp32 results, and residuals, cross a patch of LDS so that the lanes of a row read and write it in whole lines: 32 CF columns of
+  // a row, four to a lane (straight from the accumulators an instruction touches 64 lines: 3.2 us of a 128 x 64 tile's epilogue,
+  // now 2.2).  bf16 results leave from the accumulators: there is half as much of them, and the way through LDS was the longer one
+  // (128 x 256 tiles with GELU 5.5 us for 6.8, 32 x 32 tiles 0.4 for 1.2).
+  constexpr int CF = TN < 2 ? TN : 2;
+  constexpr int FL = 8 * CF;                                 // lanes of a row
+  static_assert(STAGE_BYTES >= NW * 32 * CF * 128, "patches fit a stage");
+  const bool staged = !BF16 || g.out_f32 || EPI == EPI_BIAS_RESID;
+  const bool resid_f32 = !BF16 || g.resid_f32;
+  // the residuals of the small tiles are asked for now, the large ones' when their turn comes
+  constexpr bool AHEAD = TM * TN <= 2 && BF16;
+  Resid ahead[AHEAD ? TM * TN * 4 : 1];
+  auto load_resid = [&](int i, int j, int it) {              // piece `it` of the pass that begins at column block j
+    const int r = it * (64 / FL) + lane / FL, m = wm * WTM + i * 32 + r;
+    const int col = n0 + wn * WTN + j * 32 + (lane % FL) * 4;
+    Resid v = {};
+    const size_t at = (size_t)__shfl(out_row[i], r, 64) * g.ldr + col;
+    if (m < rows && col < g.n_out) {
+      if (resid_f32) v.f = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.resid) + at);
+      else v.h = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(g.resid) + at);
+    }
+    return v;
+  };
+  if (AHEAD && EPI == EPI_BIAS_RESID && wave_active) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; j += CF)
+#pragma unroll
+        for (int it = 0; it < 4 * CF; ++it) ahead[(i * TN + j) * 4 + it] = load_resid(i, j, it);
   }
-#define HMI_MULTIPLY(KS)                                                                           \
+
+  u32x4 fx[KS][TM], fw[KS][TN];             // one fragment buffer per k-step of a stage
+  int rd = 0;                               // byte offset of the slot that is read
+#define HMI_READ_FRAGS(S)                                                                          \
+  {                                                                                                \
+    const unsigned char* sb_ = smem + rd + ((S) / 4) * LINE_BYTES;                                 \
+    _Pragma("unroll") for (int i = 0; i < TM; ++i) fx[S][i] = *reinterpret_cast<const u32x4*>(sb_ + (fx_base ^ (((S) & 3) << 5)) + i * 32 * ROW_BYTES); \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j) fw[S][j] = *reinterpret_cast<const u32x4*>(sb_ + (fw_base ^ (((S) & 3) << 5)) + j * 32 * ROW_BYTES); \
+  }
+#define HMI_MULTIPLY(S)                                                                            \
   {                                                                                                \
     _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                 \
-      _Pragma("unroll") for (int j = 0; j < TN; ++j) mfma_chunk<BF16>(fw[KS][j], fx[KS][i], acc[i][j], acc2[i][j]); \
+      _Pragma("unroll") for (int j = 0; j < TN; ++j) mfma_chunk<BF16>(fw[S][j], fx[S][i], acc[i][j], acc2[i][j]); \
     __builtin_amdgcn_sched_barrier(0);                                                             \
   }
-  // Fragments are read two to three k-steps ahead of their products.  The barrier of a stage stands in the middle of the
-  // products of the stage before it: this wavefront has read all of that one, and the new stage's first fragments are on
-  // their way under the other half.
+  // Fragments are read two to three k-steps ahead of their products.  The barrier of a stage stands two k-steps before the end
+  // of the products of the stage before it: this wavefront has read all of that one, and the new stage's first fragments are on
+  // their way under the rest.
   if (KT > 0) {
     __builtin_amdgcn_s_barrier();           // stage 0 is there
     __builtin_amdgcn_sched_barrier(0);
   }
   HMI_READ_FRAGS(0) HMI_READ_FRAGS(1) HMI_READ_FRAGS(2)
   for (int s = 0; s < KT; ++s) {
-    HMI_READ_FRAGS(3)
-    HMI_MULTIPLY(0)
-    HMI_MULTIPLY(1)
+#pragma unroll
+    for (int ks = 0; ks < KS - 2; ++ks) {
+      if (ks + 3 < KS) HMI_READ_FRAGS(ks + 3)
+      HMI_MULTIPLY(ks)
+    }
     HMI_WAIT_LGKMCNT0();
     if (s + 1 < KT) __builtin_amdgcn_s_barrier();     // stage s + 1 is there
     __builtin_amdgcn_sched_barrier(0);
     rd = rd == (STAGES - 1) * STAGE_BYTES ? 0 : rd + STAGE_BYTES;
     HMI_READ_FRAGS(0) HMI_READ_FRAGS(1)               // (behind the last stage: read, but not multiplied)
-    HMI_MULTIPLY(2)
+    HMI_MULTIPLY(KS - 2)
     HMI_READ_FRAGS(2)
-    HMI_MULTIPLY(3)
+    HMI_MULTIPLY(KS - 1)
   }
+  // the slot behind the last stage's, which no wavefront reads any more but for the idle reads above
+  unsigned char* const patch = smem + (half_stage ? STAGE_BYTES : rd) + wave * (32 * CF * 128);
   if (half_stage) {
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_s_barrier();
@@ -269,16 +344,11 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
   // ---- epilogue: lane (row l32, half lh) of MFMA tile (i, j) holds columns 16 lh .. 16 lh + 15 of its 32
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
-    const int r = wm * WTM + i * 32 + l32;
-    if (r >= rows) continue;
-    const size_t orow = (size_t)out_row[i];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = n0 + wn * WTN + j * 32 + 16 * lh;
-      if (col >= g.n_out) continue;
+    if (wm * WTM + i * 32 >= rows) break;
+    auto value = [&](int j) {
       f32x16 v = acc[i][j];
       if (!BF16) v += acc2[i][j];
-      if (g.epi == EPI_BIAS_GELU) {
+      if (EPI == EPI_BIAS_GELU) {
         if (BF16 && g.gelu_poly) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) v[e] = gelu_poly(v[e]);
@@ -286,48 +356,65 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
 #pragma unroll
           for (int e = 0; e < 16; ++e) v[e] = BF16 ? gelu_f32(v[e]) : gelu_erf(v[e]);
         }
-      } else if (g.epi == EPI_BIAS_RELU) {
+      } else if (EPI == EPI_BIAS_RELU) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) v[e] = fmaxf(v[e], 0.0f);
-      } else if (g.epi == EPI_BIAS_RESID) {
-        if (!BF16 || g.resid_f32) {
-          const f32x4* rp = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.resid) + orow * g.ldr + col);
+      }
+      return v;
+    };
+    if (staged) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 rv = rp[q];
+      for (int j = 0; j < TN; j += CF) {
+        Resid later[AHEAD ? 1 : 4 * CF];
+        if (!AHEAD && EPI == EPI_BIAS_RESID) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * q + e] += rv[e];
+          for (int it = 0; it < 4 * CF; ++it) later[it] = load_resid(i, j, it);
+        }
+#pragma unroll
+        for (int jj = 0; jj < CF; ++jj) {
+          const f32x16 v = value(j + jj);
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(patch + l32 * (FL * 16) + (((jj * 8 + lh * 4 + q) ^ (l32 & (FL - 1))) << 4)) =
+                f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        }
+#pragma unroll
+        for (int it = 0; it < 4 * CF; ++it) {
+          const int r = it * (64 / FL) + lane / FL, m = wm * WTM + i * 32 + r;
+          const int col = n0 + wn * WTN + j * 32 + (lane % FL) * 4;
+          f32x4 v = *reinterpret_cast<const f32x4*>(patch + r * (FL * 16) + (((lane % FL) ^ (r & (FL - 1))) << 4));
+          const size_t off = (size_t)__shfl(out_row[i], r, 64) * g.ldc + col;
+          if (EPI == EPI_BIAS_RESID) {
+            const Resid rv = AHEAD ? ahead[(i * TN + j) * 4 + it] : later[AHEAD ? 0 : it];
+            if (resid_f32) v += rv.f;
+            else v += f32x4{bf2f(rv.h[0] & 0xFFFFu), bf2f(rv.h[0] >> 16), bf2f(rv.h[1] & 0xFFFFu), bf2f(rv.h[1] >> 16)};
           }
-        } else {
-          const u32x4* rp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(g.resid) + orow * g.ldr + col);
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const u32x4 rv = rp[q];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { v[8 * q + 2 * e] += bf2f(rv[e] & 0xFFFFu); v[8 * q + 2 * e + 1] += bf2f(rv[e] >> 16); }
+          if (m >= rows || col >= g.n_out) continue;
+          if (!BF16 || g.out_f32) *reinterpret_cast<f32x4_any*>(reinterpret_cast<float*>(g.C) + off) = v;
+          if (!BF16) {
+            if (g.C2) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C2) + off) = v;
+          } else {
+            const u32x2 h = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            if (!g.out_f32) *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + off) = h;
+            if (g.C2) *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C2) + off) = h;
           }
         }
       }
-      const size_t off = orow * g.ldc + col;
-      if (!BF16 || g.out_f32) {
-        f32x4_any* cp = reinterpret_cast<f32x4_any*>(reinterpret_cast<float*>(g.C) + off);
+    } else if (wm * WTM + i * 32 + l32 < rows) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cp[q] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-      }
-      if (!BF16) {
-        if (g.C2) {
-          f32x4* cp = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C2) + off);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) cp[q] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-        }
-      } else if (!g.out_f32 || g.C2) {
+      for (int j = 0; j < TN; ++j) {
+        const int col = n0 + wn * WTN + j * 32 + 16 * lh;
+        if (col >= g.n_out) continue;
+        const f32x16 v = value(j);
         u32x4 h[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
 #pragma unroll
           for (int e = 0; e < 4; ++e) h[q][e] = pack_bf16(v[8 * q + 2 * e], v[8 * q + 2 * e + 1]);
-        if (!g.out_f32) { u32x4* cp = reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C) + off); cp[0] = h[0]; cp[1] = h[1]; }
-        if (g.C2) { u32x4* cp = reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C2) + off); cp[0] = h[0]; cp[1] = h[1]; }
+        const size_t off = (size_t)out_row[i] * g.ldc + col;
+        u32x4* cp = reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C) + off);
+        cp[0] = h[0]; cp[1] = h[1];
+        if (g.C2) { u32x4* cp2 = reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C2) + off); cp2[0] = h[0]; cp2[1] = h[1]; }
       }
     }
   }
@@ -337,13 +424,16 @@ __global__ __launch_bounds__(64 * (NW + NP)) void gemm_tile_kernel(GemmArgs g, R
 // epilogue with it takes 1.3 us, with the exact one 2.5); small ones, where it costs nothing, and odd shapes are exact.
 bool gelu_poly_fits(const GemmArgs& g) { return g.n_rows > 1024 && g.n_out % 256 == 0 && g.k >= 192; }
 
-template <bool BF16, int BM, int BN, int WM, int WN, int STAGES>
+template <bool BF16, int BM, int BN, int WM, int WN, int U, int STAGES>
 struct Tile {
   static constexpr int NP = 4;              // producers
-  static constexpr int LDS = STAGES * (BM + BN) * ROW_BYTES;
+  static constexpr int LDS = STAGES * U * (BM + BN) * ROW_BYTES;
+  static_assert(LDS <= 163840, "LDS");
+  template <int EPI>
+  static constexpr auto kernel() { return &gemm_tile_kernel<BF16, BM, BN, WM, WN, U, STAGES, NP, EPI>; }
   static void allow_lds() {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_tile_kernel<BF16, BM, BN, WM, WN, STAGES, NP>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    for (auto k : {kernel<EPI_BIAS>(), kernel<EPI_BIAS_GELU>(), kernel<EPI_BIAS_RELU>(), kernel<EPI_BIAS_RESID>()})
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
   }
   static int per_entry(const Route& rt, int list) { return rt.tile_m[list] / BM; }
   // tiles of a launch; on a tenant route an entry of the list counts with all tiles it has room for
@@ -356,20 +446,38 @@ struct Tile {
     g.gelu_poly = gelu_poly_fits(g);
     const long long total = tiles(g, rt, list);
     if (total <= 0) return;
-    const int per = (int)((total + kXcds - 1) / kXcds);
-    hipLaunchKernelGGL((gemm_tile_kernel<BF16, BM, BN, WM, WN, STAGES, NP>), dim3(per * kXcds), dim3(64 * (NW + NP)), LDS, s,
-                       g, rt, (int)total, per_entry(rt, list));
+    long long per = (total + kXcds - 1) / kXcds;
+    int xcd_rows = 0;
+    if (rt.identity) {
+      // the split that fetches least: each XCD reads its blocks' rows of A and of W.  Only where an XCD runs all of its tiles at
+      // once: an uneven split costs a launch of several rounds more than it saves (2 664 rows, 756 tiles of QKV: 17.2 us -> 19.4).
+      const long long nt_n = (g.n_out + BN - 1) / BN, nt_m = total / nt_n;
+      const long long room = (long long)(rt.n_cu >= kXcds ? rt.n_cu : 256) / kXcds * (163840 / LDS);
+      long long best = 0;
+      for (int xr = 1; xr <= kXcds; xr *= 2) {
+        const long long xc = kXcds / xr, mine = ((nt_m + xr - 1) / xr) * ((nt_n + xc - 1) / xc);
+        const long long rows = g.n_rows * xc + (long long)g.n_out * xr;
+        if (mine <= room && (xcd_rows == 0 || rows < best)) { best = rows; per = mine; xcd_rows = xr; }
+      }
+    }
+    const auto k = g.epi == EPI_BIAS ? kernel<EPI_BIAS>() : g.epi == EPI_BIAS_GELU ? kernel<EPI_BIAS_GELU>() :
+                   g.epi == EPI_BIAS_RELU ? kernel<EPI_BIAS_RELU>() : kernel<EPI_BIAS_RESID>();
+    hipLaunchKernelGGL(k, dim3((unsigned)(per * kXcds)), dim3(64 * (WM * WN + NP)), LDS, s, g, rt, (int)total, per_entry(rt, list), xcd_rows);
   }
 };
-typedef Tile<true, 64, 64, 2, 2, 5> TileS;        // 80 KB of LDS: two workgroups per compute unit
-typedef Tile<true, 128, 64, 2, 2, 3> TileM;       // 72 KB: two
-typedef Tile<true, 128, 128, 2, 2, 3> TileL;      // 96 KB: one
-typedef Tile<true, 128, 256, 2, 2, 3> TileXL;     // 144 KB: one
-typedef Tile<false, 64, 64, 2, 2, 5> TileF32;
+typedef Tile<true, 64, 64, 2, 2, 1, 5> TileS;        // 80 KB of LDS: two workgroups per compute unit
+typedef Tile<true, 64, 64, 2, 2, 2, 3> TileS2;       // 96 KB: one
+typedef Tile<true, 32, 64, 1, 2, 2, 4> TileT2;       // 96 KB: one
+typedef Tile<true, 32, 32, 1, 1, 2, 6> TileU2;       // 96 KB: one
+typedef Tile<true, 128, 64, 2, 2, 1, 3> TileM;       // 72 KB: two
+typedef Tile<true, 128, 64, 2, 2, 2, 3> TileM2;      // 144 KB: one
+typedef Tile<true, 128, 128, 2, 2, 1, 3> TileL;      // 96 KB: one
+typedef Tile<true, 128, 256, 2, 2, 1, 3> TileXL;     // 144 KB: one
+typedef Tile<false, 64, 64, 2, 2, 1, 5> TileF32;
 }  // namespace
 
 void init_gemm_tile_kernels() {
-  TileS::allow_lds(); TileM::allow_lds(); TileL::allow_lds(); TileXL::allow_lds(); TileF32::allow_lds();
+  TileS::allow_lds(); TileS2::allow_lds(); TileT2::allow_lds(); TileU2::allow_lds(); TileM::allow_lds(); TileM2::allow_lds(); TileL::allow_lds(); TileXL::allow_lds(); TileF32::allow_lds();
 }
 
 // Which kernel a launch gets.
@@ -415,13 +523,19 @@ GemmKernel pick_gemm_bf16(const GemmArgs& g, const Route& rt) {
 void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
   if (g.n_rows <= 0 || g.n_mtiles_list[1] <= 0) return;
   GemmArgs a = g;
+  const int n_cu = rt.n_cu >= kXcds ? rt.n_cu : 256;
+  const bool two = g.k % 128 == 0;           // whole stages of two lines
   switch (pick_gemm_bf16(g, rt)) {
     case GEMM_STREAM:
       a.which_tiles = 1;
       a.n_mtiles = g.n_mtiles_list[1];
       return launch_gemm_bf16_skinny(a, rt, s);
-    case GEMM_64x64: return TileS::launch(g, rt, 1, s);
-    case GEMM_128x64: return TileM::launch(g, rt, 1, s);
+    case GEMM_64x64:
+      if (two && TileU2::tiles(g, rt, 1) <= n_cu) return TileU2::launch(g, rt, 1, s);
+      if (two && TileT2::tiles(g, rt, 1) <= n_cu) return TileT2::launch(g, rt, 1, s);
+      if (two && TileS2::tiles(g, rt, 1) <= n_cu) return TileS2::launch(g, rt, 1, s);
+      return TileS::launch(g, rt, 1, s);
+    case GEMM_128x64: return two && TileM2::tiles(g, rt, 1) <= n_cu ? TileM2::launch(g, rt, 1, s) : TileM::launch(g, rt, 1, s);
     case GEMM_128x128: return TileL::launch(g, rt, 1, s);
     case GEMM_128x256: return TileXL::launch(g, rt, 1, s);
     case GEMM_PERSISTENT:
