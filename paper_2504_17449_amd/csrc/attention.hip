@@ -32,11 +32,18 @@ constexpr int KB = 64;        // keys per LDS block
 constexpr int DH = 64;        // head width
 constexpr int VT_LD = 72;     // V^T row pitch in elements (keys), padded
 
+// STORE (a prompt in front of decode steps): the workgroup also puts the keys and values of its own rows into the request's cache
+// line, as they pass through its registers (69 632 rows of d = 768: a kernel of its own read them again, 101 us a layer).
+//
+// Heads are the fastest index of the grid, not the blocks of queries: workgroups go to the XCDs round robin, and with two or four
+// blocks in front each XCD would get the same block of every request, the first full and the last mostly empty (requests of
+// 16 to 256 rows: half of the XCDs had nothing to do for the last third of the launch).
+template <bool STORE>
 __global__ __launch_bounds__(256) void attn_bf16_kernel(AttnArgs a, Route rt) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[KB * DH];      // [key][dh], swizzled chunks
   __shared__ __attribute__((aligned(16))) uint16_t Vt[DH * VT_LD];   // [dh][key]
 
-  const int r = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * QB;
+  const int r = blockIdx.z, head = blockIdx.x, q0 = blockIdx.y * QB;
   const int start = rt.tok_off[r];
   const int len = rt.tok_off[r + 1] - start;
   if (q0 >= len) return;
@@ -85,6 +92,13 @@ __global__ __launch_bounds__(256) void attn_bf16_kernel(AttnArgs a, Route rt) {
       vw[e] = *reinterpret_cast<const uint32_t*>(Vg + (size_t)min((K0) + v_kg * 8 + e, len - 1) * ld + v_cp * 2); \
   }
   HMI_LOAD_BLOCK(0)
+  // the request's cache line: keys, then values, of this head over positions
+  uint16_t* Kc = nullptr;
+  uint16_t* Vc = nullptr;
+  if (STORE) {
+    Kc = a.cache + ((size_t)rt.kv_slot[r] * 2 * a.n_heads + head) * a.max_len * DH + (size_t)rt.kv_pos[r] * DH;
+    Vc = Kc + (size_t)a.n_heads * a.max_len * DH;
+  }
 
   for (int k0 = 0; k0 < n_keys; k0 += KB) {
     __syncthreads();  // previous block fully consumed
@@ -102,6 +116,18 @@ __global__ __launch_bounds__(256) void attn_bf16_kernel(AttnArgs a, Route rt) {
       }
       *reinterpret_cast<u32x4*>(Vt + (2 * v_cp) * VT_LD + v_kg * 8) = lo;
       *reinterpret_cast<u32x4*>(Vt + (2 * v_cp + 1) * VT_LD + v_kg * 8) = hi;
+    }
+    if (STORE && k0 >= q0) {   // (no key behind the workgroup's own queries is looked at)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int qd = t + 256 * i, key = k0 + (qd >> 3), c = qd & 7;
+        if (key < len) __builtin_nontemporal_store(kreg[i], reinterpret_cast<u32x4*>(Kc + (size_t)key * DH + c * 8));
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int key = k0 + v_kg * 8 + e;
+        if (key < len) __builtin_nontemporal_store(vw[e], reinterpret_cast<uint32_t*>(Vc + (size_t)key * DH + v_cp * 2));
+      }
     }
     if (k0 + KB < n_keys) HMI_LOAD_BLOCK(k0 + KB)   // in flight during this block's arithmetic
     __syncthreads();
@@ -226,7 +252,7 @@ __device__ __forceinline__ bool finite(float v) { return (__float_as_uint(v) & 0
 __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(AttnArgs a, Route rt) {
   __shared__ f32x4 Ks[FK * 16];
   __shared__ f32x4 Vs[FK * 16];
-  const int r = blockIdx.z, head = blockIdx.y, q0 = blockIdx.x * FQ;
+  const int r = blockIdx.z, head = blockIdx.x, q0 = blockIdx.y * FQ;
   const int start = rt.tok_off[r];
   const int len = rt.tok_off[r + 1] - start;
   if (q0 >= len) return;
@@ -418,10 +444,11 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a, Route rt, int 
 void launch_attention(const AttnArgs& a, const Route& rt, hipStream_t s) {
   if (a.R <= 0) return;
   if (a.bf16) {
-    dim3 grid((a.max_len + QB - 1) / QB, a.n_heads, a.R);
-    hipLaunchKernelGGL(attn_bf16_kernel, grid, dim3(256), 0, s, a, rt);
+    dim3 grid(a.n_heads, (a.longest + QB - 1) / QB, a.R);
+    if (a.cache) hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, dim3(256), 0, s, a, rt);
+    else hipLaunchKernelGGL(attn_bf16_kernel<false>, grid, dim3(256), 0, s, a, rt);
   } else if (a.d == 64 * a.n_heads) {
-    dim3 grid((a.max_len + FQ - 1) / FQ, a.n_heads, a.R);
+    dim3 grid(a.n_heads, (a.longest + FQ - 1) / FQ, a.R);
     hipLaunchKernelGGL(attn_f32_mfma_kernel, grid, dim3(256), 0, s, a, rt);
   } else {
     dim3 grid(a.n_rows, a.n_heads, 1);

@@ -159,8 +159,12 @@ void launch_head(const HeadArgs& a, const Route& rt, int R, int longest, bool bf
 
 // Per-request multi-head attention on packed qkv [N, 3d] (q | k | v) -> ctx [N, d].
 struct AttnArgs {
-  const void* qkv; void* ctx; int d; int n_heads; int causal; int R; int max_len; int bf16;
-  int n_rows;  // N = total rows (fp32 kernel: one wavefront per row and head)
+  const void* qkv; void* ctx; int d; int n_heads; int causal; int R;
+  int longest;         // rows of the longest request
+  int bf16;
+  int n_rows;          // N = total rows (fp32 kernel: one wavefront per row and head)
+  uint16_t* cache;     // bf16 prompts: the layer's key/value lines, into which the rows' keys and values go too (else null)
+  int max_len;         // positions of a line
 };
 void launch_attention(const AttnArgs& a, const Route& rt, hipStream_t s);
 
@@ -173,14 +177,14 @@ struct PlotArgs {
 };
 void launch_plot_aggregate(const PlotArgs& a, int R, int longest, long long rows, bool bf16, hipStream_t s);
 
-// Key/value cache of one layer: [slot][k | v][head][position][64] bf16.
+// Key/value cache of one layer: [slot][k | v][head][position][64] bf16.  A decode step appends to the lines (launch_attn_decode),
+// a prompt's rows are put there by its attention (AttnArgs::cache).
 struct KvArgs {
   const void* qkv;     // bf16 [N, 3d] of the batch (q | k | v)
   void* ctx;           // decode: bf16 [N, d] attention output (N = R, one row per request)
   uint16_t* cache;     // the layer's lines
   int d, n_heads, max_len;
 };
-void launch_kv_store(const KvArgs& a, const Route& rt, int R, int longest, hipStream_t s);   // longest: rows of the longest request
 void launch_attn_decode(const KvArgs& a, const Route& rt, int R, hipStream_t s);
 
 }  // namespace hmi

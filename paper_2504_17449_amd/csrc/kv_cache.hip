@@ -6,8 +6,9 @@
 // keys (values) of one head are contiguous over positions: a decode step streams them with
 // coalesced 1 KB reads.
 //
-//   kv_store_kernel    after a full-sequence (prefill) QKV projection: every row's k and v go
-//                      to position (first position of the request + row index) of its line.
+// After a prompt every row's key and value go to position (first position of the request + row index) of its line: the
+// attention kernel puts them there.
+//
 //   attn_decode_kernel one new token per request: one workgroup per (request, head).  Eight
 //                      lanes share a position (16 bytes of the 128-byte key each), 32 positions
 //                      per step of the workgroup, four steps' loads in flight at a time; an online
@@ -30,34 +31,6 @@ constexpr int DH = 64;
 
 __device__ __forceinline__ size_t line_off(const KvArgs& a, int slot, int kv, int head) {
   return ((((size_t)slot * 2 + kv) * a.n_heads + head) * a.max_len) * DH;
-}
-
-// A workgroup moves kStoreRows rows of one request (a request per workgroup left the chip to a few hundred workgroups and
-// the launch to the longest request: 69 632 rows of d = 768 in 254 us, 756 rows of seven requests in 56; now 100 and 6).
-// A thread keeps its 16-byte column of the row and steps through the rows: it divides once, and has four rows in flight.
-constexpr int kStoreRows = 16;
-
-__global__ __launch_bounds__(256) void kv_store_kernel(KvArgs a, Route rt) {
-  const int r = blockIdx.y;
-  const int start = rt.tok_off[r], len = rt.tok_off[r + 1] - start;
-  const int i0 = blockIdx.x * kStoreRows, i1 = min(i0 + kStoreRows, len);
-  if (i0 >= len) return;
-  const int slot = rt.kv_slot[r], pos0 = rt.kv_pos[r];
-  const uint16_t* qkv = reinterpret_cast<const uint16_t*>(a.qkv) + (size_t)start * 3 * a.d + a.d;   // k then v of a row
-  const int cpr = a.d / 8;                         // 16-byte chunks per row of k (or v)
-  for (int c = threadIdx.x; c < 2 * cpr; c += 256) {
-    const int kv = c >= cpr, cc = c - kv * cpr;
-    const uint16_t* from = qkv + c * 8;
-    uint16_t* to = a.cache + line_off(a, slot, kv, cc >> 3) + (size_t)pos0 * DH + (cc & 7) * 8;
-    for (int i = i0; i < i1; i += 4) {
-      u16x8 v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const u16x8*>(from + (size_t)min(i + u, i1 - 1) * 3 * a.d);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i + u < i1) __builtin_nontemporal_store(v[u], reinterpret_cast<u16x8*>(to + (size_t)(i + u) * DH));
-    }
-  }
 }
 
 // running softmax state of one lane: maximum, denominator, 8 numerators
@@ -177,11 +150,6 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(KvArgs a, Route rt) {
 }
 
 }  // namespace
-
-void launch_kv_store(const KvArgs& a, const Route& rt, int R, int longest, hipStream_t s) {
-  if (R <= 0) return;
-  hipLaunchKernelGGL(kv_store_kernel, dim3((longest + kStoreRows - 1) / kStoreRows, R), dim3(256), 0, s, a, rt);
-}
 
 void launch_attn_decode(const KvArgs& a, const Route& rt, int R, hipStream_t s) {
   if (R <= 0) return;

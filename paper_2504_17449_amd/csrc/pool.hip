@@ -1114,17 +1114,19 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
       launch_layernorm(a, p->rt_dense, s);
     };
     auto attention = [&](bool causal) {
-      if (kv != KV_NONE) {   // decoder blocks only (hmi_kv_create refuses the others)
+      uint16_t* const cache = kv == KV_NONE ? nullptr : p->d_kv + (size_t)layer * p->kv_seqs * 2 * (size_t)d * p->kv_max_len;
+      if (kv == KV_DECODE) {   // decoder blocks only (hmi_kv_create refuses the others)
         KvArgs k{};
         k.qkv = p->w_qkv; k.ctx = p->w_ctx; k.d = d; k.n_heads = c.n_heads; k.max_len = p->kv_max_len;
-        k.cache = p->d_kv + (size_t)layer * p->kv_seqs * 2 * (size_t)d * p->kv_max_len;
+        k.cache = cache;
         ProfSpan ps(p, HMI_KERNEL_ATTENTION);
-        if (kv == KV_PREFILL) launch_kv_store(k, rt, R, max_len, s);
-        else { launch_attn_decode(k, rt, R, s); return; }
+        launch_attn_decode(k, rt, R, s);
+        return;
       }
       AttnArgs a{};
       a.qkv = p->w_qkv; a.ctx = p->w_ctx; a.d = d; a.n_heads = c.n_heads; a.causal = causal;
-      a.R = R; a.max_len = max_len; a.bf16 = p->bf16; a.n_rows = (int)N;
+      a.R = R; a.longest = max_len; a.bf16 = p->bf16; a.n_rows = (int)N;
+      a.cache = cache; a.max_len = p->kv_max_len;
       ProfSpan ps(p, HMI_KERNEL_ATTENTION);
       launch_attention(a, rt, s);
     };
