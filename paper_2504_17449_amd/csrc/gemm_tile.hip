@@ -21,7 +21,8 @@
 //     (element e of the two lane halves' chunks is one k-step of two; the k order inside a stage is the same for both
 //     operands, so it does not matter that it is not ascending).  fp32 products go to two accumulators in turn: a sum of half
 //     as many, whose rounding errors are 0.7 of one chain's (in one chain fp32 layers were 1.3 % further from 64 bits than
-//     with the vector ALU's fused chain; two encoder layers of 1 728 rows 672.5 us with one, 673.1 with two).
+//     with the vector ALU's fused chain; two encoder layers of 1 728 rows 672.5 us with one, 673.1 with two); where wavefronts
+//     share k there are two such sums for each of them (24 drawn fp32 cases: 0.85 of the error of two).
 //   * Weights are the MFMA's first operand, in a permuted row order, so that a lane ends up with 16 consecutive columns
 //     of one row of C: the epilogue reads residuals and writes results straight from the accumulators in 16-byte pieces.
 //     Accumulators start at the bias.
@@ -35,7 +36,8 @@
 //   756 rows    output projection and FFN2 together -, 19.7, 18.7
 //   141 rows    QKV -, 6.0, 5.0;  output projection -, 5.6, 4.2
 //   7 rows      QKV -, 5.5, 4.4;  output projection -, 5.4, 4.3;  FFN1 -, 6.6, 5.2
-// fp32 (before: products on the vector ALU): 1 728 rows of eight tenants, two encoder layers with their attention: 1.28 -> 0.67 ms.
+// fp32: 1 728 rows of eight tenants, two encoder layers with their attention: products on the vector ALU 1.28 ms, 64 x 64 tiles
+// 0.67, now 0.62;  128 rows of four tenants, an FFN block of d = 64 25.3 us, now 21.3.
 #include "hmi_kernels.h"
 
 #include "gelu.h"
@@ -92,18 +94,18 @@ __device__ __forceinline__ void mfma_chunk(const u32x4& w, const u32x4& x, f32x1
 // 16 bytes of residual (four columns, fp32 or bf16) as they are loaded, and added.
 union Resid { f32x4 f; u32x2 h; };
 
-// BM x BN: the tile; WM x WN consumers; a stage is U lines of k; STAGES of them in the ring; NP producers.  The epilogue is a
+// BM x BN: the tile; WM x WN consumers, KH sets of them that share k; a stage is U lines of k; STAGES of them in the ring; NP producers.  The epilogue is a
 // parameter too: small launches feel its instructions (as a run-time choice the compiler evaluated GELU for all of them, 0.8 us).
-template <bool BF16, int BM, int BN, int WM, int WN, int U, int STAGES, int NP, int EPI>
-__global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs g, Route rt, int total, int tiles_per_entry, int xcd_rows) {
-  constexpr int NW = WM * WN;
+template <bool BF16, int BM, int BN, int WM, int WN, int KH, int U, int STAGES, int NP, int EPI>
+__global__ __launch_bounds__(64 * (WM * WN * KH + NP)) void gemm_tile_kernel(GemmArgs g, Route rt, int total, int tiles_per_entry, int xcd_rows) {
+  constexpr int NW = WM * WN * KH;
   constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
   constexpr int A_LD = BM / 8 / NP, W_LD = BN / 8 / NP;      // 1 KB copies (8 rows) per producer and line of k
   constexpr int LINE_BYTES = (BM + BN) * ROW_BYTES, STAGE_BYTES = U * LINE_BYTES;
   constexpr int ES = BF16 ? 2 : 4;
-  constexpr int KS = 4 * U;                                  // k-steps of a stage
+  constexpr int KS = 4 * U / KH;                             // k-steps of a stage for one consumer
   static_assert(U * (A_LD + W_LD) * (STAGES - 1) < 64, "vmcnt range");
-  static_assert(BF16 || U == 1, "fp32 shapes may leave half a line");
+  static_assert(U % KH == 0, "a consumer has whole lines");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   // ---- which tile.  Workgroups go to the XCDs round robin.
@@ -147,7 +149,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kbytes = g.k * ES;
   const int KT = kbytes / (U * ROW_BYTES);  // whole stages; fp32 shapes may leave half a stage (64 bytes) behind
-  const bool half_stage = !BF16 && kbytes % ROW_BYTES != 0;
+  const bool half_stage = !BF16 && U == 1 && kbytes % ROW_BYTES != 0;
 
   if (wave >= NW) {
     // ================= producers: copies only =================
@@ -215,12 +217,13 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs
       }
     };
     if (BM == 32 && pw * A_LD * 8 >= rows) produce(std::false_type{}); else produce(std::true_type{});
+    if (KH > 1) __builtin_amdgcn_s_barrier();   // (the consumers' sums)
     return;
   }
 
   // ================= consumers: products and results =================
   const int l32 = lane & 31, lh = lane >> 5;
-  const int wm = wave / WN, wn = wave % WN;
+  const int kh = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
   const int rx = wm * WTM + l32, rw = wn * WTN + perm_w(l32);
   const int fx_base = rx * ROW_BYTES + ((lh ^ swz_a(rx)) << 4);       // fragment offsets inside a line of k (k-step ks: XOR ks << 5)
   const int fw_base = BM * ROW_BYTES + rw * ROW_BYTES + ((lh ^ swz_w(rw)) << 4);
@@ -248,7 +251,10 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs
 #pragma unroll
     for (int i = 1; i < TM; ++i) acc[i][j] = acc[0][j];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) acc2[i][j] = f32x16{};
+    for (int i = 0; i < TM; ++i) {
+      acc2[i][j] = f32x16{};
+      if (kh > 0) acc[i][j] = f32x16{};
+    }
   }
   int out_row[TM];                          // where this lane's rows of the tile go in C
 #pragma unroll
@@ -264,7 +270,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs
   // (128 x 256 tiles with GELU 5.5 us for 6.8, 32 x 32 tiles 0.4 for 1.2).
   constexpr int CF = TN < 2 ? TN : 2;
   constexpr int FL = 8 * CF;                                 // lanes of a row
-  static_assert(STAGE_BYTES >= NW * 32 * CF * 128, "patches fit a stage");
+  static_assert(STAGE_BYTES >= WM * WN * 32 * CF * 128, "patches fit a stage");
   const bool staged = !BF16 || g.out_f32 || EPI == EPI_BIAS_RESID;
   const bool resid_f32 = !BF16 || g.resid_f32;
   // the residuals of the small tiles are asked for now, the large ones' when their turn comes
@@ -294,7 +300,7 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs
   int rd = 0;                               // byte offset of the slot that is read
 #define HMI_READ_FRAGS(S)                                                                          \
   {                                                                                                \
-    const unsigned char* sb_ = smem + rd + ((S) / 4) * LINE_BYTES;                                 \
+    const unsigned char* sb_ = smem + rd + (kh * (U / KH) + (S) / 4) * LINE_BYTES;                 \
     _Pragma("unroll") for (int i = 0; i < TM; ++i) fx[S][i] = *reinterpret_cast<const u32x4*>(sb_ + (fx_base ^ (((S) & 3) << 5)) + i * 32 * ROW_BYTES); \
     _Pragma("unroll") for (int j = 0; j < TN; ++j) fw[S][j] = *reinterpret_cast<const u32x4*>(sb_ + (fw_base ^ (((S) & 3) << 5)) + j * 32 * ROW_BYTES); \
   }
@@ -339,6 +345,40 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs
   }
 #undef HMI_READ_FRAGS
 #undef HMI_MULTIPLY
+  if (KH > 1) {
+    // the other sets' sums, through the slots behind the patches, added in the order of k
+    f32x4* const part = reinterpret_cast<f32x4*>(smem + rd + WM * WN * 32 * CF * 128) + (wave - WM * WN) * (TM * TN * 4) * 64 + lane;
+    static_assert(KH == 1 || STAGE_BYTES >= WM * WN * 32 * CF * 128 + (KH - 1) * WM * WN * TM * TN * 4096, "sums fit a stage");
+    if (kh > 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            f32x16 v = acc[i][j];
+            if (!BF16) v += acc2[i][j];
+            part[((i * TN + j) * 4 + q) * 64] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+          }
+    }
+    HMI_WAIT_LGKMCNT0();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (kh > 0) return;
+#pragma unroll
+    for (int o = 1; o < KH; ++o)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v = part[(o * WM * WN * TM * TN * 4 + (i * TN + j) * 4 + q) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][j][4 * q + e] += v[e];
+          }
+  }
   if (!wave_active) return;
 
   // ---- epilogue: lane (row l32, half lh) of MFMA tile (i, j) holds columns 16 lh .. 16 lh + 15 of its 32
@@ -424,13 +464,12 @@ __global__ __launch_bounds__(64 * (WM * WN + NP)) void gemm_tile_kernel(GemmArgs
 // epilogue with it takes 1.3 us, with the exact one 2.5); small ones, where it costs nothing, and odd shapes are exact.
 bool gelu_poly_fits(const GemmArgs& g) { return g.n_rows > 1024 && g.n_out % 256 == 0 && g.k >= 192; }
 
-template <bool BF16, int BM, int BN, int WM, int WN, int U, int STAGES>
+template <bool BF16, int BM, int BN, int WM, int WN, int U, int STAGES, int KH = 1, int NP = 4>
 struct Tile {
-  static constexpr int NP = 4;              // producers
   static constexpr int LDS = STAGES * U * (BM + BN) * ROW_BYTES;
   static_assert(LDS <= 163840, "LDS");
   template <int EPI>
-  static constexpr auto kernel() { return &gemm_tile_kernel<BF16, BM, BN, WM, WN, U, STAGES, NP, EPI>; }
+  static constexpr auto kernel() { return &gemm_tile_kernel<BF16, BM, BN, WM, WN, KH, U, STAGES, NP, EPI>; }
   static void allow_lds() {
     for (auto k : {kernel<EPI_BIAS>(), kernel<EPI_BIAS_GELU>(), kernel<EPI_BIAS_RELU>(), kernel<EPI_BIAS_RESID>()})
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
@@ -462,7 +501,7 @@ struct Tile {
     }
     const auto k = g.epi == EPI_BIAS ? kernel<EPI_BIAS>() : g.epi == EPI_BIAS_GELU ? kernel<EPI_BIAS_GELU>() :
                    g.epi == EPI_BIAS_RELU ? kernel<EPI_BIAS_RELU>() : kernel<EPI_BIAS_RESID>();
-    hipLaunchKernelGGL(k, dim3((unsigned)(per * kXcds)), dim3(64 * (WM * WN + NP)), LDS, s, g, rt, (int)total, per_entry(rt, list), xcd_rows);
+    hipLaunchKernelGGL(k, dim3((unsigned)(per * kXcds)), dim3(64 * (WM * WN * KH + NP)), LDS, s, g, rt, (int)total, per_entry(rt, list), xcd_rows);
   }
 };
 typedef Tile<true, 64, 64, 2, 2, 1, 5> TileS;        // 80 KB of LDS: two workgroups per compute unit
@@ -473,11 +512,13 @@ typedef Tile<true, 128, 64, 2, 2, 1, 3> TileM;       // 72 KB: two
 typedef Tile<true, 128, 64, 2, 2, 2, 3> TileM2;      // 144 KB: one
 typedef Tile<true, 128, 128, 2, 2, 1, 3> TileL;      // 96 KB: one
 typedef Tile<true, 128, 256, 2, 2, 1, 3> TileXL;     // 144 KB: one
-typedef Tile<false, 64, 64, 2, 2, 1, 5> TileF32;
+typedef Tile<false, 64, 64, 2, 2, 1, 5> TileF32;     // 80 KB: two
+typedef Tile<false, 64, 32, 2, 1, 2, 3, 2> TileF32H;    // 72 KB: two
+typedef Tile<false, 32, 32, 1, 1, 4, 3, 4> TileF32Q;    // 96 KB: one
 }  // namespace
 
 void init_gemm_tile_kernels() {
-  TileS::allow_lds(); TileS2::allow_lds(); TileT2::allow_lds(); TileU2::allow_lds(); TileM::allow_lds(); TileM2::allow_lds(); TileL::allow_lds(); TileXL::allow_lds(); TileF32::allow_lds();
+  TileS::allow_lds(); TileS2::allow_lds(); TileT2::allow_lds(); TileU2::allow_lds(); TileM::allow_lds(); TileM2::allow_lds(); TileL::allow_lds(); TileXL::allow_lds(); TileF32::allow_lds(); TileF32H::allow_lds(); TileF32Q::allow_lds();
 }
 
 // Which kernel a launch gets.
@@ -545,8 +586,19 @@ void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
   }
 }
 
+// fp32 launches are bound by the matrix instructions, so what counts is how evenly their tiles meet the compute units, and in
+// small launches how long one wavefront's k is.  32 x 32 tiles with k in four parts, 64 x 32 with k in two, or 64 x 64: the first
+// that is a round; past that the smaller of the two rounds counted in half tiles, of which those of the 64 x 32 tiles, which copy
+// half as much again for a product, take 1.12 times as long.  Measured, us: 1 728 rows of eight tenants, 64 x 64 and 64 x 32: 768
+// columns, k = 768 and 3072 together 153, 136; 2 304 columns 78.5, 81.5; 3 072 columns with GELU 99, 116.
 void launch_gemm_f32(const GemmArgs& g, const Route& rt, hipStream_t s) {
   if (g.n_rows <= 0) return;
+  const int n_cu = rt.n_cu >= kXcds ? rt.n_cu : 256;
+  if (g.k % 128 == 0 && TileF32Q::tiles(g, rt, 0) <= n_cu) return TileF32Q::launch(g, rt, 0, s);
+  if (g.k % 64 == 0) {
+    const long long whole = (TileF32::tiles(g, rt, 0) + n_cu - 1) / n_cu * 2, half = (TileF32H::tiles(g, rt, 0) + n_cu - 1) / n_cu;
+    if (half == 1 || 112 * half < 100 * whole) return TileF32H::launch(g, rt, 0, s);
+  }
   TileF32::launch(g, rt, 0, s);
 }
 

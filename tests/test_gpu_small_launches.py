@@ -32,3 +32,15 @@ def test_a_tenants_own_weights(hmi, block, heads, d, f, tenants, requests, lo, h
     wl = small(block, "bf16", d_model=d, d_ff=f, n_heads=heads * d // 64, n_layers=1, n_tenants=tenants, hbm_slots=tenants,
                n_requests=requests, seq_min=lo, seq_max=hi)
     run_case(hmi, wl, sample=sorted({0, requests // 2, requests - 1}))
+
+
+@pytest.mark.parametrize("d,f,tenants,requests,lo,hi", [
+    (64, 128, 1, 1, 1, 1), (64, 192, 3, 3, 31, 33), (128, 512, 2, 4, 64, 65), (192, 768, 2, 3, 40, 70),     # k = 64, 128, 192
+    (320, 1280, 1, 2, 33, 33), (512, 2048, 3, 5, 20, 90), (768, 3072, 1, 1, 1, 1), (768, 3072, 2, 3, 60, 130),
+    (512, 2048, 4, 40, 100, 128), (768, 3072, 5, 30, 64, 64), (768, 3072, 2, 90, 65, 65),                   # several rounds
+])
+def test_fp32_tiles(hmi, d, f, tenants, requests, lo, hi):
+    """32 x 32 with k in four parts, 64 x 32 with k in two, 64 x 64: single rows, one row past a tile, one and several rounds."""
+    wl = small(synth.BLOCK_FFN, "f32", d_model=d, d_ff=f, n_layers=1, n_tenants=tenants, hbm_slots=tenants, n_requests=requests,
+               seq_min=lo, seq_max=hi)
+    run_case(hmi, wl, sample=sorted({0, requests // 2, requests - 1}))
