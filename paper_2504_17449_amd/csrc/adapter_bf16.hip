@@ -109,7 +109,7 @@ template <> struct Four<true> { typedef f32x4 type; };
 __device__ __forceinline__ f32x4 to_f32(u16x4 h) { return f32x4{bf2f(h[0]), bf2f(h[1]), bf2f(h[2]), bf2f(h[3])}; }
 __device__ __forceinline__ f32x4 to_f32(f32x4 v) { return v; }
 
-template <int NV>
+template <int NV, bool ONE>
 struct Shape {
   static constexpr int CH = NV * 32;          // 16-byte chunks of a row (d = 256 NV)
   static constexpr int ROWB = CH * 16;
@@ -117,11 +117,11 @@ struct Shape {
   static constexpr int KS = NV * 16;          // 16-wide k-steps over d
   static constexpr int KSW = KS / 4;          // ... per wavefront of the down-projection
   static constexpr int NJ = RT * CH / 256;    // copies (stores) per lane and unit
-  static constexpr int OFF_PART = 2 * BUF;
+  static constexpr int OFF_PART = (ONE ? 1 : 2) * BUF;
   static constexpr int OFF_MID = OFF_PART + PART_BYTES;
   static constexpr int OFF_RS = OFF_MID + MID_BYTES;
-  static constexpr int OFF_DESC = OFF_RS + RS_BYTES;
-  static constexpr int OFF_NORM = OFF_DESC + DESC_BYTES;   // LayerNorm gain, then shift, as stored
+  static constexpr int OFF_DESC = OFF_RS + (ONE ? RT * 4 : RS_BYTES);
+  static constexpr int OFF_NORM = OFF_DESC + (ONE ? 0 : DESC_BYTES);   // LayerNorm gain, then shift, as stored
   static constexpr int OFF_BIAS = OFF_NORM + 2 * ROWB;     // the tenant's up-projection bias
   static constexpr int LDS = OFF_BIAS + ROWB;
   static_assert(LDS <= 163840, "LDS");
@@ -140,7 +140,7 @@ struct Shape {
 template <int NV, bool ONCE, int OUT, bool ONE>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void adapter_bf16_kernel(AdapterArgs a, Route rt) {
-  using S = Shape<NV>;
+  using S = Shape<NV, ONE>;
   constexpr bool LN = OUT != OUT_STREAM;
   typedef typename Four<OUT == LN_RESID_F32>::type four_t;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -208,14 +208,17 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   // A lane's NJ = 4 NV chunks of a unit: chunk jj * 256 + t8 with t8 = tid mod 256.  256 NV
   // chunks are exactly 8 rows, so chunk (NV g + r3) * 256 + t8 lies in row 8 g + ro[r3] at a
   // row position that does not depend on g; sw[r3] is that position swizzled for g even.
-  const int t8 = tid & 255;
-  int ro[NV], sw[NV];
+  int t8, ro[NV], sw[NV];
+  auto place = [&]() {
+    t8 = tid & 255;
 #pragma unroll
-  for (int r3 = 0; r3 < NV; ++r3) {
-    const int c = r3 * 256 + t8;
-    ro[r3] = c / S::CH;
-    sw[r3] = ((c % S::CH) ^ ro[r3]) << 4;
-  }
+    for (int r3 = 0; r3 < NV; ++r3) {
+      const int c = r3 * 256 + t8;
+      ro[r3] = c / S::CH;
+      sw[r3] = ((c % S::CH) ^ ro[r3]) << 4;
+    }
+  };
+  place();
 #define HMI_ISSUE_COPIES(UI, B)                                                                    \
   {                                                                                                \
     _Pragma("unroll") for (int g_ = 0; g_ < 4; ++g_)                                               \
@@ -248,14 +251,23 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   // early as may be, in the order in which they are needed (loads return in order): Down, the first unit's rows (through
   // registers, so that nothing behind them has to be waited for with them), its residual rows, Up.
   const int my_src = rt.row_src[first_row + min(lane & 31, first_rows - 1)];
+  auto row_of = [&](int idx) {             // of unit idx / 32: surplus rows of a short unit repeat its last row
+    const int u = idx >> 5, r = idx & 31;
+    return rt.row_src[desc[u * 4] + min(r, desc[u * 4 + 1] - 1)];
+  };
+  int src = 0;                             // row tid of the workgroup's units
+  if (!ONE) {
+    HMI_BARRIER();                         // desc
+    if (tid < m * RT) src = row_of(tid);
+  }
   HMI_LOAD_WD(cur_slot)
   __builtin_amdgcn_sched_barrier(0);
   u32x4 x0[2 * NV];
 #pragma unroll
   for (int jj = 0; jj < 2 * NV; ++jj) {
     const int c = jj * NTH + tid, row = c / S::CH;
-    const int src = __shfl(my_src, row, 64);
-    if (row < first_rows) x0[jj] = *reinterpret_cast<const u32x4*>(X + (size_t)src * S::ROWB + (c % S::CH) * 16);
+    const int from = __shfl(my_src, row, 64);
+    if (row < first_rows) x0[jj] = *reinterpret_cast<const u32x4*>(X + (size_t)from * S::ROWB + (c % S::CH) * 16);
   }
   u32x4 norm = {};
   if (LN && tid < 2 * S::CH) norm = reinterpret_cast<const u32x4*>(tid < S::CH ? a.ln_g : a.ln_b)[tid < S::CH ? tid : tid - S::CH];
@@ -283,7 +295,8 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   HMI_LOAD_WU(cur_slot)
   __builtin_amdgcn_sched_barrier(0);
   // the units' row numbers and the LayerNorm's parameters to LDS, then the first unit's rows
-  if (wave == 0 && lane < RT) rs[lane] = my_src;
+  if (ONE && wave == 0 && lane < RT) rs[lane] = my_src;
+  if (!ONE && tid < m * RT) rs[tid] = src;
   if (LN && tid < 2 * S::CH) reinterpret_cast<u32x4*>(smem + S::OFF_NORM)[tid] = norm;
 #pragma unroll
   for (int jj = 0; jj < 2 * NV; ++jj) {
@@ -292,6 +305,10 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   }
   HMI_BARRIER();
   if (!ONE) {
+    if (wave < 4 && m > 1) HMI_ISSUE_COPIES(1, 1)
+    if (m * RT > NTH) {
+      for (int idx = NTH + tid; idx < m * RT; idx += NTH) rs[idx] = row_of(idx);   // read behind the loop's first barrier at the earliest
+    }
 #pragma unroll
     for (int s = 0; s < S::KSW; ++s) asm volatile("" :: "v"(wd[s]));       // (waited for here)
 #pragma unroll
@@ -300,14 +317,6 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
       for (int s = 0; s < 4; ++s) asm volatile("" :: "v"(wu[c][s]));
     asm volatile("" :: "v"(bu), "v"(bd));
   }
-  if (m > 1) {
-    for (int idx = RT + tid; idx < m * RT; idx += NTH) {   // surplus rows of a short unit repeat its last row
-      const int u = idx >> 5, r = idx & 31;
-      rs[idx] = rt.row_src[desc[u * 4] + min(r, desc[u * 4 + 1] - 1)];
-    }
-    HMI_BARRIER();
-    if (wave < 4) HMI_ISSUE_COPIES(1, 1)
-  }
 
   for (int i = 0; i < m; ++i) {
     const int b = i & 1;
@@ -315,6 +324,7 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
     if (LN) {   // the addresses made from the thread's number are made anew for each unit: there are no registers to keep them in
       asm volatile("" : "+v"(tid));
       lane = tid & 63; j = lane & 31; h = lane >> 5;
+      place();
     }
     const int rows = ONE ? first_rows : desc[i * 4 + 1];
     // the tenant of the next unit, if it is another one: its matrices replace this unit's as
@@ -495,7 +505,6 @@ decltype(&adapter_bf16_kernel<NV, false, OUT_STREAM, ONE>) pick(const AdapterArg
 
 template <int NV>
 void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
-  using S = Shape<NV>;
   const int n_cu = rt.n_cu >= 1 ? rt.n_cu : 256;
   if (a.n_tiles128 <= 0) return;
   AdapterArgs b = a;
@@ -504,11 +513,11 @@ void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   // to 0.49 MB each, 8.3 in units of 8), and they are counted exactly (a decode step of 256 rows, the most popular tenant with 34
   // of them: 14.5 us with four units for each 128-row tile, most of them empty, 12.7 with these).
   if (a.n_segs <= MAX_SEGS)
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 3; ++k)   // (two workgroups a compute unit, where rows are narrow enough, load the matrices twice: 8 586 rows of d = 256 5 % slower)
       if (a.units[k] <= n_cu) {
         b.unit_shift = 3 + k;
         b.unit_rows = 8 << k;
-        hipLaunchKernelGGL((pick<NV, true>(a)), dim3(a.units[k]), dim3(NTH), S::LDS, s, b, rt);
+        hipLaunchKernelGGL((pick<NV, true>(a)), dim3(a.units[k]), dim3(NTH), (Shape<NV, true>::LDS), s, b, rt);
         return;
       }
   const long long U = (long long)a.n_tiles128 * 4;
@@ -517,7 +526,7 @@ void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   if (grid < need) grid = need;                                       //     more units than it can list
   b.units_each = (int)(U / grid);
   b.units_more = (int)(U % grid);
-  hipLaunchKernelGGL((pick<NV, false>(a)), dim3((unsigned)grid), dim3(NTH), S::LDS, s, b, rt);
+  hipLaunchKernelGGL((pick<NV, false>(a)), dim3((unsigned)grid), dim3(NTH), (Shape<NV, false>::LDS), s, b, rt);
 }
 
 template <int NV, bool ONE>
@@ -525,7 +534,7 @@ void allow_lds() {
   for (auto kern : {adapter_bf16_kernel<NV, false, OUT_STREAM, ONE>, adapter_bf16_kernel<NV, false, LN_RESID_BF16, ONE>,
                     adapter_bf16_kernel<NV, true, LN_RESID_BF16, ONE>, adapter_bf16_kernel<NV, false, LN_RESID_F32, ONE>,
                     adapter_bf16_kernel<NV, true, LN_RESID_F32, ONE>})
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Shape<NV>::LDS);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, Shape<NV, ONE>::LDS);
 }
 
 }  // namespace
