@@ -183,6 +183,7 @@ int32_t hmi_queue_run(hmi_queue_t* q, int64_t* batch, int32_t* n_requests) {
   const int L = q->cfg.n_layers;
   hipStream_t s = hmi_internal_compute_stream(q->pool);
   if (hipSetDevice(q->cfg.device) != hipSuccess) return qfail(q, HMI_ERR_DEVICE, "hipSetDevice failed");
+  hmi_internal_note_idle(q->pool);
   hipLaunchKernelGGL(gather_rows_kernel, dim3(b->n_req), dim3(256), 0, s, b->src, b->tok_off, b->x, (int)q->row_bytes);
   if (hipEventRecord(b->gathered, s) != hipSuccess || hipGetLastError() != hipSuccess)
     return qfail(q, HMI_ERR_DEVICE, "gathering the batch's rows failed");

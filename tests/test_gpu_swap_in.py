@@ -1,0 +1,59 @@
+"""Small tenants brought in while the device is idle: by kernels that read the pinned images, more of them than one launch lists, into
+slots that others have lost, and then again behind calls that are still running; results as of a pool where all are resident."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+D, RANK, TENANTS, SLOTS = 256, 64, 600, 300
+
+
+def _pool(hmi, tier, block, layers, weights, shared):
+    pool = hmi.Pool(block=block, dtype=hmi.HMI_BF16, d_model=D, d_ff=512, n_heads=D // 64, n_layers=layers, max_tenants=TENANTS,
+                    hbm_slots=SLOTS if tier else TENANTS, host_tier=tier, max_requests=SLOTS, max_tokens=4 * SLOTS, ln_eps=1e-12,
+                    compute_stream=torch.cuda.current_stream().cuda_stream, adapter_rank=RANK, max_classes=0)
+    for layer in range(layers):
+        pool.load_shared(layer, shared[layer])
+    for t in range(TENANTS):
+        for layer in range(layers):
+            pool.load_tenant(t, layer, weights[(t * layers + layer) % len(weights)])
+    return pool
+
+
+@pytest.mark.parametrize("layers", [2, 3])
+def test_tenants_brought_in_on_an_idle_device(hmi, layers):
+    rng = np.random.default_rng(layers)
+
+    def bf16(*shape, scale=0.05, mean=0.0):
+        return (torch.from_numpy(rng.standard_normal(shape) * scale + mean)).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+
+    weights = [[bf16(RANK, D, scale=0.2), bf16(RANK), bf16(D, RANK, scale=0.2), bf16(D)] for _ in range(37)]
+    shared = [[bf16(3 * D, D), bf16(3 * D), bf16(D, D), bf16(D), bf16(D, mean=1.0), bf16(D), bf16(512, D), bf16(512), bf16(D, 512), bf16(D),
+               bf16(D, mean=1.0), bf16(D)] for _ in range(layers)]
+    tiered = _pool(hmi, True, hmi.HMI_BLOCK_ENC_ADAPTER, layers, weights, shared)
+    resident = _pool(hmi, False, hmi.HMI_BLOCK_ENC_ADAPTER, layers, weights, shared)
+    try:
+        before = tiered.stats()
+        held = set(range(SLOTS))                 # tenants take free slots in the order in which they are loaded
+        missing = 0
+        for step, idle in enumerate([True, True, False, False, True]):
+            ids = rng.choice(TENANTS, size=SLOTS - 1 if step != 1 else 3, replace=False).astype(np.int32)
+            if step == 0:
+                ids[:] = np.arange(SLOTS, 2 * SLOTS - 1)          # 299 tenants that are not there: two launches
+                missing = len(set(ids.tolist()) - held)
+            lens = rng.integers(1, 4, size=len(ids)).astype(np.int32)
+            x = torch.from_numpy(rng.standard_normal((int(lens.sum()), D))).to(torch.bfloat16).cuda()
+            y, want = torch.empty_like(x), torch.empty_like(x)
+            resident.stack_forward(0, layers, x, want, ids, lens)
+            if idle:
+                torch.cuda.synchronize()
+            tiered.stack_forward(0, layers, x, y, ids, lens)
+            assert torch.equal(y, want), step
+            if step == 0:
+                after = tiered.stats()
+                assert after["misses"] - before["misses"] == missing == SLOTS - 1
+                assert after["bytes_h2d"] - before["bytes_h2d"] == missing * layers * tiered.image_bytes
+    finally:
+        tiered.close()
+        resident.close()
