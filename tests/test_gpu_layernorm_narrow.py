@@ -1,0 +1,18 @@
+"""LayerNorm of rows that are no multiple of 256 wide: a template per width of 64, 128, 192 and 320 columns, the general form for the
+others (384), over rows that leave wavefronts of the last workgroup without one, with the tenants' own and with shared parameters."""
+import pytest
+
+import synth
+from tests.test_gpu_parity import run_case, small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 320, 384])
+@pytest.mark.parametrize("block,dtype", [(synth.BLOCK_ENC_POSTLN, "f32"), (synth.BLOCK_ENC_POSTLN, "bf16"),
+                                         (synth.BLOCK_DEC_PRELN, "bf16"), (synth.BLOCK_DEC_ADAPTER, "bf16")])
+@pytest.mark.parametrize("tenants,requests,lo,hi", [(1, 1, 1, 1), (3, 3, 1, 3), (40, 60, 2, 5)])
+def test_narrow_rows(hmi, d, block, dtype, tenants, requests, lo, hi):
+    wl = small(block, dtype, d_model=d, d_ff=4 * d, n_heads=d // 64, n_layers=1, n_tenants=tenants, hbm_slots=tenants,
+               n_requests=requests, seq_min=lo, seq_max=hi)
+    run_case(hmi, wl, sample=sorted({0, requests // 2, requests - 1}))
