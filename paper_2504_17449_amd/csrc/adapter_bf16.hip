@@ -512,9 +512,11 @@ void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   // through one of them, besides its matrices' (two requests of 101 and 40 rows with LayerNorm: 12.4 us in units of 32 rows, up
   // to 0.49 MB each, 8.3 in units of 8), and they are counted exactly (a decode step of 256 rows, the most popular tenant with 34
   // of them: 14.5 us with four units for each 128-row tile, most of them empty, 12.7 with these).
+  // Without LayerNorm a unit's own rows are little work and units of 16 rows only read the matrices twice: where 8-row units are
+  // too many, units of 32 (2 789 rows of d = 512, 15.3 us in units of 16, 14.1 in units of 32; 3 473 of d = 256 12.3 and 11.7).
   if (a.n_segs <= MAX_SEGS)
     for (int k = 0; k < 3; ++k)   // (two workgroups a compute unit, where rows are narrow enough, load the matrices twice: 8 586 rows of d = 256 5 % slower)
-      if (a.units[k] <= n_cu) {
+      if (a.units[k] <= n_cu && !(a.stream_out && k == 1)) {
         b.unit_shift = 3 + k;
         b.unit_rows = 8 << k;
         hipLaunchKernelGGL((pick<NV, true>(a)), dim3(a.units[k]), dim3(NTH), (Shape<NV, true>::LDS), s, b, rt);
