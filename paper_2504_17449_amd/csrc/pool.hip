@@ -73,6 +73,15 @@ struct EventRing {
     uint64_t oldest = newest >= (uint64_t)kRing ? newest - kRing + 1 : 1;
     return ev[std::max(seq, oldest) % kRing];
   }
+  // The host waits for sequence seq (0: nothing to wait for; one whose record is still to come, because a call failed in front
+  // of it, gets it now).
+  hipError_t host_wait(uint64_t seq, hipStream_t s) {
+    if (seq == 0) return hipSuccess;
+    if (seq >= next) record(s);
+    if (hipEventSynchronize(at_least(seq)) == hipSuccess) return hipSuccess;
+    (void)hipGetLastError();              // an event that belongs to a captured call: all of the stream, then
+    return hipStreamSynchronize(s);
+  }
 };
 
 struct TensorLoc { size_t off, bytes; };
@@ -132,6 +141,8 @@ struct hmi_pool {
   std::vector<int32_t> free_slots;
   uint64_t clock = 0;
   std::vector<char*> host_img;       // [tenant] pinned, all layers (host tier)
+  std::vector<uint64_t> img_copy;    // [tenant] copy sequence and
+  std::vector<uint64_t> img_fwd;     // ... forward sequence that last read the tenant's image; they outlive its slot
   std::vector<int32_t> alias_of;     // [tenant] the tenant whose pinned image this one shares (-1: its own)
   std::vector<int32_t> alias_count;  // [tenant] tenants that share this one's image
   std::vector<char*> arenas;
@@ -400,7 +411,7 @@ int32_t enqueue_swap_in(hmi_pool* p, int tenant, int slot, int layer) {
                             hipMemcpyHostToDevice, p->copy));
   if (whole) for (int l = 0; l < L; ++l) p->slot_valid[(size_t)slot * L + l] = 1;
   else p->slot_valid[(size_t)slot * L + layer] = 1;
-  p->slot_copy[slot] = p->copy_done.next;  // the record() that follows this batch of copies
+  p->slot_copy[slot] = p->img_copy[tenant] = p->copy_done.next;  // the record() that follows this batch of copies
   p->bytes_h2d += (int64_t)bytes;
   return HMI_OK;
 }
@@ -458,11 +469,11 @@ int32_t swap_in_now(hmi_pool* p) {
     hipLaunchKernelGGL(swap_in_kernel, dim3((unsigned)std::min<long long>(chunks, 256)), dim3(256), 0, p->compute, list, n,
                        (unsigned)p->slot_stride);
   }
-  HIP_TRY(p, hipGetLastError());
-  // a later copy into one of these slots waits for this, also if the call ends early
+  // a later copy into one of these slots waits for this, and so does whoever writes one of these images, also if the call ends early
   const uint64_t seq = p->fwd_done.record(p->compute);
+  for (const auto& in : p->incoming) p->slot_fwd[in.slot] = p->img_fwd[in.tenant] = seq;
+  HIP_TRY(p, hipGetLastError());
   for (const auto& in : p->incoming) {
-    p->slot_fwd[in.slot] = seq;
     std::fill_n(p->slot_valid.begin() + (size_t)in.slot * p->cfg.n_layers, p->cfg.n_layers, 1);
     p->bytes_h2d += (int64_t)p->slot_stride;
   }
@@ -618,6 +629,8 @@ static int32_t create_impl(const hmi_pool_config_t* cfg, hmi_pool_t** out) {
   for (int s = c.hbm_slots - 1; s >= 0; --s) p->free_slots.push_back(s);
   if (c.host_tier) {
     p->host_img.assign(c.max_tenants, nullptr);
+    p->img_copy.assign(c.max_tenants, 0);
+    p->img_fwd.assign(c.max_tenants, 0);
     p->alias_of.assign(c.max_tenants, -1);
     p->alias_count.assign(c.max_tenants, 0);
   }
@@ -771,6 +784,11 @@ int32_t hmi_pool_load_tenant(hmi_pool_t* p, int32_t tenant, int32_t layer,
       // replacing weights that may be in use or in flight: drain both streams first
       HIP_TRY(p, hipStreamSynchronize(p->compute));
       HIP_TRY(p, hipStreamSynchronize(p->copy));
+    } else if (p->loaded[(size_t)tenant * L + layer]) {
+      // not in HBM (any more), but a swap-in of a call that is still under way may not have read the image yet: the tenant can
+      // have lost its slot again on the host before any of that ran
+      HIP_TRY(p, p->copy_done.host_wait(p->img_copy[tenant], p->copy));
+      HIP_TRY(p, p->fwd_done.host_wait(p->img_fwd[tenant], p->compute));
     }
     char* img = p->host_img[tenant] + (size_t)layer * p->image_bytes;
     write_image(p, img, tensors);

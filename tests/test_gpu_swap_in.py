@@ -21,16 +21,20 @@ def _pool(hmi, tier, block, layers, weights, shared):
     return pool
 
 
-@pytest.mark.parametrize("layers", [2, 3])
-def test_tenants_brought_in_on_an_idle_device(hmi, layers):
-    rng = np.random.default_rng(layers)
-
+def _weights(rng, layers):
     def bf16(*shape, scale=0.05, mean=0.0):
         return (torch.from_numpy(rng.standard_normal(shape) * scale + mean)).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
 
     weights = [[bf16(RANK, D, scale=0.2), bf16(RANK), bf16(D, RANK, scale=0.2), bf16(D)] for _ in range(37)]
     shared = [[bf16(3 * D, D), bf16(3 * D), bf16(D, D), bf16(D), bf16(D, mean=1.0), bf16(D), bf16(512, D), bf16(512), bf16(D, 512), bf16(D),
                bf16(D, mean=1.0), bf16(D)] for _ in range(layers)]
+    return weights, shared
+
+
+@pytest.mark.parametrize("layers", [2, 3])
+def test_tenants_brought_in_on_an_idle_device(hmi, layers):
+    rng = np.random.default_rng(layers)
+    weights, shared = _weights(rng, layers)
     tiered = _pool(hmi, True, hmi.HMI_BLOCK_ENC_ADAPTER, layers, weights, shared)
     resident = _pool(hmi, False, hmi.HMI_BLOCK_ENC_ADAPTER, layers, weights, shared)
     try:
@@ -54,6 +58,50 @@ def test_tenants_brought_in_on_an_idle_device(hmi, layers):
                 after = tiered.stats()
                 assert after["misses"] - before["misses"] == missing == SLOTS - 1
                 assert after["bytes_h2d"] - before["bytes_h2d"] == missing * layers * tiered.image_bytes
+    finally:
+        tiered.close()
+        resident.close()
+
+
+@pytest.mark.parametrize("idle", [True, False])
+def test_a_tenant_loaded_again_while_its_image_is_still_being_read(hmi, idle):
+    """A call brings tenants in, the next one takes their slots away, and one of them is then loaded again, with nothing
+    synchronised: the first call has its old weights all the same, whether a kernel (idle device) or the copy engine, which waits
+    for the slots' readers behind some 20 ms of other work, has yet to read them."""
+    layers, rng = 3, np.random.default_rng(5)
+    weights, shared = _weights(rng, layers)
+    tiered = _pool(hmi, True, hmi.HMI_BLOCK_ENC_ADAPTER, layers, weights, shared)
+    resident = _pool(hmi, False, hmi.HMI_BLOCK_ENC_ADAPTER, layers, weights, shared)
+    try:
+        missing, there = np.arange(SLOTS, 2 * SLOTS, dtype=np.int32), np.arange(SLOTS, dtype=np.int32)
+        again = missing[-5:]
+        lens = rng.integers(1, 4, size=SLOTS).astype(np.int32)
+        x = torch.from_numpy(rng.standard_normal((int(lens.sum()), D))).to(torch.bfloat16).cuda()
+        old, new, y, spare, y_new = (torch.empty_like(x) for _ in range(5))
+        resident.stack_forward(0, layers, x, old, missing, lens)
+        torch.cuda.synchronize()
+        for t in again:
+            for layer in range(layers):
+                resident.load_tenant(int(t), layer, weights[(int(t) * layers + layer + 11) % len(weights)])
+        resident.stack_forward(0, layers, x, new, missing, lens)
+        big = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+        tiered.stack_forward(0, layers, x, spare, there, lens)
+        torch.cuda.synchronize()
+        if not idle:
+            for _ in range(20):
+                torch.mm(big, big)
+            tiered.stack_forward(0, layers, x, spare, there, lens)
+        tiered.stack_forward(0, layers, x, y, missing, lens)
+        tiered.stack_forward(0, layers, x, spare, there, lens)
+        for t in again:
+            for layer in range(layers):
+                tiered.load_tenant(int(t), layer, weights[(int(t) * layers + layer + 11) % len(weights)])
+        tiered.stack_forward(0, layers, x, y_new, missing, lens)
+        torch.cuda.synchronize()
+        assert tiered.stats()["evictions"] >= 3 * SLOTS
+        assert not torch.equal(old, new)
+        assert torch.equal(y, old)
+        assert torch.equal(y_new, new)
     finally:
         tiered.close()
         resident.close()
