@@ -18,7 +18,6 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <utility>
 #include <vector>
 
 using namespace hmi;
@@ -209,10 +208,9 @@ struct hmi_pool {
   std::vector<int32_t> ones;        // [max_requests] the sequence lengths of a decode step
   struct Incoming { int tenant, slot; };
   std::vector<Incoming> incoming;   // tenants a call brings in by kernels, capacity max_requests
-  bool noted_idle = false;          // the queue found the compute stream idle before it put the next call's gather there
   uint32_t epoch = 0;
 
-  int64_t hits = 0, misses = 0, bytes_h2d = 0, evictions = 0;
+  int64_t hits = 0, misses = 0, bytes_h2d = 0, evictions = 0, brought_by_kernel = 0;
 
   // optional per-kernel timing (hipEvents around each launch on the compute stream)
   bool profiling = false;
@@ -476,6 +474,7 @@ int32_t swap_in_now(hmi_pool* p) {
   for (const auto& in : p->incoming) {
     std::fill_n(p->slot_valid.begin() + (size_t)in.slot * p->cfg.n_layers, p->cfg.n_layers, 1);
     p->bytes_h2d += (int64_t)p->slot_stride;
+    ++p->brought_by_kernel;
   }
   return HMI_OK;
 }
@@ -989,9 +988,10 @@ enum { KV_NONE = 0, KV_PREFILL = 1, KV_DECODE = 2 };
 // The forward of layers [layer_begin, layer_end) over one batch.  kv: KV_PREFILL also stores every
 // row's key and value in the request's cache line seq_slots[r] (from position 0); KV_DECODE takes
 // one row per request (seq_lens == nullptr), appends it to the line and attends over the line.
+// was_idle: the caller found the compute stream idle just now, before it put work of its own there that this call continues.
 static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_end, const void* x, void* y,
                             const int32_t* tenant_ids, const int32_t* seq_lens, int32_t R, int kv,
-                            const int32_t* seq_slots, bool y_f32 = false) {
+                            const int32_t* seq_slots, bool y_f32 = false, bool was_idle = false) {
   if (!p) return HMI_ERR_ARG;
   if (R == 0) return HMI_OK;
   if (y_f32 && p->cfg.block == HMI_BLOCK_ADAPTER && p->adapter_fused)
@@ -1052,14 +1052,13 @@ static int32_t forward_impl(hmi_pool_t* p, int32_t layer_begin, int32_t layer_en
     const int s = p->slot_of_tenant[t];
     if (s >= 0) p->slot_stamp[s] = now;
   }
-  const bool noted_idle = std::exchange(p->noted_idle, false);
-  // Brings `layer` of every tenant of the batch into HBM (copy stream); returns the copy
-  // sequence the compute stream has to wait for before reading those weights.
+  // Brings `layer` of every tenant of the batch into HBM (by the copy engine or, small tenants on an idle device, by kernels
+  // of the compute stream); returns the copy sequence the compute stream has to wait for before reading those weights.
   auto make_resident = [&](int layer, bool count, uint64_t* need_out) -> int32_t {
     bool copied = false;
     uint64_t need = 0;
     p->incoming.clear();
-    int idle = noted_idle ? 1 : -1;   // asked at the first tenant that is not there
+    int idle = was_idle ? 1 : -1;     // else asked at the first tenant that is not there
     for (int t : p->distinct) {
       int s = p->slot_of_tenant[t];
       const bool hit = s >= 0 && p->slot_valid[(size_t)s * L + layer];
@@ -1538,7 +1537,11 @@ int32_t hmi_pool_profile_read(hmi_pool_t* p, double* ms, int64_t* launches) {
 
 const hmi_pool_config_t* hmi_internal_config(const hmi_pool_t* p) { return &p->cfg; }
 hipStream_t hmi_internal_compute_stream(const hmi_pool_t* p) { return p->compute; }
-void hmi_internal_note_idle(hmi_pool_t* p) { p->noted_idle = p->cfg.host_tier && compute_idle(p); }
+bool hmi_internal_idle(hmi_pool_t* p) { return p->cfg.host_tier && compute_idle(p); }
+int32_t hmi_internal_stack_forward(hmi_pool_t* p, const void* x, void* y, const int32_t* tenant_ids, const int32_t* seq_lens, int32_t R,
+                                   bool was_idle) {
+  return forward_impl(p, 0, p->cfg.n_layers, x, y, tenant_ids, seq_lens, R, KV_NONE, nullptr, false, was_idle);
+}
 bool hmi_internal_tenant_ready(const hmi_pool_t* p, int32_t tenant) {
   if (tenant < 0 || tenant >= p->cfg.max_tenants) return false;
   for (int l = 0; l < p->cfg.n_layers; ++l)
@@ -1547,6 +1550,9 @@ bool hmi_internal_tenant_ready(const hmi_pool_t* p, int32_t tenant) {
 }
 
 extern "C" {
+
+// For the tests: tenants that calls have brought in by kernels of the compute stream.
+int64_t hmi_internal_brought_by_kernel(const hmi_pool_t* p) { return p ? p->brought_by_kernel : 0; }
 
 int64_t hmi_pool_image_bytes(const hmi_pool_t* p) { return p ? (int64_t)p->image_bytes : 0; }
 

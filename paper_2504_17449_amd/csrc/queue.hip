@@ -183,13 +183,14 @@ int32_t hmi_queue_run(hmi_queue_t* q, int64_t* batch, int32_t* n_requests) {
   const int L = q->cfg.n_layers;
   hipStream_t s = hmi_internal_compute_stream(q->pool);
   if (hipSetDevice(q->cfg.device) != hipSuccess) return qfail(q, HMI_ERR_DEVICE, "hipSetDevice failed");
-  hmi_internal_note_idle(q->pool);
+  const bool was_idle = hmi_internal_idle(q->pool);
   hipLaunchKernelGGL(gather_rows_kernel, dim3(b->n_req), dim3(256), 0, s, b->src, b->tok_off, b->x, (int)q->row_bytes);
   if (hipEventRecord(b->gathered, s) != hipSuccess || hipGetLastError() != hipSuccess)
     return qfail(q, HMI_ERR_DEVICE, "gathering the batch's rows failed");
-  int32_t rc = hmi_stack_forward(q->pool, 0, L, b->x, b->y, b->ids.data(), b->lens.data(), b->n_req);
+  int32_t rc = hmi_internal_stack_forward(q->pool, b->x, b->y, b->ids.data(), b->lens.data(), b->n_req, was_idle);
   if (rc != HMI_OK) {
-    // cannot happen for what push admitted, short of a device error: give the batch up rather than block the queue
+    // short of a device error only where push cannot look (shared parameters that were never loaded): give the batch up rather
+    // than block the queue
     snprintf(q->err, sizeof(q->err), "batch %lld failed: %s", (long long)b->seq, hmi_last_error(q->pool));
     b->state = EMPTY;
     ++q->next_run;

@@ -1,5 +1,7 @@
 """Small tenants brought in while the device is idle: by kernels that read the pinned images, more of them than one launch lists, into
 slots that others have lost, and then again behind calls that are still running; results as of a pool where all are resident."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -105,3 +107,47 @@ def test_a_tenant_loaded_again_while_its_image_is_still_being_read(hmi, idle):
     finally:
         tiered.close()
         resident.close()
+
+
+def _brought_by_kernel(hmi, pool):
+    fn = hmi.lib.hmi_internal_brought_by_kernel
+    fn.restype, fn.argtypes = C.c_int64, [C.c_void_p]
+    return fn(pool.h)
+
+
+def test_what_a_failed_queue_run_found_does_not_reach_the_next_call(hmi):
+    """A queue's run asks whether the device is idle in front of its gather.  Where its forward is then refused (shared layers that
+    nobody has loaded), the next call, behind other work, asks for itself: its tenants come by the copy engine."""
+    layers, rng = 2, np.random.default_rng(7)
+    weights, shared = _weights(rng, layers)
+    pool = hmi.Pool(block=hmi.HMI_BLOCK_ENC_ADAPTER, dtype=hmi.HMI_BF16, d_model=D, d_ff=512, n_heads=D // 64, n_layers=layers, max_tenants=8,
+                    hbm_slots=4, host_tier=True, max_requests=4, max_tokens=64, ln_eps=1e-12,
+                    compute_stream=torch.cuda.current_stream().cuda_stream, adapter_rank=RANK, max_classes=0)
+    queue = None
+    try:
+        for t in range(8):                       # the first four take the slots
+            for layer in range(layers):
+                pool.load_tenant(t, layer, weights[t])
+        queue = hmi.Queue(pool, 4, 64, max_waiting_batches=1)
+        x = torch.randn(4, D, device="cuda").to(torch.bfloat16)
+        y = torch.empty_like(x)
+        torch.cuda.synchronize()
+        assert queue.push(0, x) is not None
+        with pytest.raises(hmi.HmiError):
+            queue.run()
+        for layer in range(layers):
+            pool.load_shared(layer, shared[layer])
+        big = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+        torch.cuda.synchronize()
+        for _ in range(20):
+            torch.mm(big, big)
+        pool.stack_forward(0, layers, x, y, np.arange(4, 8, dtype=np.int32), np.ones(4, dtype=np.int32))
+        assert pool.stats()["misses"] == 4 and _brought_by_kernel(hmi, pool) == 0
+        torch.cuda.synchronize()
+        pool.stack_forward(0, layers, x, y, np.arange(4, dtype=np.int32), np.ones(4, dtype=np.int32))
+        assert pool.stats()["misses"] == 8 and _brought_by_kernel(hmi, pool) == 4
+        torch.cuda.synchronize()
+    finally:
+        if queue is not None:
+            queue.close()
+        pool.close()
