@@ -503,11 +503,8 @@ decltype(&adapter_bf16_kernel<NV, false, OUT_STREAM, ONE>) pick(const AdapterArg
   return a.weights_once ? adapter_bf16_kernel<NV, true, LN_RESID_BF16, ONE> : adapter_bf16_kernel<NV, false, LN_RESID_BF16, ONE>;
 }
 
-template <int NV>
-void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
-  const int n_cu = rt.n_cu >= 1 ? rt.n_cu : 256;
-  if (a.n_tiles128 <= 0) return;
-  AdapterArgs b = a;
+// log2 of the rows of the units that a launch of one unit a workgroup is cut into, or 0: the general form.
+int unit_shift(const AdapterArgs& a, int n_cu) {
   // While there is a compute unit for each, the units are as small as may be: what one costs is then the traffic of its rows
   // through one of them, besides its matrices' (two requests of 101 and 40 rows with LayerNorm: 12.4 us in units of 32 rows, up
   // to 0.49 MB each, 8.3 in units of 8), and they are counted exactly (a decode step of 256 rows, the most popular tenant with 34
@@ -516,12 +513,21 @@ void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
   // too many, units of 32 (2 789 rows of d = 512, 15.3 us in units of 16, 14.1 in units of 32; 3 473 of d = 256 12.3 and 11.7).
   if (a.n_segs <= MAX_SEGS)
     for (int k = 0; k < 3; ++k)   // (two workgroups a compute unit, where rows are narrow enough, load the matrices twice: 8 586 rows of d = 256 5 % slower)
-      if (a.units[k] <= n_cu && !(a.stream_out && k == 1)) {
-        b.unit_shift = 3 + k;
-        b.unit_rows = 8 << k;
-        hipLaunchKernelGGL((pick<NV, true>(a)), dim3(a.units[k]), dim3(NTH), (Shape<NV, true>::LDS), s, b, rt);
-        return;
-      }
+      if (a.units[k] <= n_cu && !(a.stream_out && k == 1)) return 3 + k;
+  return 0;
+}
+
+template <int NV>
+void launch_nv(const AdapterArgs& a, const Route& rt, hipStream_t s) {
+  const int n_cu = rt.n_cu >= 1 ? rt.n_cu : 256;
+  if (a.n_tiles128 <= 0) return;
+  AdapterArgs b = a;
+  if (const int shift = unit_shift(a, n_cu)) {
+    b.unit_shift = shift;
+    b.unit_rows = 1 << shift;
+    hipLaunchKernelGGL((pick<NV, true>(a)), dim3(a.units[shift - 3]), dim3(NTH), (Shape<NV, true>::LDS), s, b, rt);
+    return;
+  }
   const long long U = (long long)a.n_tiles128 * 4;
   long long grid = U < n_cu ? U : n_cu;                               // one workgroup per compute unit ...
   const long long need = (U + MAX_UNITS - 1) / MAX_UNITS;            // ... unless that hands a workgroup
@@ -580,3 +586,13 @@ void launch_adapter_bf16(const AdapterArgs& a, const Route& rt, hipStream_t s) {
 }
 
 }  // namespace hmi
+
+// The rule alone, for the tests: rows of a unit (8, 16, 32), or 0 for the general form.  units8, units16, units32: units of that
+// many rows, summed over the batch's tenants.
+extern "C" int32_t hmi_internal_adapter_unit(int32_t tenants, int32_t units8, int32_t units16, int32_t units32, int32_t with_norm, int32_t n_cu) {
+  hmi::AdapterArgs a{};
+  a.n_segs = tenants; a.stream_out = !with_norm;
+  a.units[0] = units8; a.units[1] = units16; a.units[2] = units32;
+  const int shift = hmi::unit_shift(a, n_cu);
+  return shift ? 1 << shift : 0;
+}

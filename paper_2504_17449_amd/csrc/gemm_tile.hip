@@ -515,6 +515,9 @@ typedef Tile<true, 128, 256, 2, 2, 1, 3> TileXL;     // 144 KB: one
 typedef Tile<false, 64, 64, 2, 2, 1, 5> TileF32;     // 80 KB: two
 typedef Tile<false, 64, 32, 2, 1, 2, 3, 2> TileF32H;    // 72 KB: two
 typedef Tile<false, 32, 32, 1, 1, 4, 3, 4> TileF32Q;    // 96 KB: one
+
+enum TileForm : int { TILE_ONE_LINE = 0, TILE_32x32_TWO, TILE_32x64_TWO, TILE_64x64_TWO, TILE_128x64_TWO };
+enum TileFormF32 : int { TILE_F32_32x32 = 0, TILE_F32_64x32, TILE_F32_64x64 };
 }  // namespace
 
 void init_gemm_tile_kernels() {
@@ -561,22 +564,36 @@ GemmKernel pick_gemm_bf16(const GemmArgs& g, const Route& rt) {
   return which;
 }
 
+// The tile kernel that a launch of 64 x 64 or 128 x 64 tiles gets: with two lines of k a stage in a launch of one round, and then
+// the smallest that still is one.
+TileForm tile_form(GemmKernel which, const GemmArgs& g, const Route& rt) {
+  const int n_cu = rt.n_cu >= kXcds ? rt.n_cu : 256;
+  const bool two = g.k % 128 == 0;           // whole stages of two lines
+  if (which == GEMM_64x64) {
+    if (two && TileU2::tiles(g, rt, 1) <= n_cu) return TILE_32x32_TWO;
+    if (two && TileT2::tiles(g, rt, 1) <= n_cu) return TILE_32x64_TWO;
+    if (two && TileS2::tiles(g, rt, 1) <= n_cu) return TILE_64x64_TWO;
+    return TILE_ONE_LINE;
+  }
+  return which == GEMM_128x64 && two && TileM2::tiles(g, rt, 1) <= n_cu ? TILE_128x64_TWO : TILE_ONE_LINE;
+}
+
 void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
   if (g.n_rows <= 0 || g.n_mtiles_list[1] <= 0) return;
   GemmArgs a = g;
-  const int n_cu = rt.n_cu >= kXcds ? rt.n_cu : 256;
-  const bool two = g.k % 128 == 0;           // whole stages of two lines
-  switch (pick_gemm_bf16(g, rt)) {
+  const GemmKernel which = pick_gemm_bf16(g, rt);
+  const TileForm form = tile_form(which, g, rt);
+  switch (which) {
     case GEMM_STREAM:
       a.which_tiles = 1;
       a.n_mtiles = g.n_mtiles_list[1];
       return launch_gemm_bf16_skinny(a, rt, s);
     case GEMM_64x64:
-      if (two && TileU2::tiles(g, rt, 1) <= n_cu) return TileU2::launch(g, rt, 1, s);
-      if (two && TileT2::tiles(g, rt, 1) <= n_cu) return TileT2::launch(g, rt, 1, s);
-      if (two && TileS2::tiles(g, rt, 1) <= n_cu) return TileS2::launch(g, rt, 1, s);
+      if (form == TILE_32x32_TWO) return TileU2::launch(g, rt, 1, s);
+      if (form == TILE_32x64_TWO) return TileT2::launch(g, rt, 1, s);
+      if (form == TILE_64x64_TWO) return TileS2::launch(g, rt, 1, s);
       return TileS::launch(g, rt, 1, s);
-    case GEMM_128x64: return two && TileM2::tiles(g, rt, 1) <= n_cu ? TileM2::launch(g, rt, 1, s) : TileM::launch(g, rt, 1, s);
+    case GEMM_128x64: return form == TILE_128x64_TWO ? TileM2::launch(g, rt, 1, s) : TileM::launch(g, rt, 1, s);
     case GEMM_128x128: return TileL::launch(g, rt, 1, s);
     case GEMM_128x256: return TileXL::launch(g, rt, 1, s);
     case GEMM_PERSISTENT:
@@ -591,28 +608,57 @@ void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
 // that is a round; past that the smaller of the two rounds counted in half tiles, of which those of the 64 x 32 tiles, which copy
 // half as much again for a product, take 1.12 times as long.  Measured, us: 1 728 rows of eight tenants, 64 x 64 and 64 x 32: 768
 // columns, k = 768 and 3072 together 153, 136; 2 304 columns 78.5, 81.5; 3 072 columns with GELU 99, 116.
-void launch_gemm_f32(const GemmArgs& g, const Route& rt, hipStream_t s) {
-  if (g.n_rows <= 0) return;
+TileFormF32 tile_form_f32(const GemmArgs& g, const Route& rt) {
   const int n_cu = rt.n_cu >= kXcds ? rt.n_cu : 256;
-  if (g.k % 128 == 0 && TileF32Q::tiles(g, rt, 0) <= n_cu) return TileF32Q::launch(g, rt, 0, s);
+  if (g.k % 128 == 0 && TileF32Q::tiles(g, rt, 0) <= n_cu) return TILE_F32_32x32;
   if (g.k % 64 == 0) {
     const long long whole = (TileF32::tiles(g, rt, 0) + n_cu - 1) / n_cu * 2, half = (TileF32H::tiles(g, rt, 0) + n_cu - 1) / n_cu;
-    if (half == 1 || 112 * half < 100 * whole) return TileF32H::launch(g, rt, 0, s);
+    if (half == 1 || 112 * half < 100 * whole) return TILE_F32_64x32;
   }
-  TileF32::launch(g, rt, 0, s);
+  return TILE_F32_64x64;
+}
+
+void launch_gemm_f32(const GemmArgs& g, const Route& rt, hipStream_t s) {
+  if (g.n_rows <= 0) return;
+  switch (tile_form_f32(g, rt)) {
+    case TILE_F32_32x32: return TileF32Q::launch(g, rt, 0, s);
+    case TILE_F32_64x32: return TileF32H::launch(g, rt, 0, s);
+    case TILE_F32_64x64: return TileF32::launch(g, rt, 0, s);
+  }
 }
 
 }  // namespace hmi
 
-// The rule alone, for the tests: which kernel (GemmKernel) a bf16 launch of these sizes gets.  tiles256, tiles128: m-tiles of
-// 256 and 128 rows, summed over the batch's tenants (or of all rows, where the weights are shared).
-extern "C" int32_t hmi_internal_gemm_kernel(int32_t n_rows, int32_t tiles256, int32_t tiles128, int32_t n_out, int32_t k,
-                                            int32_t gelu, int32_t shared, int32_t n_cu) {
+// The rules alone, for the tests.  Which kernel (GemmKernel) a bf16 launch of these sizes gets, and which of its tile kernels
+// (TileForm); which one (TileFormF32) an fp32 launch gets.  tiles256, tiles128, tiles64: m-tiles of 256, 128 and 64 rows, summed
+// over the batch's tenants (or of all rows, where the weights are shared).
+namespace {
+hmi::GemmArgs rule_args(int32_t n_rows, int32_t list0, int32_t list1, int32_t n_out, int32_t k, int32_t gelu) {
   hmi::GemmArgs g{};
   g.n_rows = n_rows; g.n_out = n_out; g.k = k; g.epi = gelu ? hmi::EPI_BIAS_GELU : hmi::EPI_BIAS;
-  g.n_mtiles_list[0] = tiles256; g.n_mtiles_list[1] = tiles128;
+  g.n_mtiles_list[0] = list0; g.n_mtiles_list[1] = list1;
+  return g;
+}
+hmi::Route rule_route(int32_t tile0, int32_t tile1, int32_t shared, int32_t n_cu) {
   hmi::Route rt{};
-  rt.tile_m[0] = hmi::kBf16TileM0; rt.tile_m[1] = hmi::kBf16TileM1;
+  rt.tile_m[0] = tile0; rt.tile_m[1] = tile1;
   rt.identity = shared; rt.n_cu = n_cu;
-  return hmi::pick_gemm_bf16(g, rt);
+  return rt;
+}
+}  // namespace
+
+extern "C" int32_t hmi_internal_gemm_kernel(int32_t n_rows, int32_t tiles256, int32_t tiles128, int32_t n_out, int32_t k,
+                                            int32_t gelu, int32_t shared, int32_t n_cu) {
+  return hmi::pick_gemm_bf16(rule_args(n_rows, tiles256, tiles128, n_out, k, gelu), rule_route(hmi::kBf16TileM0, hmi::kBf16TileM1, shared, n_cu));
+}
+
+extern "C" int32_t hmi_internal_gemm_form(int32_t n_rows, int32_t tiles256, int32_t tiles128, int32_t n_out, int32_t k,
+                                          int32_t gelu, int32_t shared, int32_t n_cu) {
+  const hmi::GemmArgs g = rule_args(n_rows, tiles256, tiles128, n_out, k, gelu);
+  const hmi::Route rt = rule_route(hmi::kBf16TileM0, hmi::kBf16TileM1, shared, n_cu);
+  return hmi::tile_form(hmi::pick_gemm_bf16(g, rt), g, rt);
+}
+
+extern "C" int32_t hmi_internal_gemm_form_f32(int32_t n_rows, int32_t tiles64, int32_t n_out, int32_t k, int32_t shared, int32_t n_cu) {
+  return hmi::tile_form_f32(rule_args(n_rows, tiles64, 0, n_out, k, 0), rule_route(hmi::kF32TileM, 0, shared, n_cu));
 }
