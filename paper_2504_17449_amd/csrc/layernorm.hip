@@ -8,6 +8,8 @@
 
 #include "wave_sum.h"
 
+#include <utility>
+
 namespace hmi {
 namespace {
 
@@ -31,9 +33,10 @@ __device__ __forceinline__ int find_segment(const Route& rt, int srow, int* seg_
   return lo;
 }
 
-// A lane owns columns lane, lane + 64, ... : PER of them where d = 64 PER, else (PER = 0) as many as there are below d.  Narrow
-// layers are latency alone: row, gain and shift are asked for together, in front of the sums (128 rows of d = 64, fp32: with the
-// loops of the general form and a search through global memory 5.0 us, now 2.9).
+// A lane owns columns lane, lane + 64, ... : PER of them where d = 64 PER, else (fp32 only, PER = 0) as many as there are below d.
+// Small launches are latency alone: row, gain and shift are asked for together, in front of the sums (128 rows of d = 64, fp32: with
+// the loops of the general form and a search through global memory 5.0 us, now 2.9); in large ones the general form's checks of
+// every column cost it half the rate (figures at the launcher).
 template <bool BF16, int PER>
 __global__ __launch_bounds__(256) void layernorm_kernel(LnArgs a, Route rt) {
   __shared__ int seg_s[kMaxRequests + 1];
@@ -175,10 +178,20 @@ static void launch_vec(const LnArgs& a, const Route& rt, hipStream_t s, unsigned
   else hipLaunchKernelGGL((layernorm_vec_kernel<true, false, NV>), dim3(blocks), dim3(256), 0, s, a, rt);
 }
 
+// Whole multiples of 64 columns that layernorm_vec_kernel does not take.
+constexpr bool takes_vec(int d) { return d == 256 || d == 512 || d == 768 || d == 1024 || d == 2048; }
+
 template <int PER>
-static void launch_narrow(const LnArgs& a, const Route& rt, hipStream_t s, unsigned blocks) {
-  if (a.bf16) hipLaunchKernelGGL((layernorm_kernel<true, PER>), dim3(blocks), dim3(256), 0, s, a, rt);
-  else hipLaunchKernelGGL((layernorm_kernel<false, PER>), dim3(blocks), dim3(256), 0, s, a, rt);
+static void launch_whole(const LnArgs& a, const Route& rt, hipStream_t s, unsigned blocks) {
+  if constexpr (!takes_vec(64 * PER)) {
+    if (a.bf16) hipLaunchKernelGGL((layernorm_kernel<true, PER>), dim3(blocks), dim3(256), 0, s, a, rt);
+    else hipLaunchKernelGGL((layernorm_kernel<false, PER>), dim3(blocks), dim3(256), 0, s, a, rt);
+  }
+}
+
+template <int... I>
+static void launch_per(int per, const LnArgs& a, const Route& rt, hipStream_t s, unsigned blocks, std::integer_sequence<int, I...>) {
+  ((per == I + 1 ? launch_whole<I + 1>(a, rt, s, blocks) : void()), ...);
 }
 
 void launch_layernorm(const LnArgs& a, const Route& rt, hipStream_t s) {
@@ -192,13 +205,11 @@ void launch_layernorm(const LnArgs& a, const Route& rt, hipStream_t s) {
     case 2048: return launch_vec<8>(a, rt, s, blocks);
     default: break;
   }
-  switch (a.d) {
-    case 64: return launch_narrow<1>(a, rt, s, blocks);
-    case 128: return launch_narrow<2>(a, rt, s, blocks);
-    case 192: return launch_narrow<3>(a, rt, s, blocks);
-    case 320: return launch_narrow<5>(a, rt, s, blocks);
-    default: return launch_narrow<0>(a, rt, s, blocks);
-  }
+  // Whole multiples of 64 columns (all there is in bf16): as many a lane as there are.  At every width up to 1 984 that was the faster
+  // one, us, general form and this: 128 rows of 384, 960, 1 984 fp32 6.2, 7.8, 10.7 and 2.8, 4.0, 5.7; 16 384 rows 23.9, 39.7, 85.0
+  // and 12.1, 22.4, 51.8; bf16 16 384 rows 23.5, 38.7, 77.3 and 11.0, 20.3, 41.1.
+  if (a.d % 64 == 0) return launch_per(a.d / 64, a, rt, s, blocks, std::make_integer_sequence<int, kMaxPerLane>());
+  hipLaunchKernelGGL((layernorm_kernel<false, 0>), dim3(blocks), dim3(256), 0, s, a, rt);
 }
 
 }  // namespace hmi
