@@ -38,7 +38,7 @@
 // 2 664 rows 15.5 -> 13.1.
 #include "hmi_kernels.h"
 
-#include "wave_sum.h"
+#include "wave.h"
 
 namespace hmi {
 namespace {
@@ -62,16 +62,6 @@ constexpr int MID_BYTES = RT * RANK * 2;
 constexpr int RS_BYTES = MAX_UNITS * RT * 4;
 constexpr int DESC_BYTES = (MAX_UNITS * 4 + 4) * 4;
 
-// What the wavefronts pass on through LDS before a barrier; direct-to-LDS copies are waited for where their rows are due
-// (__syncthreads would wait for all of them, and for the stores, at the first barrier behind them).
-#define HMI_BARRIER()                                                                              \
-  {                                                                                                \
-    asm volatile("" ::: "memory");                                                                 \
-    __builtin_amdgcn_s_waitcnt(0xC07F);                                                            \
-    __builtin_amdgcn_s_barrier();                                                                  \
-    asm volatile("" ::: "memory");                                                                 \
-  }
-#define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
 __device__ __forceinline__ float bf2f(uint32_t u16) { return __uint_as_float(u16 << 16); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
@@ -87,17 +77,6 @@ template <bool ONCE>
 __device__ __forceinline__ bf16x8 load_w(const bf16x8* p) {
   if (ONCE) return __builtin_nontemporal_load(p);
   return *p;
-}
-
-// Inclusive prefix sum over the 64 lanes (rows of 16 by row shifts, then across rows by row broadcasts).
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
-  return v;
 }
 
 // What happens to the finished rows of a unit.

@@ -42,6 +42,7 @@
 #include "hmi_kernels.h"
 
 #include "gelu.h"
+#include "wave.h"
 
 namespace hmi {
 namespace {
@@ -93,8 +94,6 @@ __device__ __forceinline__ int perm_w(int i) { return ((i >> 2) & 1) * 16 + (i >
 // take stays with the operand panels that other workgroups of the XCD are about to ask for (measured: 1-2 % fewer
 // bytes fetched, GEMM time -0.7 to -1 % on the FFN, encoder and shared-layer workloads).
 #define HMI_STORE_OUT(PTR, V) __builtin_nontemporal_store((V), (PTR))
-#define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-#define HMI_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(0xC07F)
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;

@@ -23,6 +23,7 @@
 #include "hmi_kernels.h"
 
 #include "gelu.h"
+#include "wave.h"
 
 namespace hmi {
 namespace {
@@ -60,15 +61,6 @@ struct Ring {
 };
 constexpr int kDeepMaxItems = 1024;
 
-// what a wavefront wrote to LDS is there for the others behind it
-#define HMI_BARRIER()                                                                              \
-  {                                                                                                \
-    asm volatile("" ::: "memory");                                                                 \
-    __builtin_amdgcn_s_waitcnt(0xC07F);                                                            \
-    __builtin_amdgcn_s_barrier();                                                                  \
-    asm volatile("" ::: "memory");                                                                 \
-  }
-#define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
 __device__ __forceinline__ float bf2f(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {

@@ -41,6 +41,7 @@
 #include "hmi_kernels.h"
 
 #include "gelu.h"
+#include "wave.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -60,8 +61,6 @@ typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 constexpr int kXcds = 8;
 constexpr int ROW_BYTES = 128;            // k bytes of a row and stage
 
-#define HMI_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(0xC07F)
-#define HMI_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 0xF) | (((N) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
 __device__ __forceinline__ float bf2f(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {

@@ -6,7 +6,7 @@
 // An optional second input is added first (residual stream + adapted attention output).
 #include "hmi_kernels.h"
 
-#include "wave_sum.h"
+#include "wave.h"
 
 #include <utility>
 

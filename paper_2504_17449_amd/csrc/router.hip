@@ -20,22 +20,12 @@
 // 65 536 rows over 10 000 ids 24.4 -> 13.1; 2 us of each are the reads of the inputs over the host link.
 #include "hmi_kernels.h"
 
+#include "wave.h"
+
 namespace hmi {
 namespace {
 
 constexpr int kMaxWorkgroups = 8;
-
-// Inclusive prefix sum over the 64 lanes: inside rows of 16 by row shifts, then across rows by row broadcasts (six
-// additions with their operand moved on the way, where a shuffle is a trip through the LDS crossbar).
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-  return v;
-}
 
 // Exclusive prefix sums of two values per element over the workgroup's elements in order (round, wavefront, lane), and
 // their totals.  One barrier; `tots` must not be in use by an earlier call (each call gets its own).
