@@ -16,6 +16,8 @@
 // exchange with the partner lane 32 apart, which holds the other half of the keys).
 #include "hmi_kernels.h"
 
+#include <algorithm>
+
 namespace hmi {
 namespace {
 
@@ -43,7 +45,7 @@ __global__ __launch_bounds__(256) void attn_bf16_kernel(AttnArgs a, Route rt) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[KB * DH];      // [key][dh], swizzled chunks
   __shared__ __attribute__((aligned(16))) uint16_t Vt[DH * VT_LD];   // [dh][key]
 
-  const int r = blockIdx.z, head = blockIdx.x, q0 = blockIdx.y * QB;
+  const int r = blockIdx.z, head = blockIdx.x, q0 = (a.first_block + blockIdx.y) * QB;
   const int start = rt.tok_off[r];
   const int len = rt.tok_off[r + 1] - start;
   if (q0 >= len) return;
@@ -252,7 +254,7 @@ __device__ __forceinline__ bool finite(float v) { return (__float_as_uint(v) & 0
 __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(AttnArgs a, Route rt) {
   __shared__ f32x4 Ks[FK * 16];
   __shared__ f32x4 Vs[FK * 16];
-  const int r = blockIdx.z, head = blockIdx.x, q0 = blockIdx.y * FQ;
+  const int r = blockIdx.z, head = blockIdx.x, q0 = (a.first_block + blockIdx.y) * FQ;
   const int start = rt.tok_off[r];
   const int len = rt.tok_off[r + 1] - start;
   if (q0 >= len) return;
@@ -441,19 +443,35 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a, Route rt, int 
 
 }  // namespace
 
-void launch_attention(const AttnArgs& a, const Route& rt, hipStream_t s) {
+// The second index of a grid ends at 65 535, which is 4 million rows of one request in fp32 (narrow layers have room for 16 million):
+// longer requests take several launches.
+void launch_attention(const AttnArgs& a, const Route& rt, hipStream_t s, int blocks_a_launch) {
   if (a.R <= 0) return;
-  if (a.bf16) {
-    dim3 grid(a.n_heads, (a.longest + QB - 1) / QB, a.R);
-    if (a.cache) hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, dim3(256), 0, s, a, rt);
-    else hipLaunchKernelGGL(attn_bf16_kernel<false>, grid, dim3(256), 0, s, a, rt);
-  } else if (a.d == 64 * a.n_heads) {
-    dim3 grid(a.n_heads, (a.longest + FQ - 1) / FQ, a.R);
-    hipLaunchKernelGGL(attn_f32_mfma_kernel, grid, dim3(256), 0, s, a, rt);
-  } else {
+  if (!a.bf16 && a.d != 64 * a.n_heads) {
     dim3 grid(a.n_rows, a.n_heads, 1);
     hipLaunchKernelGGL(attn_f32_kernel, grid, dim3(64), 0, s, a, rt, a.n_rows);
+    return;
+  }
+  const int queries = a.bf16 ? QB : FQ, blocks = (a.longest + queries - 1) / queries;
+  AttnArgs b = a;
+  for (b.first_block = 0; b.first_block < blocks; b.first_block += blocks_a_launch) {
+    const dim3 grid(a.n_heads, std::min(blocks - b.first_block, blocks_a_launch), a.R);
+    if (!a.bf16) hipLaunchKernelGGL(attn_f32_mfma_kernel, grid, dim3(256), 0, s, b, rt);
+    else if (a.cache) hipLaunchKernelGGL(attn_bf16_kernel<true>, grid, dim3(256), 0, s, b, rt);
+    else hipLaunchKernelGGL(attn_bf16_kernel<false>, grid, dim3(256), 0, s, b, rt);
   }
 }
 
 }  // namespace hmi
+
+// For the tests: attention over qkv [n_rows, 3 d] (device), requests at tok_off [R + 1] (device), as a model's layers call it but with
+// that many blocks of queries a launch.
+extern "C" void hmi_internal_attention(const void* qkv, void* ctx, const int32_t* tok_off, int32_t R, int32_t longest, int32_t n_rows, int32_t d,
+                                       int32_t n_heads, int32_t causal, int32_t bf16, int32_t blocks_a_launch, void* stream) {
+  hmi::AttnArgs a{};
+  a.qkv = qkv; a.ctx = ctx; a.d = d; a.n_heads = n_heads; a.causal = causal; a.R = R;
+  a.longest = longest; a.bf16 = bf16; a.n_rows = n_rows;
+  hmi::Route rt{};
+  rt.tok_off = const_cast<int32_t*>(tok_off);
+  hmi::launch_attention(a, rt, reinterpret_cast<hipStream_t>(stream), blocks_a_launch);
+}

@@ -165,8 +165,10 @@ struct AttnArgs {
   int n_rows;          // N = total rows (fp32 kernel: one wavefront per row and head)
   uint16_t* cache;     // bf16 prompts: the layer's key/value lines, into which the rows' keys and values go too (else null)
   int max_len;         // positions of a line
+  int first_block;     // set by the launcher: the launch's first block of queries
 };
-void launch_attention(const AttnArgs& a, const Route& rt, hipStream_t s);
+constexpr int kMaxGridY = 65535;
+void launch_attention(const AttnArgs& a, const Route& rt, hipStream_t s, int blocks_a_launch = kMaxGridY);
 
 // Aggregate of precomputed tri-gram representations: table [n_entries, 3, d] and x [N, d] in the
 // storage dtype, frag_ids [N] device, tok_off [R + 1] (may be pinned host memory).
