@@ -34,8 +34,8 @@
 // In small launches (a unit a workgroup, ONE below) it is a chain of latencies on top of the 0.2 MB of matrices, which take a
 // compute unit 1.4 us.  The chain is kept short: each wavefront finds its unit by itself, from the segments' ends; everything
 // is asked for before anything is waited for; sums over a wavefront stay in registers.  141 rows of two tenants with LayerNorm
-// 13.4 -> 8.3 us, a decode step's 7 rows 13.3 -> 9.6 and 256 rows of 137 tenants 15.8 -> 12.7 (their 27 MB come from HBM),
-// 2 664 rows 15.5 -> 13.1.
+// 13.4 -> 8.3 us, a decode step's 7 rows 13.3 -> 9.2 and 256 rows of 137 tenants 15.8 -> 12.6 (their 27 MB come from HBM),
+// 2 664 rows 15.5 -> 14.0.
 #include "hmi_kernels.h"
 
 #include "wave.h"
@@ -61,7 +61,6 @@ constexpr int PART_BYTES = 4 * RT * RANK * 4;   // four partial sums of the 32 x
 constexpr int MID_BYTES = RT * RANK * 2;
 constexpr int RS_BYTES = MAX_UNITS * RT * 4;
 constexpr int DESC_BYTES = (MAX_UNITS * 4 + 4) * 4;
-
 
 __device__ __forceinline__ float bf2f(uint32_t u16) { return __uint_as_float(u16 << 16); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
@@ -487,9 +486,11 @@ int unit_shift(const AdapterArgs& a, int n_cu) {
   // While there is a compute unit for each, the units are as small as may be: what one costs is then the traffic of its rows
   // through one of them, besides its matrices' (two requests of 101 and 40 rows with LayerNorm: 12.4 us in units of 32 rows, up
   // to 0.49 MB each, 8.3 in units of 8), and they are counted exactly (a decode step of 256 rows, the most popular tenant with 34
-  // of them: 14.5 us with four units for each 128-row tile, most of them empty, 12.7 with these).
+  // of them: 14.5 us with four units for each 128-row tile, most of them empty, 12.6 with these).  The general form does not
+  // count: it has four units for every 128-row tile, and a step of 257 tenants with a row each takes 18.2 us, of 256 15.1.
   // Without LayerNorm a unit's own rows are little work and units of 16 rows only read the matrices twice: where 8-row units are
-  // too many, units of 32 (2 789 rows of d = 512, 15.3 us in units of 16, 14.1 in units of 32; 3 473 of d = 256 12.3 and 11.7).
+  // too many, units of 32 (two batches: 2 789 rows of d = 512, 15.3 us in units of 16, 14.1 in units of 32; 3 473 of d = 256
+  // 12.3 and 11.7).
   if (a.n_segs <= MAX_SEGS)
     for (int k = 0; k < 3; ++k)   // (two workgroups a compute unit, where rows are narrow enough, load the matrices twice: 8 586 rows of d = 256 5 % slower)
       if (a.units[k] <= n_cu && !(a.stream_out && k == 1)) return 3 + k;

@@ -38,8 +38,9 @@ constexpr int VT_LD = 72;     // V^T row pitch in elements (keys), padded
 // line, as they pass through its registers (69 632 rows of d = 768: a kernel of its own read them again, 101 us a layer).
 //
 // Heads are the fastest index of the grid, not the blocks of queries: workgroups go to the XCDs round robin, and with two or four
-// blocks in front each XCD would get the same block of every request, the first full and the last mostly empty (requests of
-// 16 to 256 rows: half of the XCDs had nothing to do for the last third of the launch).
+// blocks in front each XCD would get the same block of every request, the first full and the last mostly empty (12 heads,
+// requests of 16 to 256 rows: half of the XCDs had nothing to do for the last third of the launch).  With 1, 2 or 4 heads and an
+// even number of blocks it still does: there heads and blocks together are what the round of eight XCDs repeats.
 template <bool STORE>
 __global__ __launch_bounds__(256) void attn_bf16_kernel(AttnArgs a, Route rt) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[KB * DH];      // [key][dh], swizzled chunks

@@ -61,7 +61,6 @@ struct Ring {
 };
 constexpr int kDeepMaxItems = 1024;
 
-
 __device__ __forceinline__ float bf2f(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

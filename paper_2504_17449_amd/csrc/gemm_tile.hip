@@ -12,9 +12,10 @@
 //   * A compute unit takes 66 bytes per clock through its L1, whether into LDS or into registers (measured; LDS reads
 //     270): a stage of a 128 x 128 tile is 512 clocks of copies and 512 of MFMAs.  They only overlap if they are issued by
 //     different wavefronts: a wavefront that has copies to issue stands still until L1 takes them (measured: 8 MFMAs and
-//     4 copies in one instruction stream take 357 clocks for 249 of either).  So a workgroup is four consumers, WM x WN
-//     over the BM x BN tile, which read LDS and multiply, and four producers, which do nothing but copy: one launch of
-//     768 x 3072 weights over 100 rows 28.8 -> 23.7 us with 128 x 128 tiles, 15.9 -> 11.4 with 64 x 64.
+//     4 copies in one instruction stream take 357 clocks for 249 of either).  So a workgroup is one to four consumers,
+//     WM x WN over the BM x BN tile (fp32: times KH sets that share k), which read LDS and multiply, and four
+//     producers, which do nothing but copy: one launch of 768 x 3072 weights over 100 rows 28.8 -> 23.7 us with 128 x 128
+//     tiles, 15.9 -> 11.4 with 64 x 64.
 //   * Operands come in stages of 128 bytes of k per row (64 bf16 or 32 fp32: one cache line, eight lanes fetch a row's
 //     line) by direct-to-LDS copies into a ring of STAGES, one barrier per stage.
 //   * A 16-byte chunk of a row is one fragment read: one v_mfma_f32_32x32x16_bf16, or four v_mfma_f32_32x32x2_f32
@@ -24,8 +25,8 @@
 //     with the vector ALU's fused chain; two encoder layers of 1 728 rows 672.5 us with one, 673.1 with two); where wavefronts
 //     share k there are two such sums for each of them (24 drawn fp32 cases: 0.85 of the error of two).
 //   * Weights are the MFMA's first operand, in a permuted row order, so that a lane ends up with 16 consecutive columns
-//     of one row of C: the epilogue reads residuals and writes results straight from the accumulators in 16-byte pieces.
-//     Accumulators start at the bias.
+//     of one row of C: bf16 results without a residual leave straight from the accumulators in 16-byte pieces, fp32 results
+//     and sums with residuals through a patch of LDS (below).  Accumulators start at the bias.
 //   * What the launch fetches is what the XCDs' L2s fetch, each for itself: m-tile by m-tile a launch of a few of them reads
 //     the weights once for each.  So the tiles of shared weights are shared out among the XCDs in blocks of rows and columns
 //     (xcd_rows below); with a tenant's own weights an XCD has a contiguous range of tiles, m-tile by m-tile.
@@ -59,8 +60,7 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
 constexpr int kXcds = 8;
-constexpr int ROW_BYTES = 128;            // k bytes of a row and stage
-
+constexpr int ROW_BYTES = 128;            // k bytes of a row and line
 
 __device__ __forceinline__ float bf2f(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
@@ -527,14 +527,21 @@ void init_gemm_tile_kernels() {
 //
 // Few rows per weight matrix (a decode step over many tenants: at most 32 rows per 128-row m-tile on average): the weights
 // are read once and nothing else matters, gemm_bf16_skinny.hip streams them.  A launch whose 32 x 32 items do not fill the
-// compute units and whose k is long goes there too: it shares k among the four wavefronts of an item (100 rows x 768
-// columns x k = 3072: 7.2 us, 64 x 64 tiles 11.4; 300 rows, 288 items: 13.6 and 12.1; k = 768: 5.0 and 5.0).
+// compute units and whose k is long goes there too: it shares k among the four wavefronts of an item (768 columns x k = 3072,
+// us, split and the best tiles, 32 x 32 with two lines of k a stage: 7 rows 6.2, 7.3; 100 rows 8.2, 7.7; 300 rows 8.7, 8.5).
 //
 // Everything else is tiles, and the size of the tile is a matter of how many compute units the launch would leave idle: a
 // larger tile moves fewer bytes per product, a smaller one comes in more pieces.  The estimate is the time of the busiest
 // compute unit: its tiles times (stages of 64 k times the time of one stage, plus what a tile costs besides, which the
 // second workgroup of a compute unit hides for the small tiles; the activation adds to that).  Microseconds, measured with
-// d = 768, f = 3072 over 100 to 16 384 rows of one weight set; the estimate's choice was the fastest or within 10 % of it.
+// d = 768, f = 3072 over 100 to 16 384 rows of one weight set.  The two small tiles are weighed with one line of k a stage,
+// also where the launch, being one round, gets them with two (tile_form below), 0.6 to 0.95 of the time: there the estimate
+// ranks sizes, it is no time.  What the rule launches against each of the other forms, 7 to 4 096 rows of one weight set, four
+// GEMMs of a layer each: the fastest, or behind it by no more than the same kernel's times differ with what the launches
+// before it leave in the caches (14 %, 28 % in the second FFN GEMM of 4 096 rows), but for, us: 1 024 rows QKV 13.2 in
+// 64 x 64 tiles (128 x 128: 11.2); 4 096 rows output projection 12.2 in 64 x 64 (128 x 128: 9.7); FFN1 with GELU of 756 and
+// 1 024 rows 15.8 and 16.8 in 64 x 64 (128 x 64: 13.4 and 13.3), of 640 10.9 (128 x 64 with two lines: 9.4), of 7 rows 5.5 (the
+// split kernel: 4.6).
 // It says nothing about weights that come from HBM or panels that are fetched again, so a launch that gives the
 // persistent kernel's workgroups more than one and a half tiles each is not weighed at all: it was the faster one for all
 // of those (two encoder layers of 177 tenants, 65 536 rows: 3.1 ms, with 128 x 256 tiles where the estimate is lower 3.4).
