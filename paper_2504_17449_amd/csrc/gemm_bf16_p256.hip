@@ -10,8 +10,8 @@
 //     cache line, 64 if it covers half of one (33 TB/s against 17-20 TB/s for direct-to-LDS
 //     copies that hit in L2).  Stores follow the same rule: a wavefront store that touches
 //     64 different lines costs 64 requests however few bytes it carries.
-//   * The matrix pipe blocks a wavefront's instruction issue for half the duration of an
-//     MFMA; about four other instructions fit behind each one.
+//   * What the matrix cores sustain on random operands is a matter of power: fragments out of LDS, 64 x 128 a
+//     wavefront, v_mfma_f32_16x16x32_bf16 1 860 TFLOP/s, v_mfma_f32_32x32x16_bf16 1 660 (out of registers 2 120 and 1 860).
 //   * LDS reads run at 256 B/clk.
 // Hence
 //   * 256 x 256 tiles: the fewest operand bytes per FLOP the register file allows, held either by
@@ -24,17 +24,20 @@
 //     tenant) run further ahead than activation copies (mostly hits).  A wavefront issues a
 //     stage's activation copies before its weight copies, so with in-order completion "all but
 //     the newest weight stage have landed" is exactly the condition for the next stage;
+//   * products on the 16 x 16 x 32 instruction, with each fragment read again for the next k-step as soon as it has been used for
+//     the last time: one set of fragment registers, and a barrier a stage that stands where a wavefront has its last fragments.
+//     65 536 rows of one weight set (d = 768, f = 3072), 32 x 32 x 16 products with two sets of fragments and these: QKV and output
+//     projection together 329 us -> 313, FFN1 with GELU 344 -> 319, FFN2 with fp32 residuals 318 -> 290; 64 tenants' 32 768
+//     rows, FFN1 239 -> 219, FFN2 224 -> 193;
 //   * a compute unit takes 66 bytes per clock through its L1: a stage's copies are spread over its
 //     MFMAs, since a wavefront that issues them faster than that stands still with its products
 //     (all sixteen behind the sixteen MFMAs of one k-step, as before: second FFN GEMM of 65 536 rows
 //     329 us -> 307 with four wavefronts; of 64 tenants' 32 768 rows 209 -> 190; the launches with
 //     eight wavefronts 0 to 1.5 % faster);
 //   * one workgroup per compute unit walks over its share of the tiles.  Copies for the
-//     next tile are issued while the current one finishes, fragment reads are double
-//     buffered in registers one k-step ahead (across stage and tile boundaries), and there
-//     is one barrier per stage, placed so that the MFMAs of the last k-step hide it;
+//     next tile are issued while the current one finishes;
 //   * operand roles are swapped (weights are the MFMA's first operand, in a permuted row
-//     order): a lane ends up with one row of C and 16 consecutive columns per MFMA tile;
+//     order): a lane ends up with one row of C and 16 consecutive columns per four MFMA tiles;
 //     bias is folded into the accumulator initialisation.  For the stores each wavefront
 //     transposes its results through the part of the two idle ring slots that only its
 //     own copies overwrite (no barrier), so that 16 or 32 consecutive lanes write one
@@ -42,20 +45,20 @@
 #include "hmi_kernels.h"
 
 #include "gelu.h"
+#include "lds_copy.h"
 #include "wave.h"
 
 namespace hmi {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kXcds = 8;
 constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int WTN = 128, TN = 4;                             // a wavefront's 128 columns: four MFMA tiles
+constexpr int WTN = 128, TN = 8;                             // a wavefront's 128 columns: eight MFMA tiles
 // The workgroup is NW = 8 or 4 wavefronts, NW/2 x 2 over the tile: wavefront tiles of 64 x 128 (two per SIMD,
 // 128 accumulator registers each) or 128 x 128 (one per SIMD with 256 accumulators in the AGPR half of a
 // 512-register budget: a third less fragment traffic per MFMA and one instruction stream per matrix pipe,
@@ -63,7 +66,8 @@ constexpr int WTN = 128, TN = 4;                             // a wavefront's 12
 template <int NW>
 struct Geo {
   static constexpr int NTH = 64 * NW;
-  static constexpr int WTM = BM / (NW / 2), TM = WTM / 32;  // wavefront tile rows, MFMA tiles
+  static constexpr int WTM = BM / (NW / 2), TM = WTM / 16;  // wavefront tile rows, MFMA tiles
+  static constexpr int FWB = NW == 4 ? 2 : 1;               // register buffers of weight fragments (see HMI_ROWS)
   static constexpr int RH = WTM / 64;                       // output-row ids a lane keeps per tile
   static constexpr int LD = BM / 8 / NW;                    // one-KB copies (8 rows x 128 B) per wavefront, operand and stage: 4 or 8
   static constexpr int WAVE_SLICE = LD * 1024;              // the part of a stage slot that one wavefront's copies fill
@@ -81,22 +85,20 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, p);
 }
 
-// LDS chunk swizzles (a row is 8 chunks of 16 bytes, two rows per 256-byte bank line).
-// Activation rows are read by consecutive lanes in consecutive order; weight rows in the
-// permuted order perm_w.  Either way the 16 lanes served together hit 16 distinct chunks.
+// LDS chunk swizzles (a row is 8 chunks of 16 bytes, two rows per 256-byte bank line).  A fragment read takes one chunk of 16
+// rows for each quarter of the lanes: consecutive activation rows, weight rows in the order perm_w.  Either way the 16 lanes
+// served together hit 16 distinct chunks.
 __device__ __forceinline__ int swz_a(int row) { return (row >> 1) & 7; }
-__device__ __forceinline__ int swz_w(int row) { return ((row >> 1) & 3) | (((row >> 4) & 1) << 2); }
-// MFMA first-operand position i (0..31) <- weight row perm_w(i) of the 32-row tile, chosen
-// so that output register r of lane half h is column 16 h + r.
-__device__ __forceinline__ int perm_w(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
+__device__ __forceinline__ int swz_w(int row) { return ((row >> 1) & 1) | (((row >> 4) & 3) << 1); }
+// MFMA first-operand position i (0..15) of MFMA tile j <- weight row perm_w(i) + 64 (j / 4) + 4 (j % 4) of the wavefront's 128,
+// chosen so that output register r of tile j and lane quarter q is column 64 (j / 4) + 16 q + 4 (j % 4) + r.
+__device__ __forceinline__ int perm_w(int i) { return (i >> 2) * 16 + (i & 3); }
 
 // Results leave with the non-temporal hint: nothing in this launch reads them again, and every line of L2 they do not
 // take stays with the operand panels that other workgroups of the XCD are about to ask for (measured: 1-2 % fewer
 // bytes fetched, GEMM time -0.7 to -1 % on the FFN, encoder and shared-layer workloads).
 #define HMI_STORE_OUT(PTR, V) __builtin_nontemporal_store((V), (PTR))
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
 // What a lane needs to know about a tile: where its copies come from and where the bias is.
 constexpr int kMBlock = 8;   // m-tiles per block of a long segment's tile order
@@ -110,6 +112,9 @@ struct TileRegs {
   int out_row[Geo<NW>::RH];        // where row (wavefront's first row + 64 h + lane) of the tile goes in C (row clamped to the tile)
 };
 
+// (the same for all lanes, so that it goes to a scalar register)
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 template <int NW>
 __device__ __forceinline__ void load_tile(const GemmArgs& g, const Route& rt, int w, int wave, int lane, TileRegs<NW>& tr) {
   constexpr int WTM = Geo<NW>::WTM, RH = Geo<NW>::RH, LD = Geo<NW>::LD;
@@ -118,9 +123,9 @@ __device__ __forceinline__ void load_tile(const GemmArgs& g, const Route& rt, in
   // share an activation panel) run next to each other and the panel is fetched from HBM once.
   const int nt_n = g.n_out / BN;
   const int mt_any = w / nt_n;                               // some m-tile of the segment w falls in
-  const int seg = rt.tile_seg[g.which_tiles][mt_any];
-  const int s0 = rt.seg_tok_off[seg], s1 = rt.seg_tok_off[seg + 1];
-  const int mt_first = mt_any - (rt.tile_row0[g.which_tiles][mt_any] - s0) / BM;
+  const int seg = uniform(rt.tile_seg[g.which_tiles][mt_any]);
+  const int s0 = uniform(rt.seg_tok_off[seg]), s1 = uniform(rt.seg_tok_off[seg + 1]);
+  const int mt_first = mt_any - (uniform(rt.tile_row0[g.which_tiles][mt_any]) - s0) / BM;
   const int mt_cnt = (s1 - s0 + BM - 1) / BM;
   const int q = w - mt_first * nt_n;
   // A long segment goes block by block of kMBlock m-tiles (the last block may be shorter): an activation panel's
@@ -131,7 +136,7 @@ __device__ __forceinline__ void load_tile(const GemmArgs& g, const Route& rt, in
   tr.n0 = (rem / bm) * BN;
   tr.row0 = s0 + (b * kMBlock + rem % bm) * BM;
   tr.rows = min(BM, s1 - tr.row0);
-  const size_t slot_base = (size_t)rt.seg_slot[seg] * g.slot_stride;
+  const size_t slot_base = (size_t)uniform(rt.seg_slot[seg]) * g.slot_stride;
   tr.Wb = g.pool + slot_base + g.w_off + (size_t)tr.n0 * (size_t)(g.k * 2);
   tr.bias = reinterpret_cast<const uint16_t*>(g.pool + slot_base + g.b_off);
 #pragma unroll
@@ -162,14 +167,14 @@ template <int NW, int EPI, bool OUT_F32, bool RESID_F32, bool HAS_C2>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
 void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int WTM = Geo<NW>::WTM, TM = Geo<NW>::TM, LD = Geo<NW>::LD, WAVE_SLICE = Geo<NW>::WAVE_SLICE;
+  constexpr int WTM = Geo<NW>::WTM, TM = Geo<NW>::TM, FWB = Geo<NW>::FWB, LD = Geo<NW>::LD, WAVE_SLICE = Geo<NW>::WAVE_SLICE;
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int l32 = lane & 31, lh = lane >> 5;
+  const int l16 = lane & 15, lq = lane >> 4;
   const int wm = wave >> 1, wn = wave & 1;
   const int KT = g.k / BK;
-  const char* Ab = reinterpret_cast<const char*>(g.A);
+  const buffer_t a_buf = buffer_at(reinterpret_cast<const char*>(g.A) - 3072);
 
   // ---- this workgroup's tiles: XCD x (workgroups are dealt to XCDs round robin) owns the
   // contiguous range [x per_xcd, (x+1) per_xcd).  A workgroup's first two tiles are fixed
@@ -203,14 +208,14 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
     b_off[j] = (uint32_t)row * (uint32_t)(g.k * 2) + (((lane & 7) ^ swz_w(row)) << 4) + (3072 - (j & 3) * 1024);
   }
 
-  // ---- fragment read offsets inside a stage slot for the four k-steps of a stage
-  // (k-step ks reads chunk (2 ks + lh) ^ swizzle: that is the k-step 0 offset with ks << 5 XORed in)
+  // ---- fragment read offsets inside a stage slot for the two k-steps of a stage
+  // (k-step ks reads chunk (4 ks + lq) ^ swizzle: that is the k-step 0 offset with ks << 6 XORed in)
   int fx_base, fw_base;
   {
-    const int rx = wm * WTM + l32;                       // + 32 i: swizzle unchanged
-    const int rw = wn * WTN + perm_w(l32);               // + 32 j: swizzle unchanged
-    fx_base = rx * ROW_BYTES + ((lh ^ swz_a(rx)) << 4);
-    fw_base = W_RING + rw * ROW_BYTES + ((lh ^ swz_w(rw)) << 4);
+    const int rx = wm * WTM + l16;                       // + 16 i: swizzle unchanged
+    const int rw = wn * WTN + perm_w(l16);               // + 64 (j / 4) + 4 (j % 4): swizzle unchanged
+    fx_base = rx * ROW_BYTES + ((lq ^ swz_a(rx)) << 4);
+    fw_base = W_RING + rw * ROW_BYTES + ((lq ^ swz_w(rw)) << 4);
   }
 
   // Ring bookkeeping (uniform): a_rd / w_rd are the byte offsets of the slots that hold the stage being multiplied.
@@ -218,95 +223,95 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
   // of KT or more means a stage of the next tile (for the last tile: an in-bounds re-read of its own first stages that
   // nobody consumes).  Needs KT >= 3, so that the copies never reach the tile after next.
   int a_rd = 0, w_rd = 0;
-  // Copies FROM .. FROM + COUNT - 1 of a wavefront's slice (1 KB each).  Four in a row share one LDS base (one M0 write);
-  // the instruction offset j KB that separates them applies to the global address too, so the lane offsets carry
-  // 3072 - j KB and the uniform base pointer -3072.
-#define HMI_COPY(SRC, VOFF, SLOT_OFF, FROM, COUNT)                                                \
+  // Copies FROM .. FROM + COUNT - 1 of a wavefront's slice (1 KB each), from buffer SRC (uniform, of which the offset SOFF is), by
+  // buffer loads: a global load to LDS counts among the LDS operations too, out of order, so that any wait for a fragment would
+  // be one for all of them.  Four in a row share one LDS base (one M0 write); the instruction offset j KB that separates them
+  // applies to the global address too, so the lane offsets carry 3072 - j KB and the buffers begin 3072 bytes early.
+#define HMI_COPY(SRC, SOFF, VOFF, SLOT_OFF, FROM, COUNT)                                          \
   {                                                                                               \
-    const char* src_ = (SRC) - 3072;                                                              \
     _Pragma("unroll") for (int j_ = (FROM); j_ < (FROM) + (COUNT); ++j_) {                        \
       lds_ptr_t dst_ = (lds_ptr_t)(smem + (SLOT_OFF) + wave * WAVE_SLICE + (j_ / 4) * 4096);      \
-      if ((j_ & 3) == 0) __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 0, 0);         \
-      else if ((j_ & 3) == 1) __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 1024, 0); \
-      else if ((j_ & 3) == 2) __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 2048, 0); \
-      else __builtin_amdgcn_global_load_lds((glb_ptr_t)(src_ + (VOFF)[j_]), dst_, 16, 3072, 0);   \
+      if ((j_ & 3) == 0) copy_to_lds<0>(SRC, dst_, (VOFF)[j_], SOFF);                             \
+      else if ((j_ & 3) == 1) copy_to_lds<1024>(SRC, dst_, (VOFF)[j_], SOFF);                     \
+      else if ((j_ & 3) == 2) copy_to_lds<2048>(SRC, dst_, (VOFF)[j_], SOFF);                     \
+      else copy_to_lds<3072>(SRC, dst_, (VOFF)[j_], SOFF);                                        \
     }                                                                                             \
   }
   static_assert(LD % 4 == 0, "HMI_COPY addresses the copies in groups of four");
 
-  bf16x8 fx[2][TM], fw[2][TN];
-  f32x16 acc[TM][TN];
+  bf16x8 fx[TM], fw[FWB][TN];
+  f32x4 acc[TM][TN];
 
-  // loads the MFMA fragments of k-step KS of the stage in slots a_rd / w_rd into register buffer B
-#define HMI_READ_FRAGS(B, KS)                                                                     \
-  {                                                                                               \
-    const unsigned char* xa_ = smem + a_rd + (fx_base ^ ((KS) << 5));                             \
-    const unsigned char* wa_ = smem + w_rd + (fw_base ^ ((KS) << 5));                             \
-    _Pragma("unroll") for (int i = 0; i < TM; ++i) fx[B][i] = *reinterpret_cast<const bf16x8*>(xa_ + i * 32 * ROW_BYTES); \
-    _Pragma("unroll") for (int j = 0; j < TN; ++j) fw[B][j] = *reinterpret_cast<const bf16x8*>(wa_ + j * 32 * ROW_BYTES); \
-  }
-#define HMI_MFMAS(B)                                                                              \
-  _Pragma("unroll") for (int i = 0; i < TM; ++i)                                                  \
-    _Pragma("unroll") for (int j = 0; j < TN; ++j)                                                \
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[B][j], fx[B][i], acc[i][j], 0, 0, 0);
+  // MFMA fragments of k-step KS of the stage in slots A_SLOT / W_SLOT
+#define HMI_READ_X(I, A_SLOT, KS)                                                                 \
+  fx[I] = *reinterpret_cast<const bf16x8*>(smem + (A_SLOT) + (fx_base ^ ((KS) << 6)) + (I) * 16 * ROW_BYTES);
+#define HMI_READ_W(B, J, W_SLOT, KS)                                                              \
+  fw[B][J] = *reinterpret_cast<const bf16x8*>(smem + (W_SLOT) + (fw_base ^ ((KS) << 6)) + ((J) >> 2) * 64 * ROW_BYTES + ((J) & 3) * 4 * ROW_BYTES);
 
-  // scheduling of a k-step: each fragment read of the next k-step goes behind one MFMA of this one (the wait for this
-  // k-step's fragments then comes before any new read), and C copies are spread over the MFMAs that are left
-#define HMI_SCHED_KSTEP(C)                                                                        \
-  _Pragma("unroll") for (int z_ = 0; z_ < TM + TN; ++z_) {                                        \
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                            \
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                            \
-  }                                                                                               \
-  _Pragma("unroll") for (int z_ = 0; z_ < (C); ++z_) {                                            \
-    __builtin_amdgcn_sched_group_barrier(0x008, (TM * TN - TM - TN) / ((C) ? (C) : 1), 0);        \
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                            \
-  }                                                                                               \
-  if ((C) == 0) __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - TM - TN, 0);                \
-  __builtin_amdgcn_sched_barrier(0);
+  // The products of MFMA rows R0 .. R1 - 1 of the k-step whose fragments are in fx and fw[B], in this order, and between them
+  //   * the reads of k-step KS of slots A_SLOT / W_SLOT, whose fragments take the place of this one's as soon as each has been
+  //     used for the last time (RD = 1): activations behind their row, weights behind the last row's products, which are eight
+  //     MFMAs and the other wavefront's ahead of their next use.  With one wavefront per SIMD that is too short: weights have a
+  //     second buffer there (fw[NB]) and are read two a row from row 1 on;
+  //   * COPIES copies, evenly: COPY(c) is the c-th.
+#define HMI_ROWS(B, NB, R0, R1, RD, A_SLOT, W_SLOT, KS, COPIES, COPY)                             \
+  _Pragma("unroll") for (int i = (R0); i < (R1); ++i)                                             \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j) {                                              \
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[B][j], fx[i], acc[i][j], 0, 0, 0);   \
+      if (RD) {                                                                                   \
+        if (FWB == 1 && i == TM - 1) HMI_READ_W(0, j, W_SLOT, KS)                                 \
+        if (FWB == 2 && i >= 1 && i <= TN / 2 && (j == 2 || j == 5)) HMI_READ_W((NB) % FWB, ((i - 1) * 2 + (j == 5)) % TN, W_SLOT, KS) \
+        if (j == TN - 1) HMI_READ_X(i, A_SLOT, KS)                                                \
+      }                                                                                           \
+      {                                                                                           \
+        constexpr int N_ = ((R1) - (R0)) * TN;                                                    \
+        const int at_ = (i - (R0)) * TN + j, c0_ = (2 * at_ * (COPIES) + N_) / (2 * N_), c1_ = (2 * (at_ + 1) * (COPIES) + N_) / (2 * N_); \
+        if (c1_ > c0_ && c0_ < (COPIES)) COPY(c0_)                                                \
+      }                                                                                           \
+      __builtin_amdgcn_sched_barrier(0);                                                          \
+    }
 
-  // accumulators of a tile start at its bias: lane half h of MFMA tile j holds columns
-  // n0 + wn*128 + j*32 + 16 h + (0..15), the same for both m-tiles.
+  // accumulators of a tile start at its bias: lane quarter q of the MFMA tiles 4 h .. 4 h + 3 holds columns
+  // n0 + wn * 128 + 64 h + 16 q + (0..15), the same for all rows.
 #define HMI_INIT_ACC(TR)                                                                          \
-  _Pragma("unroll") for (int j = 0; j < TN; ++j) {                                                \
-    const int col0_ = (TR).n0 + wn * WTN + j * 32 + 16 * lh;                                      \
+  _Pragma("unroll") for (int h = 0; h < TN / 4; ++h) {                                            \
+    const int col0_ = (TR).n0 + wn * WTN + h * 64 + 16 * lq;                                      \
     const u32x4 b0_ = *reinterpret_cast<const u32x4*>((TR).bias + col0_);                         \
     const u32x4 b1_ = *reinterpret_cast<const u32x4*>((TR).bias + col0_ + 8);                     \
-    _Pragma("unroll") for (int q = 0; q < 4; ++q) {                                               \
-      acc[0][j][2 * q] = bf2f(b0_[q] & 0xffffu);      acc[0][j][2 * q + 1] = bf2f(b0_[q] >> 16);  \
-      acc[0][j][8 + 2 * q] = bf2f(b1_[q] & 0xffffu);  acc[0][j][8 + 2 * q + 1] = bf2f(b1_[q] >> 16); \
+    _Pragma("unroll") for (int q = 0; q < 2; ++q) {                                               \
+      acc[0][4 * h + q] = f32x4{bf2f(b0_[2 * q] & 0xffffu), bf2f(b0_[2 * q] >> 16), bf2f(b0_[2 * q + 1] & 0xffffu), bf2f(b0_[2 * q + 1] >> 16)}; \
+      acc[0][4 * h + 2 + q] = f32x4{bf2f(b1_[2 * q] & 0xffffu), bf2f(b1_[2 * q] >> 16), bf2f(b1_[2 * q + 1] & 0xffffu), bf2f(b1_[2 * q + 1] >> 16)}; \
     }                                                                                             \
-    _Pragma("unroll") for (int i = 1; i < TM; ++i) acc[i][j] = acc[0][j];                         \
-  }
+  }                                                                                               \
+  _Pragma("unroll") for (int i = 1; i < TM; ++i)                                                  \
+    _Pragma("unroll") for (int j = 0; j < TN; ++j) acc[i][j] = acc[0][j];
 
-  // One stage.  A wavefront's L1 takes 66 bytes a clock for the whole compute unit, a 1 KB copy every 16 clocks, and a
-  // wavefront that issues them faster stands still with its MFMAs: the copies are spread.  The weights of stage s + 2 go
-  // between the products of k-steps 0 and 1 (into the slot of stage s - 1), the activations of stage s + 2 between those of
-  // k-step 3, behind the barrier that frees the slot of stage s.  Activation copies have three k-steps to land, weight
-  // copies six.  MODE says where they come from:
+  // One stage: two k-steps of 32, and a barrier behind the first row of the second one's products, where this wavefront has all
+  // of the stage in registers.  A wavefront's L1 takes 66 bytes a clock for the whole compute unit, a 1 KB copy every 16 clocks,
+  // and a wavefront that issues them faster stands still with its MFMAs: the copies are spread.  The weights of stage s + 2 go
+  // between the products of the first k-step (into the slot of stage s - 1), the activations of stage s + 2 between those of
+  // the second one, behind the barrier that frees the slot of stage s.
+  // MODE says where they come from:
   //   0: the current tile (s <= KT-4)
   //   1: (s = KT-3) the current tile; the tile claimed for the round after next goes into the mailbox
   //   2: (s = KT-2) the next tile's stage 0; its weights only behind the barrier, so that nothing is in flight in front of it
   //      and the mailbox store is done
   //   3: (s = KT-1) the next tile's weight stage 1; no activations: the freed slots serve the epilogue first
+#define HMI_COPY_W(C) HMI_COPY(w_buf_, w_at_, b_off, W_RING + wf_, C, 1)
+#define HMI_COPY_A(C) HMI_COPY(a_buf, a_at_, a_off_, fa_, C, 1)
+#define HMI_COPY_AW(C) { if ((C) < LD) { HMI_COPY(a_buf, a_at_, a_off_, fa_, (C) % LD, 1) } else { HMI_COPY(w_buf_, 0, b_off, W_RING + wf_, (C) % LD, 1) } }
+#define HMI_COPY_NONE(C) {}
 #define HMI_ITER(MODE)                                                                            \
   {                                                                                               \
     const int wf_ = w_rd == 0 ? (W_STAGES - 1) * STAGE_BYTES : w_rd - STAGE_BYTES;   /* the slot of stage s - 1, and of s + 2 */ \
-    const char* ws_ = (MODE) < 2 ? cur.Wb + (s + 2) * ROW_BYTES : nxt.Wb + ROW_BYTES;             \
-    constexpr int WC = (MODE) == 2 ? 0 : LD / 2;                                                  \
+    const buffer_t w_buf_ = buffer_at(((MODE) < 2 ? cur.Wb : nxt.Wb) - 3072);                \
+    const int w_at_ = (MODE) < 2 ? (s + 2) * ROW_BYTES : ROW_BYTES;                               \
+    constexpr int WC = (MODE) == 2 ? 0 : LD;                                                      \
     if (wave_active) {                                                                            \
-      HMI_READ_FRAGS(1, 1)                                                                        \
-      HMI_COPY(ws_, b_off, W_RING + wf_, 0, WC)                                                   \
-      HMI_MFMAS(0)                                                                                \
-      HMI_SCHED_KSTEP(WC)                                                                         \
-      HMI_READ_FRAGS(0, 2)                                                                        \
-      HMI_COPY(ws_, b_off, W_RING + wf_, LD / 2, WC)                                              \
-      HMI_MFMAS(1)                                                                                \
-      HMI_SCHED_KSTEP(WC)                                                                         \
-      HMI_READ_FRAGS(1, 3)                                                                        \
-      HMI_MFMAS(0)                                                                                \
-      HMI_SCHED_KSTEP(0)                                                                          \
+      HMI_ROWS(0, 1, 0, TM, 1, a_rd, w_rd, 1, WC, HMI_COPY_W)                                     \
+      HMI_ROWS(FWB - 1, 0, 0, 1, 0, 0, 0, 0, 0, HMI_COPY_NONE)                                    \
     } else {                                                                                      \
-      HMI_COPY(ws_, b_off, W_RING + wf_, 0, 2 * WC)                                               \
+      HMI_COPY(w_buf_, w_at_, b_off, W_RING + wf_, 0, WC)                                                   \
     }                                                                                             \
     HMI_WAIT_LGKMCNT0();          /* this wavefront no longer reads stage s from LDS */           \
     if ((MODE) == 2) HMI_WAIT_VMCNT(0);              /* its copies of stage s+1 (both operands) have landed: nothing newer, */ \
@@ -320,25 +325,17 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
     w_rd = w_rd == (W_STAGES - 1) * STAGE_BYTES ? 0 : w_rd + STAGE_BYTES;                         \
     if ((MODE) == 3) {                                                                            \
       patch_a = fa_; patch_w = fw_;                                                               \
-      if (wm * WTM < nxt.rows) HMI_READ_FRAGS(0, 0)                                               \
-      __builtin_amdgcn_sched_barrier(0);                                                          \
-      if (wave_active) { HMI_MFMAS(1) }                                                           \
+      if (wave_active) { HMI_ROWS(FWB - 1, 0, 1, TM, 0, 0, 0, 0, 0, HMI_COPY_NONE) }              \
     } else {                                                                                      \
-      constexpr int AC = LD, WB = (MODE) == 2 ? LD : 0;                                           \
+      const int a_at_ = (MODE) == 2 ? 0 : (s + 2) * ROW_BYTES;                                    \
+      const uint32_t* const a_off_ = (MODE) == 2 ? nxt.a_off : cur.a_off;                         \
       if (wave_active) {                                                                          \
-        /* first fragments of stage s+1, then the last k-step's MFMAs with the copies between them */ \
-        HMI_READ_FRAGS(0, 0)                                                                      \
-        if ((MODE) == 2) { HMI_COPY(Ab, nxt.a_off, fa_, 0, AC) HMI_COPY(nxt.Wb, b_off, W_RING + wf_, 0, WB) } \
-        else HMI_COPY(Ab + (s + 2) * ROW_BYTES, cur.a_off, fa_, 0, AC)                            \
-        HMI_MFMAS(1)                                                                              \
-        __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);                                  \
-        _Pragma("unroll") for (int z_ = 0; z_ < AC + WB; ++z_) {                                  \
-          __builtin_amdgcn_sched_group_barrier(0x008, (MODE) == 2 ? 1 : 2, 0);                    \
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                      \
-        }                                                                                         \
+        HMI_READ_X(0, a_rd, 0)                                                                    \
+        if ((MODE) == 2) HMI_ROWS(FWB - 1, 0, 1, TM, 1, a_rd, w_rd, 0, 2 * LD, HMI_COPY_AW)       \
+        else HMI_ROWS(FWB - 1, 0, 1, TM, 1, a_rd, w_rd, 0, LD, HMI_COPY_A)                        \
       } else {                                                                                    \
-        if ((MODE) == 2) { HMI_COPY(Ab, nxt.a_off, fa_, 0, AC) HMI_COPY(nxt.Wb, b_off, W_RING + wf_, 0, WB) } \
-        else HMI_COPY(Ab + (s + 2) * ROW_BYTES, cur.a_off, fa_, 0, AC)                            \
+        HMI_COPY(a_buf, a_at_, a_off_, fa_, 0, LD)                                                \
+        if ((MODE) == 2) HMI_COPY(w_buf_, 0, b_off, W_RING + wf_, 0, LD)                          \
       }                                                                                           \
     }                                                                                             \
     __builtin_amdgcn_sched_barrier(0);                                                            \
@@ -346,20 +343,28 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
 
   // ---- prologue of the first tile: stages 0 and 1 in the order in which the steady state issues them
   HMI_INIT_ACC(cur)
-  HMI_COPY(cur.Wb, b_off, W_RING, 0, LD)
-  HMI_COPY(Ab, cur.a_off, 0, 0, LD)
-  HMI_COPY(cur.Wb + ROW_BYTES, b_off, W_RING + STAGE_BYTES, 0, LD)
-  HMI_COPY(Ab + ROW_BYTES, cur.a_off, STAGE_BYTES, 0, LD)
+  {
+    const buffer_t w_buf = buffer_at(cur.Wb - 3072);
+    HMI_COPY(w_buf, 0, b_off, W_RING, 0, LD)
+    HMI_COPY(a_buf, 0, cur.a_off, 0, 0, LD)
+    HMI_COPY(w_buf, ROW_BYTES, b_off, W_RING + STAGE_BYTES, 0, LD)
+    HMI_COPY(a_buf, ROW_BYTES, cur.a_off, STAGE_BYTES, 0, LD)
+  }
   HMI_WAIT_VMCNT(2 * LD);
   __builtin_amdgcn_s_barrier();
   bool wave_active = wm * WTM < cur.rows;
-  if (wave_active) HMI_READ_FRAGS(0, 0)
   int patch_a = 0, patch_w = 0;
 
   for (;;) {
     // ================= main loop of the current tile =================
     {
       int s = 0;
+      if (wave_active) {                                       // the first k-step's fragments
+#pragma unroll
+        for (int j = 0; j < TN; ++j) HMI_READ_W(0, j, w_rd, 0)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) HMI_READ_X(i, a_rd, 0)
+      }
       for (; s < KT - 3; ++s) HMI_ITER(0)
       HMI_ITER(1)
       HMI_ITER(2)
@@ -385,20 +390,19 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
       constexpr int COLS_PER_CHUNK = STAGE_F32 ? 4 : 8;
       const int c = lane & 15;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int mbase = wm * WTM + i * 32;
+      for (int ib = 0; ib < TM / 2; ++ib) {                    // 32 rows: MFMA rows 2 ib and 2 ib + 1
+        const int mbase = wm * WTM + ib * 32;
         if (mbase < cur.rows) {
           if (NW == 4) {   // the row blocks still to come stay where the MFMAs left them (the AGPR half) until their turn
 #pragma unroll
-            for (int i2 = i + 1; i2 < TM; ++i2)
+            for (int i2 = 2 * ib + 2; i2 < TM; ++i2)
 #pragma unroll
               for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i2][j]));
           }
           const int rmax = min(31, cur.rows - 1 - mbase);     // last valid row of this 32-row block
-          unsigned char* wrow = ((l32 & 16) ? patch1 : patch0) + (l32 & 15) * 256;
           uint32_t orow[8];                                   // row of C for each of this lane's 8 pieces
 #pragma unroll
-          for (int it = 0; it < 8; ++it) orow[it] = (uint32_t)__shfl(cur.out_row[i >> 1], (i & 1) * 32 + min(it * 4 + (lane >> 4), rmax), 64);
+          for (int it = 0; it < 8; ++it) orow[it] = (uint32_t)__shfl(cur.out_row[ib >> 1], (ib & 1) * 32 + min(it * 4 + (lane >> 4), rmax), 64);
 #pragma unroll
           for (int pass = 0; pass < PASSES; ++pass) {
             const int col = cur.n0 + wn * WTN + pass * 64 + c * COLS_PER_CHUNK;
@@ -413,36 +417,31 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
               }
             }
             // accumulator layout -> patch
-            if (STAGE_F32) {
 #pragma unroll
-              for (int jj = 0; jj < 2; ++jj) {
-                const int j = pass * 2 + jj;
+            for (int half = 0; half < 2; ++half) {
+              unsigned char* wrow = (half ? patch1 : patch0) + l16 * 256;
+              if (STAGE_F32) {
 #pragma unroll
-                for (int qd = 0; qd < 4; ++qd) {
-                  f32x4 o = {acc[i][j][4 * qd], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]};
+                for (int jt = 0; jt < 4; ++jt) {
+                  f32x4 o = acc[2 * ib + half][pass * 4 + jt];
                   if (EPI == EPI_BIAS_GELU) { o[0] = gelu_poly(o[0]); o[1] = gelu_poly(o[1]); o[2] = gelu_poly(o[2]); o[3] = gelu_poly(o[3]); }
                   else if (EPI == EPI_BIAS_RELU) { o[0] = fmaxf(o[0], 0.f); o[1] = fmaxf(o[1], 0.f); o[2] = fmaxf(o[2], 0.f); o[3] = fmaxf(o[3], 0.f); }
-                  const int c0 = jj * 8 + lh * 4 + qd;
-                  *reinterpret_cast<f32x4*>(wrow + ((c0 ^ (l32 & 15)) << 4)) = o;
+                  *reinterpret_cast<f32x4*>(wrow + (((lq * 4 + jt) ^ l16) << 4)) = o;
                 }
-              }
-            } else {
+              } else {
 #pragma unroll
-              for (int j = 0; j < TN; ++j) {
-                u32x4 h0, h1;
+                for (int jj = 0; jj < TN; jj += 2) {           // eight columns
+                  u32x4 h;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  float v0 = acc[i][j][2 * e], v1 = acc[i][j][2 * e + 1], v2 = acc[i][j][8 + 2 * e], v3 = acc[i][j][8 + 2 * e + 1];
-                  if (EPI == EPI_BIAS_GELU) {
-                    h0[e] = pack_bf16(gelu_poly(v0), gelu_poly(v1)); h1[e] = pack_bf16(gelu_poly(v2), gelu_poly(v3));
-                  } else {
-                    if (EPI == EPI_BIAS_RELU) { v0 = fmaxf(v0, 0.0f); v1 = fmaxf(v1, 0.0f); v2 = fmaxf(v2, 0.0f); v3 = fmaxf(v3, 0.0f); }
-                    h0[e] = pack_bf16(v0, v1); h1[e] = pack_bf16(v2, v3);
+                  for (int e = 0; e < 4; ++e) {
+                    float v0 = acc[2 * ib + half][jj + (e >> 1)][2 * (e & 1)], v1 = acc[2 * ib + half][jj + (e >> 1)][2 * (e & 1) + 1];
+                    if (EPI == EPI_BIAS_GELU) { v0 = gelu_poly(v0); v1 = gelu_poly(v1); }
+                    else if (EPI == EPI_BIAS_RELU) { v0 = fmaxf(v0, 0.0f); v1 = fmaxf(v1, 0.0f); }
+                    h[e] = pack_bf16(v0, v1);
                   }
+                  const int c0 = (jj >> 2) * 8 + lq * 2 + ((jj >> 1) & 1);
+                  *reinterpret_cast<u32x4*>(wrow + ((c0 ^ l16) << 4)) = h;
                 }
-                const int c0 = j * 4 + lh * 2;
-                *reinterpret_cast<u32x4*>(wrow + ((c0 ^ (l32 & 15)) << 4)) = h0;
-                *reinterpret_cast<u32x4*>(wrow + (((c0 + 1) ^ (l32 & 15)) << 4)) = h1;
               }
             }
             HMI_WAIT_LGKMCNT0();
@@ -487,7 +486,7 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
     // the copies that were held back at the last stage (the new tile's activation stage 1) go into the slot the epilogue
     // just used, as its weight stage 2 will in its first stage; a wavefront's copies fill only its own slice of a slot,
     // which is its own staging patch: no barrier
-    HMI_COPY(Ab + ROW_BYTES, cur.a_off, patch_a, 0, LD)
+    HMI_COPY(a_buf, ROW_BYTES, cur.a_off, patch_a, 0, LD)
     load_tile(g, rt, w_next < w_end ? w_next : w, wave, lane, nxt);
   }
   HMI_WAIT_VMCNT(0);   // none of this workgroup's copies may outlive it
