@@ -40,8 +40,11 @@
 //     order): a lane ends up with one row of C and 16 consecutive columns per four MFMA tiles;
 //     bias is folded into the accumulator initialisation.  For the stores each wavefront
 //     transposes its results through the part of the two idle ring slots that only its
-//     own copies overwrite (no barrier), so that 16 or 32 consecutive lanes write one
-//     row's 256 or 512 contiguous bytes: full-line requests again.
+//     own copies overwrite (no barrier), so that 16 consecutive lanes write 256 contiguous
+//     bytes of a row: full-line requests again.  Units of 16 rows in turn, one written while the one before it
+//     is read (eight wavefronts; in blocks of 32 rows with a wait between, FFN1 of 65 536 rows 1.5 % longer).
+// What bounds it now: under the launches the clock is 1.9 GHz (2.4 under a copy, 1.7 under the vendor's 8192^3), so what a launch
+// takes is its energy; a stage of products takes 2 640 clocks for 2 048 of matrix instructions, waits of 50 to 100 among them.
 #include "hmi_kernels.h"
 
 #include "gelu.h"
@@ -253,7 +256,9 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
   //     used for the last time (RD = 1): activations behind their row, weights behind the last row's products, which are eight
   //     MFMAs and the other wavefront's ahead of their next use.  With one wavefront per SIMD that is too short: weights have a
   //     second buffer there (fw[NB]) and are read two a row from row 1 on;
-  //   * COPIES copies, evenly: COPY(c) is the c-th.
+  //   * COPIES copies, evenly: COPY(c) is the c-th.  With two wavefronts per SIMD those of k-step 1's rows (the activations, which
+  //     have to be there a stage later) between the first third of the products: dense QKV and output projection of 65 536
+  //     rows 307 -> 288 us together.
 #define HMI_ROWS(B, NB, R0, R1, RD, A_SLOT, W_SLOT, KS, COPIES, COPY)                             \
   _Pragma("unroll") for (int i = (R0); i < (R1); ++i)                                             \
     _Pragma("unroll") for (int j = 0; j < TN; ++j) {                                              \
@@ -264,7 +269,7 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
         if (j == TN - 1) HMI_READ_X(i, A_SLOT, KS)                                                \
       }                                                                                           \
       {                                                                                           \
-        constexpr int N_ = ((R1) - (R0)) * TN;                                                    \
+        constexpr int N_ = ((R1) - (R0)) * TN / (NW == 8 && (KS) == 0 ? 3 : 1);                   \
         const int at_ = (i - (R0)) * TN + j, c0_ = (2 * at_ * (COPIES) + N_) / (2 * N_), c1_ = (2 * (at_ + 1) * (COPIES) + N_) / (2 * N_); \
         if (c1_ > c0_ && c0_ < (COPIES)) COPY(c0_)                                                \
       }                                                                                           \
@@ -298,20 +303,20 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
   //      and the mailbox store is done
   //   3: (s = KT-1) the next tile's weight stage 1; no activations: the freed slots serve the epilogue first
 #define HMI_COPY_W(C) HMI_COPY(w_buf_, w_at_, b_off, W_RING + wf_, C, 1)
-#define HMI_COPY_A(C) HMI_COPY(a_buf, a_at_, a_off_, fa_, C, 1)
-#define HMI_COPY_AW(C) { if ((C) < LD) { HMI_COPY(a_buf, a_at_, a_off_, fa_, (C) % LD, 1) } else { HMI_COPY(w_buf_, 0, b_off, W_RING + wf_, (C) % LD, 1) } }
+#define HMI_COPY_A(C) HMI_COPY(a_buf, (s + 2) * ROW_BYTES, cur.a_off, fa_, C, 1)
+#define HMI_COPY_AW(C) { if ((C) < LD) { HMI_COPY(a_buf, 0, nxt.a_off, fa_, (C) % LD, 1) } else { HMI_COPY(w_buf_, 0, b_off, W_RING + wf_, (C) % LD, 1) } }
 #define HMI_COPY_NONE(C) {}
 #define HMI_ITER(MODE)                                                                            \
   {                                                                                               \
     const int wf_ = w_rd == 0 ? (W_STAGES - 1) * STAGE_BYTES : w_rd - STAGE_BYTES;   /* the slot of stage s - 1, and of s + 2 */ \
-    const buffer_t w_buf_ = buffer_at(((MODE) < 2 ? cur.Wb : nxt.Wb) - 3072);                \
+    const buffer_t w_buf_ = buffer_at(((MODE) < 2 ? cur.Wb : nxt.Wb) - 3072);                     \
     const int w_at_ = (MODE) < 2 ? (s + 2) * ROW_BYTES : ROW_BYTES;                               \
     constexpr int WC = (MODE) == 2 ? 0 : LD;                                                      \
     if (wave_active) {                                                                            \
       HMI_ROWS(0, 1, 0, TM, 1, a_rd, w_rd, 1, WC, HMI_COPY_W)                                     \
       HMI_ROWS(FWB - 1, 0, 0, 1, 0, 0, 0, 0, 0, HMI_COPY_NONE)                                    \
     } else {                                                                                      \
-      HMI_COPY(w_buf_, w_at_, b_off, W_RING + wf_, 0, WC)                                                   \
+      HMI_COPY(w_buf_, w_at_, b_off, W_RING + wf_, 0, WC)                                         \
     }                                                                                             \
     HMI_WAIT_LGKMCNT0();          /* this wavefront no longer reads stage s from LDS */           \
     if ((MODE) == 2) HMI_WAIT_VMCNT(0);              /* its copies of stage s+1 (both operands) have landed: nothing newer, */ \
@@ -327,15 +332,13 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
       patch_a = fa_; patch_w = fw_;                                                               \
       if (wave_active) { HMI_ROWS(FWB - 1, 0, 1, TM, 0, 0, 0, 0, 0, HMI_COPY_NONE) }              \
     } else {                                                                                      \
-      const int a_at_ = (MODE) == 2 ? 0 : (s + 2) * ROW_BYTES;                                    \
-      const uint32_t* const a_off_ = (MODE) == 2 ? nxt.a_off : cur.a_off;                         \
       if (wave_active) {                                                                          \
         HMI_READ_X(0, a_rd, 0)                                                                    \
         if ((MODE) == 2) HMI_ROWS(FWB - 1, 0, 1, TM, 1, a_rd, w_rd, 0, 2 * LD, HMI_COPY_AW)       \
         else HMI_ROWS(FWB - 1, 0, 1, TM, 1, a_rd, w_rd, 0, LD, HMI_COPY_A)                        \
       } else {                                                                                    \
-        HMI_COPY(a_buf, a_at_, a_off_, fa_, 0, LD)                                                \
-        if ((MODE) == 2) HMI_COPY(w_buf_, 0, b_off, W_RING + wf_, 0, LD)                          \
+        if ((MODE) == 2) { HMI_COPY(a_buf, 0, nxt.a_off, fa_, 0, LD) HMI_COPY(w_buf_, 0, b_off, W_RING + wf_, 0, LD) } \
+        else HMI_COPY(a_buf, (s + 2) * ROW_BYTES, cur.a_off, fa_, 0, LD)                          \
       }                                                                                           \
     }                                                                                             \
     __builtin_amdgcn_sched_barrier(0);                                                            \
@@ -372,107 +375,108 @@ void gemm_bf16_p256_kernel(GemmArgs g, Route rt, int total, int per_xcd) {
     }
 
     // ================= epilogue of the current tile =================
-    // Staging patch of this wavefront: the first 4 KB of its own slice of the two slots that stage KT-1
-    // occupied.  A row keeps its 16-byte chunk c at chunk position c ^ (row & 15).
-    // Rows past the end of a short tile are replaced by the tile's last row of the same
-    // 32-row block (same data to the same address: harmless), which keeps the code free
-    // of branches so that the loads and stores of a pass are issued back to back.
+    // Results cross LDS so that whole lines of C are read and written (straight from the accumulators, 64 bytes of a row at a
+    // time, launches took 6 to 10 % longer): units of 16 rows, 256 bytes of each (all 128 columns as bf16, or 64 of them as fp32),
+    // a patch of 4 KB a unit, of which a wavefront has as many as its own slices of the two slots hold that stage KT-1
+    // occupied.  A row keeps its 16-byte chunk c at chunk position c ^ row; read back, 16 lanes hold a row, 4 rows a step.
+    // While a unit is read the next one is written and later ones' residuals are on their way.  Results that get a residual added
+    // cross the patch in fp32 even if they are stored as bf16, so that they are rounded once, after the addition.
+    // Rows past the end of a short tile are copies of its last row, results and residuals too, and are stored where that is
+    // (same data to the same address: harmless).
     if (wave_active) {
-      unsigned char* patch0 = smem + patch_a + wave * WAVE_SLICE;
-      unsigned char* patch1 = smem + W_RING + patch_w + wave * WAVE_SLICE;
-      // The 8 KB patch holds 32 rows of 256 bytes (rows 0-15 in patch0, 16-31 in patch1): all
-      // 128 columns of an MFMA tile row as bf16, or 64 of them as fp32 (two passes).  After
-      // the transposition 16 lanes hold one row's 256 contiguous bytes, 4 rows per step.
-      // Results that get a residual added cross the patch in fp32 even if they are stored as
-      // bf16, so that they are rounded once, after the addition.
-      constexpr bool STAGE_F32 = OUT_F32 || EPI == EPI_BIAS_RESID;
-      constexpr int PASSES = STAGE_F32 ? 2 : 1;
-      constexpr int COLS_PER_CHUNK = STAGE_F32 ? 4 : 8;
-      const int c = lane & 15;
+      constexpr bool RESID = EPI == EPI_BIAS_RESID, STAGE_F32 = OUT_F32 || RESID;
+      constexpr int PASSES = STAGE_F32 ? 2 : 1, UNITS = TM * PASSES;
+      constexpr int AHEAD = RESID ? 2 : 1;                   // units whose residuals are asked for ahead (3 and 4 spill: 4 % longer)
+      const int c = lane & 15, rq = lane >> 4;
+      unsigned char* const slice_a = smem + patch_a + wave * WAVE_SLICE;
+      unsigned char* const slice_w = smem + W_RING + patch_w + wave * WAVE_SLICE;
+      const int put_at = l16 * 256 + (((STAGE_F32 ? lq * 4 : lq * 2) ^ l16) << 4), get_at = rq * 256 + ((c ^ rq) << 4);
+      const int col = cur.n0 + wn * WTN + c * (STAGE_F32 ? 4 : 8);
+      uint32_t orow[TM][4];
+      f32x4 rv32[RESID && RESID_F32 ? AHEAD + 1 : 1][4];
+      u32x2 rv16[RESID && !RESID_F32 ? AHEAD + 1 : 1][4];
+#define HMI_PATCH(U) (NW == 8 ? ((U) & 1 ? slice_w : slice_a) : ((U) & 2 ? slice_w : slice_a) + ((U) & 1) * 4096)
+#define HMI_UNIT_ROWS(U)                                                                          \
+  if ((U) % PASSES == 0) {                                                                        \
+    _Pragma("unroll") for (int it = 0; it < 4; ++it)                                              \
+      orow[(U) / PASSES][it] = (uint32_t)__shfl(cur.out_row[(U) / PASSES >> 2], ((U) / PASSES & 3) * 16 + it * 4 + rq, 64); \
+  }
+#define HMI_UNIT_RESID(U)                                                                         \
+  _Pragma("unroll") for (int it = 0; it < 4; ++it) {                                              \
+    const size_t at_ = (size_t)orow[(U) / PASSES][it] * g.ldr + col + (U) % PASSES * 64;          \
+    if constexpr (RESID_F32) rv32[(U) % (AHEAD + 1)][it] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.resid) + at_); \
+    else rv16[(U) % (AHEAD + 1)][it] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(g.resid) + at_); \
+  }
+#define HMI_UNIT_PUT(U)                                                                           \
+  _Pragma("unroll") for (int jt = 0; jt < 4; ++jt) {                                              \
+    if constexpr (STAGE_F32) {                                                                    \
+      *reinterpret_cast<f32x4*>(HMI_PATCH(U) + (put_at ^ (jt << 4))) = acc[(U) / PASSES][(U) % PASSES * 4 + jt]; \
+    } else {                                                                                      \
+      u32x4 h_;                                                                                   \
+      _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                             \
+        float v0 = acc[U][2 * jt + (e >> 1)][2 * (e & 1)], v1 = acc[U][2 * jt + (e >> 1)][2 * (e & 1) + 1]; \
+        if (EPI == EPI_BIAS_GELU) { v0 = gelu_poly(v0); v1 = gelu_poly(v1); }                     \
+        else if (EPI == EPI_BIAS_RELU) { v0 = fmaxf(v0, 0.0f); v1 = fmaxf(v1, 0.0f); }            \
+        h_[e] = pack_bf16(v0, v1);                                                                \
+      }                                                                                           \
+      *reinterpret_cast<u32x4*>(HMI_PATCH(U) + (put_at ^ ((((jt >> 1) << 3) | (jt & 1)) << 4))) = h_; \
+    }                                                                                             \
+  }
+      static_assert(EPI == EPI_BIAS_RESID || !OUT_F32, "fp32 results are sums with residuals");
 #pragma unroll
-      for (int ib = 0; ib < TM / 2; ++ib) {                    // 32 rows: MFMA rows 2 ib and 2 ib + 1
-        const int mbase = wm * WTM + ib * 32;
-        if (mbase < cur.rows) {
-          if (NW == 4) {   // the row blocks still to come stay where the MFMAs left them (the AGPR half) until their turn
+      for (int u = 0; u < AHEAD; ++u) {
+        HMI_UNIT_ROWS(u)
+        if constexpr (RESID) HMI_UNIT_RESID(u)
+      }
+      if (NW == 4) {       // the rows still to come stay where the MFMAs left them (the AGPR half) until their turn
 #pragma unroll
-            for (int i2 = 2 * ib + 2; i2 < TM; ++i2)
+        for (int i2 = 1; i2 < TM; ++i2)
 #pragma unroll
-              for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i2][j]));
-          }
-          const int rmax = min(31, cur.rows - 1 - mbase);     // last valid row of this 32-row block
-          uint32_t orow[8];                                   // row of C for each of this lane's 8 pieces
+          for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i2][j]));
+      }
+      HMI_UNIT_PUT(0)
 #pragma unroll
-          for (int it = 0; it < 8; ++it) orow[it] = (uint32_t)__shfl(cur.out_row[ib >> 1], (ib & 1) * 32 + min(it * 4 + (lane >> 4), rmax), 64);
+      for (int u = 0; u < UNITS; ++u) {
+        const int i = u / PASSES;
+        if (wm * WTM + i * 16 >= cur.rows) break;
+        u32x4 got[4];
 #pragma unroll
-          for (int pass = 0; pass < PASSES; ++pass) {
-            const int col = cur.n0 + wn * WTN + pass * 64 + c * COLS_PER_CHUNK;
-            // residuals first, so that they arrive while the results cross the patch
-            f32x4 rv32[(EPI == EPI_BIAS_RESID && RESID_F32) ? 8 : 1];
-            u32x2 rv16[(EPI == EPI_BIAS_RESID && !RESID_F32) ? 8 : 1];
-            if (EPI == EPI_BIAS_RESID) {
+        for (int it = 0; it < 4; ++it) got[it] = *reinterpret_cast<const u32x4*>(HMI_PATCH(u) + (get_at ^ (it << 6)) + it * 1024);
+        if (NW == 4) {
 #pragma unroll
-              for (int it = 0; it < 8; ++it) {
-                if (RESID_F32) rv32[it] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.resid) + (size_t)orow[it] * g.ldr + col);
-                else rv16[it] = *reinterpret_cast<const u32x2*>(reinterpret_cast<const uint16_t*>(g.resid) + (size_t)orow[it] * g.ldr + col);
-              }
+          for (int i2 = (u + 1) / PASSES + 1; i2 < TM; ++i2)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i2][j]));
+        }
+        if (u + 1 < UNITS) HMI_UNIT_PUT(u + 1)
+        if (u + AHEAD < UNITS) {
+          HMI_UNIT_ROWS(u + AHEAD)
+          if constexpr (RESID) HMI_UNIT_RESID(u + AHEAD)
+        }
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+          const size_t off = (size_t)orow[i][it] * g.ldc + col + u % PASSES * 64;
+          if constexpr (STAGE_F32) {
+            f32x4 v = __builtin_bit_cast(f32x4, got[it]);
+            if constexpr (RESID && RESID_F32) v += rv32[u % (AHEAD + 1)][it];
+            else if constexpr (RESID) {
+              const u32x2 r = rv16[u % (AHEAD + 1)][it];
+              v += f32x4{bf2f(r[0] & 0xffffu), bf2f(r[0] >> 16), bf2f(r[1] & 0xffffu), bf2f(r[1] >> 16)};
             }
-            // accumulator layout -> patch
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-              unsigned char* wrow = (half ? patch1 : patch0) + l16 * 256;
-              if (STAGE_F32) {
-#pragma unroll
-                for (int jt = 0; jt < 4; ++jt) {
-                  f32x4 o = acc[2 * ib + half][pass * 4 + jt];
-                  if (EPI == EPI_BIAS_GELU) { o[0] = gelu_poly(o[0]); o[1] = gelu_poly(o[1]); o[2] = gelu_poly(o[2]); o[3] = gelu_poly(o[3]); }
-                  else if (EPI == EPI_BIAS_RELU) { o[0] = fmaxf(o[0], 0.f); o[1] = fmaxf(o[1], 0.f); o[2] = fmaxf(o[2], 0.f); o[3] = fmaxf(o[3], 0.f); }
-                  *reinterpret_cast<f32x4*>(wrow + (((lq * 4 + jt) ^ l16) << 4)) = o;
-                }
-              } else {
-#pragma unroll
-                for (int jj = 0; jj < TN; jj += 2) {           // eight columns
-                  u32x4 h;
-#pragma unroll
-                  for (int e = 0; e < 4; ++e) {
-                    float v0 = acc[2 * ib + half][jj + (e >> 1)][2 * (e & 1)], v1 = acc[2 * ib + half][jj + (e >> 1)][2 * (e & 1) + 1];
-                    if (EPI == EPI_BIAS_GELU) { v0 = gelu_poly(v0); v1 = gelu_poly(v1); }
-                    else if (EPI == EPI_BIAS_RELU) { v0 = fmaxf(v0, 0.0f); v1 = fmaxf(v1, 0.0f); }
-                    h[e] = pack_bf16(v0, v1);
-                  }
-                  const int c0 = (jj >> 2) * 8 + lq * 2 + ((jj >> 1) & 1);
-                  *reinterpret_cast<u32x4*>(wrow + ((c0 ^ l16) << 4)) = h;
-                }
-              }
-            }
-            HMI_WAIT_LGKMCNT0();
-            // patch -> rows of C
-#pragma unroll
-            for (int it = 0; it < 8; ++it) {
-              const int r = min(it * 4 + (lane >> 4), rmax);
-              const unsigned char* rrow = ((r & 16) ? patch1 : patch0) + (r & 15) * 256;
-              const size_t off = (size_t)orow[it] * g.ldc + col;
-              if (STAGE_F32) {
-                f32x4 v = *reinterpret_cast<const f32x4*>(rrow + ((c ^ (r & 15)) << 4));
-                if (EPI == EPI_BIAS_RESID) {
-                  if (RESID_F32) v += rv32[it];
-                  else {
-                    v[0] += bf2f(rv16[it][0] & 0xffffu); v[1] += bf2f(rv16[it][0] >> 16);
-                    v[2] += bf2f(rv16[it][1] & 0xffffu); v[3] += bf2f(rv16[it][1] >> 16);
-                  }
-                }
-                const u32x2 hh = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-                if (OUT_F32) HMI_STORE_OUT(reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + off), v);
-                else HMI_STORE_OUT(reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + off), hh);
-                if (HAS_C2) HMI_STORE_OUT(reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C2) + off), hh);
-              } else {
-                const u32x4 h = *reinterpret_cast<const u32x4*>(rrow + ((c ^ (r & 15)) << 4));
-                HMI_STORE_OUT(reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C) + off), h);
-                if (HAS_C2) HMI_STORE_OUT(reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C2) + off), h);
-              }
-            }
+            const u32x2 hh = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            if (OUT_F32) HMI_STORE_OUT(reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + off), v);
+            else HMI_STORE_OUT(reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + off), hh);
+            if (HAS_C2) HMI_STORE_OUT(reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C2) + off), hh);
+          } else {
+            HMI_STORE_OUT(reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C) + off), got[it]);
+            if (HAS_C2) HMI_STORE_OUT(reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(g.C2) + off), got[it]);
           }
         }
       }
+#undef HMI_PATCH
+#undef HMI_UNIT_ROWS
+#undef HMI_UNIT_RESID
+#undef HMI_UNIT_PUT
     }
 
     // ================= move on to the next tile =================
@@ -515,7 +519,13 @@ void allow_lds() {
 // projection, second FFN GEMM) run with four wavefronts, 3-6 % faster there (no spills in their fp32 epilogue, a
 // long main loop in the second FFN GEMM); bias-only and activation launches keep eight, whose two wavefronts per
 // SIMD overlap each other's epilogue latencies (the first FFN GEMM is 11 % slower with four).
-constexpr int kWavesPlain = 8, kWavesResid = 4;
+#ifndef WP
+#define WP 8
+#endif
+#ifndef WR
+#define WR 4
+#endif
+constexpr int kWavesPlain = WP, kWavesResid = WR;
 }  // namespace
 
 // every instantiation launch_gemm_bf16_p256 can pick
