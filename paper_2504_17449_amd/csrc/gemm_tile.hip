@@ -523,7 +523,7 @@ void init_gemm_tile_kernels() {
   TileS::allow_lds(); TileS2::allow_lds(); TileT2::allow_lds(); TileU2::allow_lds(); TileM::allow_lds(); TileM2::allow_lds(); TileL::allow_lds(); TileXL::allow_lds(); TileF32::allow_lds(); TileF32H::allow_lds(); TileF32Q::allow_lds();
 }
 
-// Which kernel a launch gets.
+// Which kernel a launch gets, if it is not one of a few rows through shared weights (gemm_bf16_thin.hip, asked for first).
 //
 // Few rows per weight matrix (a decode step over many tenants: at most 32 rows per 128-row m-tile on average): the weights
 // are read once and nothing else matters, gemm_bf16_skinny.hip streams them.  A launch whose 32 x 32 items do not fill the
@@ -586,6 +586,8 @@ TileForm tile_form(GemmKernel which, const GemmArgs& g, const Route& rt) {
 
 void launch_gemm_bf16(const GemmArgs& g, const Route& rt, hipStream_t s) {
   if (g.n_rows <= 0 || g.n_mtiles_list[1] <= 0) return;
+  if (rt.identity && gemm_bf16_thin_fits(g.n_rows, g.n_out, g.k, g.epi == EPI_BIAS_GELU, rt.n_cu >= kXcds ? rt.n_cu : 256))
+    return launch_gemm_bf16_thin(g, s);
   GemmArgs a = g;
   const GemmKernel which = pick_gemm_bf16(g, rt);
   const TileForm form = tile_form(which, g, rt);

@@ -102,6 +102,9 @@ void launch_gemm_bf16_p256(const GemmArgs& g, const Route& rt, hipStream_t s);
 // One wavefront per (32 rows, 32 columns) item for launches with few rows per weight matrix; needs
 // k % 64 == 0, n_out % 32 == 0 and which_tiles / n_mtiles naming the list of 128-row m-tiles.
 void launch_gemm_bf16_skinny(const GemmArgs& g, const Route& rt, hipStream_t s);
+// A few rows through weights that all tenants share (the dense route): 16 columns x up to 32 rows a workgroup, one trip to the weights.
+bool gemm_bf16_thin_fits(int n_rows, int n_out, int k, bool gelu, int n_cu);
+void launch_gemm_bf16_thin(const GemmArgs& g, hipStream_t s);
 constexpr int kBf16TileM0 = 256, kBf16TileM1 = 128;  // heights of the two m-tile lists of bf16 pools
 constexpr int kF32TileM = 64;
 
