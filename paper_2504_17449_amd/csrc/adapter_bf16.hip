@@ -35,7 +35,7 @@
 // compute unit 1.4 us.  The chain is kept short: each wavefront finds its unit by itself, from the segments' ends; everything
 // is asked for before anything is waited for; sums over a wavefront stay in registers.  141 rows of two tenants with LayerNorm
 // 13.4 -> 8.3 us, a decode step's 7 rows 13.3 -> 9.2 and 256 rows of 137 tenants 15.8 -> 12.6 (their 27 MB come from HBM),
-// 2 664 rows 15.5 -> 14.0.
+// 2 664 rows 15.5 -> 11.8.
 #include "hmi_kernels.h"
 
 #include "wave.h"
@@ -52,6 +52,7 @@ typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* glb_ptr_t;
 
+constexpr int kXcds = 8;
 constexpr int RT = 32;            // rows of a unit at most
 constexpr int RANK = 64;          // bottleneck width
 constexpr int NTH = 512;
@@ -133,13 +134,18 @@ void adapter_bf16_kernel(AdapterArgs a, Route rt) {
   //      them); the first one writes it down.
   int m = 1, first_row, first_rows, cur_slot;
   if (ONE) {
-    // unit blockIdx.x of the segments' units in order: a lane counts those of four segments
+    // Workgroups are dealt to the XCDs round robin; an XCD's take neighbouring units, so that a tenant's matrices are fetched into one
+    // L2 and not into all eight (2 664 rows of 37 requests 14.1 us -> 11.8; in the general form, where a workgroup has several units
+    // and mostly several tenants, launches got 1 to 5 % longer).
+    const int xcd = blockIdx.x % kXcds, n_wgs = gridDim.x;
+    const int wg = xcd * (n_wgs / kXcds) + min(xcd, n_wgs % kXcds) + (int)blockIdx.x / kXcds;
+    // unit wg of the segments' units in order: a lane counts those of four segments
     int cut[5], units = 0;
 #pragma unroll
     for (int e = 0; e < 5; ++e) cut[e] = rt.seg_tok_off[min(4 * lane + e, a.n_segs)];
 #pragma unroll
     for (int e = 0; e < 4; ++e) units += (cut[e + 1] - cut[e] + a.unit_rows - 1) >> a.unit_shift;
-    const int upto = wave_incl_scan(units), b = blockIdx.x;
+    const int upto = wave_incl_scan(units), b = wg;
     const int l0 = __builtin_ctzll(__ballot(upto > b));       // (the launch has exactly as many workgroups as there are units)
     int u = b - (upto - units), seg = 4 * lane, row0 = 0, rows = 0;
 #pragma unroll
