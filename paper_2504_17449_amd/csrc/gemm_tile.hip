@@ -36,7 +36,7 @@
 //   2 664 rows  QKV 22.1, 15.6 - 17.2, 17.2;  output projection 20.6, 8.2, 7.7;  FFN1 25.6, 21.5, 21.2;  FFN2 71.7, 22.8, 19.9
 //   756 rows    output projection and FFN2 together -, 19.7, 18.7
 //   141 rows    QKV -, 6.0, 5.0;  output projection -, 5.6, 4.2
-//   7 rows      QKV -, 5.5, 4.4;  output projection -, 5.4, 4.3;  FFN1 -, 6.6, 5.2
+//   (7 rows, now gemm_bf16_thin.hip's: QKV -, 5.5, 4.4;  output projection -, 5.4, 4.3;  FFN1 -, 6.6, 5.2)
 // fp32: 1 728 rows of eight tenants, two encoder layers with their attention: products on the vector ALU 1.28 ms, 64 x 64 tiles
 // 0.67, now 0.62;  128 rows of four tenants, an FFN block of d = 64 25.3 us, now 21.3.
 #include "hmi_kernels.h"
@@ -540,8 +540,7 @@ void init_gemm_tile_kernels() {
 // GEMMs of a layer each: the fastest, or behind it by no more than the same kernel's times differ with what the launches
 // before it leave in the caches (14 %, 28 % in the second FFN GEMM of 4 096 rows), but for, us: 1 024 rows QKV 13.2 in
 // 64 x 64 tiles (128 x 128: 11.2); 4 096 rows output projection 12.2 in 64 x 64 (128 x 128: 9.7); FFN1 with GELU of 756 and
-// 1 024 rows 15.8 and 16.8 in 64 x 64 (128 x 64: 13.4 and 13.3), of 640 10.9 (128 x 64 with two lines: 9.4), of 7 rows 5.5 (the
-// split kernel: 4.6).
+// 1 024 rows 15.8 and 16.8 in 64 x 64 (128 x 64: 13.4 and 13.3), of 640 10.9 (128 x 64 with two lines: 9.4).
 // It says nothing about weights that come from HBM or panels that are fetched again, so a launch that gives the
 // persistent kernel's workgroups more than one and a half tiles each is not weighed at all: it was the faster one for all
 // of those (two encoder layers of 177 tenants, 65 536 rows: 3.1 ms, with 128 x 256 tiles where the estimate is lower 3.4).
